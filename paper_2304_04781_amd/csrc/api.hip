@@ -274,7 +274,7 @@ struct wv_ctx {
     int nbd = 0;                 // decode work-groups per state
     long long pipe_grid = 0;     // work-groups per decode launch of the running decode pipeline (0: one launch)
     float* mmpart = nullptr;     // [3][S][P][H][4][2] (min, max) partials of the forward step
-    int H = 1;                   // y sub-tiles per patch
+    int H = 1;                   // partials per patch: y sub-tiles times z sub-chunks
     // Autoencoder stores and decodes run beside the stencil steps: `side` encodes
     // x_j (and decodes e^k for the reverse sweeps), `side2` selects and copies the
     // exception patches of x_j. Forward states rotate through three buffers, so
@@ -405,6 +405,8 @@ StepArgs base_args(const wv_ctx* c)
     a.kc = c->tl.kc;
     a.chunks_adj = c->tl.chunks_adj;
     a.kc_adj = c->tl.kc_adj;
+    a.chunks_mm = c->tl.chunks_mm;
+    a.kc_mm = c->tl.kc_mm;
     a.mm_out = nullptr;
     return a;
 }
@@ -739,21 +741,16 @@ void time_store_level(wv_ctx* c, TimeStore& T, int n)
     WV_HIP(hipEventRecord(T.ev_enc[b], s1));
 }
 
-// store x_n (n = 1..T-1) of every source on the main stream (full storage), or
-// into the autoencoder store L on stream st when given, with the per-patch
-// (min, max) partials mm of the step that wrote it when given
-// (else the encode computes them)
+// store x_n (n = 1..T-1) of every source into the autoencoder store L on stream st when
+// given (else the main stream), with the per-patch (min, max) partials mm of the step that
+// wrote it when given (else the encode computes them). In full storage and in time
+// compression the step itself wrote e^n into the history or its window slot.
 void store_state(wv_ctx* c, LatStore& L, int n, const float* state, hipStream_t st = nullptr,
                  const float* mm = nullptr)
 {
     if (n < 1 || n > c->T - 1) return;
     if (!st) st = c->st;
-    if (c->mode == WV_STORE_FULL) {
-        for (int s = 0; s < c->S; ++s)
-            WV_HIP(hipMemcpyAsync(c->ehist + ((long long)(n - 1) * c->S + s) * c->N, state + s * 4 * c->N,
-                                  sizeof(float) * c->N, hipMemcpyDeviceToDevice, c->st));
-    } else if (is_time(c->mode)) {
-        (void)state;  // the forward step wrote e^n into its window slot
+    if (is_time(c->mode)) {
         time_store_level(c, c->ts, n);
     } else if (is_ae(c->mode)) {
         encode_state_into(c, L, n, state, st, mm);
@@ -1055,8 +1052,10 @@ float* forward_sweep(wv_ctx* c, float* traces, const std::vector<int>* snap, flo
         }
         float* mm = (ae && store) ? c->mmpart + (j % 3) * mm_stride : nullptr;
         // time compression: the step writes e^j straight into its window slot; the
-        // buffer held window w - 2, whose compression must have read it
-        float* ew = is_time(c->mode) && store ? time_slot(c, c->ts, j) : nullptr;
+        // buffer held window w - 2, whose compression must have read it. Full storage: into
+        // the history (a copy after each step cost the 128 x 128 solve 1.6 us of its 5)
+        float* ew = !store ? nullptr : is_time(c->mode) ? time_slot(c, c->ts, j)
+                    : c->mode == WV_STORE_FULL ? c->ehist + (long long)(j - 1) * c->S * c->N : nullptr;
         fwd_step(c, cur, out, n, traces, mm, ew);
         if (store) {
             if (ae)
@@ -1244,7 +1243,7 @@ int wv_create(const wv_grid* grid, const int32_t* h_src, const int32_t* h_rec, v
         check_pts(src, "source");
         check_pts(rec, "receiver");
         build_tables(c.get());
-        c->tl = make_tiling(g.nz, g.ny, g.nx, rec);
+        c->tl = make_tiling(g.nz, g.ny, g.nx, g.nsrc, rec);
         c->src_kji = dev_alloc<int>(src.size());
         WV_HIP(hipMemcpy(c->src_kji, src.data(), sizeof(int) * src.size(), hipMemcpyHostToDevice));
         const float one = 1.0f;
@@ -1378,7 +1377,7 @@ void set_storage_mode(wv_ctx* c, int mode, int32_t n_checkpoints, ae_net* ae, in
         WV_REQUIRE(c->budget <= 0 || bytes <= c->budget, WV_ENOMEM, "latent store exceeds the memory budget");
         alloc_latstore(c, c->fs, mode, K);
         c->K = K;
-        c->H = 8 / c->tl.by;
+        c->H = 8 / c->tl.by * (c->tl.kc_mm < 8 ? 8 / c->tl.kc_mm : 1);
         c->mmpart = dev_alloc<float>((size_t)3 * c->S * c->P * c->H * 8);
         if (guard_tol > 0.0) {
             c->gbuf = dev_alloc<float>((size_t)c->S * c->N);
@@ -1738,7 +1737,8 @@ float* inc_forward_sweep(wv_ctx* c, const float* cdev, const float* dc, const st
         } else {
             en = load_e(c, n, &stride, +1);
         }
-        float* dew = keep_time && n + 1 <= c->T - 1 ? time_slot(c, c->tds, n + 1) : nullptr;
+        float* dew = n + 1 > c->T - 1 ? nullptr : keep_time ? time_slot(c, c->tds, n + 1)
+                     : keep_full ? c->dehist + (long long)n * c->S * c->N : nullptr;
         if (dasync) {
             din = c->incb[n % 3];
             dout = c->incb[(n + 1) % 3];
@@ -1763,10 +1763,6 @@ float* inc_forward_sweep(wv_ctx* c, const float* cdev, const float* dc, const st
                 store_state(c, c->ds, j, din, c->st, dmmp);
             }
         }
-        if (keep_full && n + 1 <= c->T - 1)
-            for (int s = 0; s < c->S; ++s)
-                WV_HIP(hipMemcpyAsync(c->dehist + ((long long)n * c->S + s) * c->N, din + s * 4 * c->N,
-                                      sizeof(float) * c->N, hipMemcpyDeviceToDevice, c->st));
         if (ckpt) {
             float* out = (*snap)[n + 1] > 0 ? c->slot_ptr((*snap)[n + 1]) : other_work(c, cur);
             fwd_step(c, cur, out, n, nullptr);

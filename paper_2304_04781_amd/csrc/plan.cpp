@@ -16,6 +16,16 @@ ChunkPlan plan_chunks(int nz, int tiles, int target)
     return ChunkPlan{kc, (nz + kc - 1) / kc};
 }
 
+ChunkPlan fill_round(const ChunkPlan& p, int nz, long long wgs, int slots)
+{
+    WV_REQUIRE(p.kc >= 1 && p.chunks >= 1 && nz >= 1 && wgs >= 1 && slots >= 1, WV_EINVAL,
+               "fill_round: sizes must be >= 1");
+    const int chunks = (int)std::min<long long>(nz, slots / wgs);
+    if (chunks <= p.chunks) return p;
+    const int kc = (nz + chunks - 1) / chunks;
+    return ChunkPlan{kc, (nz + kc - 1) / kc};
+}
+
 void bucket_receivers(int nz, int bx, int by, int tiles_x, int tiles_y, const std::vector<int>& rec_kji,
                       std::vector<int>& ptr, std::vector<RecEnt>& ent)
 {

@@ -48,6 +48,10 @@ struct ChunkPlan {
     int kc, chunks;
 };
 ChunkPlan plan_chunks(int nz, int tiles, int target);
+// p split further while wgs work-groups per chunk times the chunks stay within one round
+// of `slots` resident work-groups (at most nz chunks, of any number of levels); p itself
+// when it already reaches the round
+ChunkPlan fill_round(const ChunkPlan& p, int nz, long long wgs, int slots);
 
 // One receiver in its (y, x) tile: depth k, cell within the tile's plane
 // (j % by) bx + (i % bx), receiver number r. Laid out as the device's int4.

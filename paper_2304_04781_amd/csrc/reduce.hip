@@ -224,16 +224,24 @@ __global__ void range_kernel(const float* __restrict__ x, long long n, double* _
     }
 }
 
-__global__ void range_finalize(const double* __restrict__ partial, int nb, double* __restrict__ out)
+// one wave: lane l takes partials l, l + 64, ... (one thread over 1024 partials took 120 us)
+__global__ void __launch_bounds__(64) range_finalize(const double* __restrict__ partial, int nb, double* __restrict__ out)
 {
+    double lo = INFINITY, hi = -INFINITY, nan = 0.0;
+    for (int q = threadIdx.x; q < nb; q += 64) {
+        lo = fmin(lo, partial[3 * q]);
+        hi = fmax(hi, partial[3 * q + 1]);
+        nan += partial[3 * q + 2];
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = fmin(lo, __shfl_xor(lo, o, 64));
+        hi = fmax(hi, __shfl_xor(hi, o, 64));
+        nan += __shfl_xor(nan, o, 64);
+    }
     if (threadIdx.x == 0) {
-        double lo = INFINITY, hi = -INFINITY, nan = 0.0;
-        for (int q = 0; q < nb; ++q) {
-            lo = fmin(lo, partial[3 * q]);
-            hi = fmax(hi, partial[3 * q + 1]);
-            nan += partial[3 * q + 2];
-        }
-        out[0] = lo; out[1] = hi; out[2] = nan;
+        out[0] = lo;
+        out[1] = hi;
+        out[2] = nan;
     }
 }
 

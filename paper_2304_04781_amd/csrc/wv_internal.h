@@ -34,6 +34,7 @@ struct Tiling {
     int bx = 64, by = 8;
     int tiles_x = 0, tiles_y = 0, chunks_z = 0, kc = 0;  // forward / incremental chunks
     int chunks_adj = 0, kc_adj = 0;                       // adjoint chunks
+    int chunks_mm = 0, kc_mm = 0;                         // chunks of the steps that write (min, max) partials
     // receivers of tile t at level k: rec_ent[rec_ptr[t (nz + 1) + k] ..
     // rec_ptr[t (nz + 1) + k + 1]), sorted by (local cell, receiver)
     int* rec_ptr = nullptr;   // [tiles][nz + 1]
@@ -82,13 +83,16 @@ struct StepArgs {
     long long enstride;
     int tiles_x, tiles_y, chunks_z, kc;
     int chunks_adj, kc_adj;
-    // forward only: per-(patch, y sub-tile) min/max of the 4 new fields,
-    // [S][P][8/BY][4][2] = (min, max), written when non-null (3D, grid of 8^3 patches)
+    int chunks_mm, kc_mm;
+    // forward only: per-(patch, y sub-tile, z sub-chunk) min/max of the 4 new fields,
+    // [S][P][8/BY][mm_sub][4][2] = (min, max), written when non-null (3D, grid of 8^3
+    // patches); mm_sub = z chunks per patch layer
     float* mm_out;
+    int mm_sub;
 };
 
 void launch_step(int mode, bool has_y, const StepArgs& a, int nsrc, hipStream_t st);
-Tiling make_tiling(int nz, int ny, int nx, const std::vector<int>& rec_kji);
+Tiling make_tiling(int nz, int ny, int nx, int nsrc, const std::vector<int>& rec_kji);
 void free_tiling(Tiling& t);
 
 // ---- reductions / elementwise -------------------------------------------------------
