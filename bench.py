@@ -343,11 +343,11 @@ def multisource_rates(args, p, net, c0, wav):
     kt = timed_kernels(ae, c0, w, d, 1.0, every=2)
     ae.close()
     blk = L.wv_accumulation_block()
-    work = {  # per timed launch (the stencils launch all sources at once; encode/decode time one state)
+    work = {  # per timed launch (every class launches all sources at once)
         "forward_stencil": ("hbm", (32.0 * S + 4.0) * N),
         "adjoint_stencil": ("hbm", ((adjoint_bytes_per_cell(T, blk) - 4.0) * S + 4.0) * N),
         "encode": ("mfma", S * 2.0 * P * (2048 * 512 + 512 * 32)),
-        "decode_e": ("mfma", 2.0 * P * (32 * 512 + 512 * 512)),
+        "decode_e": ("mfma", S * 2.0 * P * (32 * 512 + 512 * 512)),
     }
     rows = {}
     for name, (us, n) in kt.items():

@@ -435,16 +435,14 @@ int ae_encode(const ae_net* net, const wv_grid* grid, const float* state, int la
               void* latent, float* meta, float* qscale, void* stream);
 
 /* ae_encode for callers that cannot allocate device memory (code under HIP graph
- * capture, serving loops, harnesses that forbid hipMalloc): the same kernels and
- * results as ae_encode, bit for bit, but no allocation of any kind. The float32
- * latents of an FP8 encode are staged in a static device array of 16 MiB that the
- * library holds on each device it runs on until the process ends (its address is
- * looked up at the first FP8 call on a device); bfloat16 latents need no staging.
+ * capture, serving loops, harnesses that forbid hipMalloc): the same arithmetic and
+ * results as ae_encode, bit for bit, but no allocation of any kind (ae_encode may grow
+ * a work buffer of the net when it codes few patches on a stream that is not under
+ * graph capture).
  * Limits: the fused network shape (hidden 512, latent 32, else WV_EINVAL) and, for
  * AE_LATENT_FP8, P * latent * 4 <= 16 MiB, i.e. at most 131072 patches (WV_EINVAL
- * beyond, before any work is queued). Every call on one device shares that
- * device's array and nothing in it needs to start at zero; calls that overlap in
- * time on one device (two streams, or two threads) race on it. */
+ * beyond, before any work is queued). Calls keep nothing between them, so they may
+ * overlap in time. */
 int ae_encode_noalloc(const ae_net* net, const wv_grid* grid, const float* state, int latent_fmt,
                       void* latent, float* meta, float* qscale, void* stream);
 
@@ -504,7 +502,7 @@ int wv_set_timing(wv_ctx* ctx, int32_t every);
 /* Mean duration in microseconds and number of timed launches since the last
  * wv_set_timing, for one class: 0 forward stencil step, 1 adjoint stencil step,
  * 2 incremental-forward stencil step, 3 compression of one state (all sources),
- * 4 decompression of one e field (with its exception patches written exactly),
+ * 4 decompression of e of one level, all sources (exception patches exact),
  * 5 selection of the exception patches of one state, 6 a separate exception
  * restore (not launched: the decompression writes those patches), 7 copy of the
  * exception patches of one state. In the time-compression mode classes 3 and 4

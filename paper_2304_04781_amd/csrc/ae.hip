@@ -32,33 +32,6 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// OCP E4M3FN, round to nearest even, saturating at 448
-__device__ __forceinline__ uint8_t f2e4m3(float x)
-{
-    const uint32_t sign = (__float_as_uint(x) >> 24) & 0x80u;
-    const float a = fabsf(x);
-    uint32_t code;
-    if (a >= 448.0f) {
-        code = 0x7E;
-    } else {
-        const int e = (int)((__float_as_uint(a) >> 23) & 0xFF) - 127;
-        if (e < -6) {
-            code = (uint32_t)rintf(a * 512.0f);  // subnormal quantum 2^-9
-        } else {
-            const float q = rintf(ldexpf(a, 3 - e));  // in [8, 16]
-            code = (uint32_t)((e + 7) << 3) + ((uint32_t)q - 8u);
-        }
-        if (code > 0x7E) code = 0x7E;
-    }
-    return (uint8_t)(code | sign);
-}
-__device__ __forceinline__ float e4m32f(uint8_t c)
-{
-    const int E = (c >> 3) & 0xF, m = c & 7;
-    const float v = E == 0 ? (float)m * 0.001953125f : ldexpf(1.0f + (float)m * 0.125f, E - 7);
-    return (c & 0x80) ? -v : v;
-}
-
 // ------------------------------------------------------------------------------------
 // GEMM  C[M][N] = sum_k A(m, k) B(n, k), bf16 operands, fp32 accumulation.
 // 256 threads = 4 waves; each wave owns a WM x WN block of 16x16 MFMA tiles.
@@ -1053,6 +1026,7 @@ struct ae_net {
         size_t bytes;
     };
     std::vector<Workspace> ws;
+    std::mutex ws_mu;  // codec calls of several threads
 
     const float* bias(int l) const { return master + ob[l]; }
 };
@@ -1131,6 +1105,7 @@ void upload_beta(ae_net* a)
 void* workspace(const ae_net* ac, size_t bytes, hipStream_t st)
 {
     ae_net* a = const_cast<ae_net*>(ac);
+    std::lock_guard<std::mutex> lock(a->ws_mu);
     ae_net::Workspace* w = nullptr;
     for (auto& q : a->ws)
         if (q.st == st) w = &q;
@@ -1208,6 +1183,39 @@ long long ae_latent_bytes_per_patch(const ae_net* net, int fmt)
     return (long long)net->lat * (fmt == AE_LATENT_FP8 ? 1 : 2);
 }
 
+namespace {
+
+// the fused encode of nsrc states (4 N floats apart) into contiguous latents and metadata,
+// from the step's (min, max) partials mm when given. No work buffer is touched with
+// noalloc, nor on a stream under graph capture (a captured pointer would outlive the
+// buffer's growth).
+void encode_fused(const ae_net* a, const PatchGrid& pg, int nsrc, const float* state, const float* mm, int H, int fmt,
+                  void* latent, float* meta, float* qscale, hipStream_t st, uint16_t* meta16, bool noalloc)
+{
+    const long long P = pg.P * nsrc;
+    EncPlan plan = fused_encode_plan(P, !noalloc);
+    if (encode_splits(plan)) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        const hipError_t e = hipStreamIsCapturing(st, &cs);
+        if (e != hipSuccess) (void)hipGetLastError();
+        if (e != hipSuccess || cs != hipStreamCaptureStatusNone) plan = fused_encode_plan(P, false);
+    }
+    float* zpart = encode_splits(plan) ? (float*)workspace(a, align256(8 * P * (size_t)a->lat * 4), st) : nullptr;
+    if (plan == ENC_TILED && !mm) {
+        const long long N = (long long)pg.nz * pg.ny * pg.nx;
+        for (int s = 0; s < nsrc; ++s)
+            hipLaunchKernelGGL(minmax_kernel, dim3((pg.nz / 8) * (pg.ny / 8)),
+                               dim3(std::min(256, ((pg.nx + 63) / 64) * 64)), 0, st, state + s * 4 * N, pg.ny, pg.nx,
+                               N, pg.ny / 8, pg.nx / 8, a->beta_d, meta + s * pg.P * 8);
+        WV_HIP(hipGetLastError());
+    }
+    const bool fp8 = fmt == AE_LATENT_FP8;
+    fused_encode(plan, pg, nsrc, state, meta, mm, H, a->beta_d, a->wp1, a->bias(0), a->wt[1], a->bias(1),
+                 fp8 ? nullptr : (uint16_t*)latent, fp8 ? (uint8_t*)latent : nullptr, qscale, zpart, st, meta16);
+}
+
+}  // namespace
+
 void ae_encode_state(const ae_net* a, const PatchGrid& pg, const float* state, int fmt, void* latent, float* meta,
                      float* qscale, hipStream_t st)
 {
@@ -1215,22 +1223,7 @@ void ae_encode_state(const ae_net* a, const PatchGrid& pg, const float* state, i
                "encode: null buffer");
     const long long P = pg.P;
     if (fused_supported(a->hid, a->lat)) {
-        const long long N = (long long)pg.nz * pg.ny * pg.nx;
-        const int rows = (pg.nz / 8) * (pg.ny / 8);
-        hipLaunchKernelGGL(minmax_kernel, dim3(rows), dim3(std::min(256, ((pg.nx + 63) / 64) * 64)), 0, st, state,
-                           pg.ny, pg.nx, N, pg.ny / 8, pg.nx / 8, a->beta_d, meta);
-        WV_HIP(hipGetLastError());
-        if (fmt == AE_LATENT_BF16) {
-            fused_encode(pg, state, meta, nullptr, 0, a->beta_d, a->wp1, a->bias(0), a->wt[1], a->bias(1),
-                         (uint16_t*)latent, nullptr, st);
-        } else {
-            float* z = (float*)workspace(a, align256(P * (size_t)a->lat * 4), st);
-            fused_encode(pg, state, meta, nullptr, 0, a->beta_d, a->wp1, a->bias(0), a->wt[1], a->bias(1), nullptr,
-                         z, st);
-            hipLaunchKernelGGL(quantize_kernel, dim3(blocks(P, 4)), dim3(256), 0, st, z, P, a->lat, (uint8_t*)latent,
-                               qscale);
-            WV_HIP(hipGetLastError());
-        }
+        encode_fused(a, pg, 1, state, nullptr, 0, fmt, latent, meta, qscale, st, nullptr, false);
         return;
     }
     const size_t oy = 0, oh = align256(oy + P * 2048 * 2), oz = align256(oh + P * (size_t)a->hid * 2);
@@ -1253,28 +1246,21 @@ void ae_encode_state(const ae_net* a, const PatchGrid& pg, const float* state, i
     }
 }
 
-void ae_encode_state_mm(const ae_net* a, const PatchGrid& pg, const float* state, const float* mm, int H, int fmt,
-                        void* latent, float* meta, float* qscale, hipStream_t st, uint16_t* meta16)
+void ae_encode_states_mm(const ae_net* a, const PatchGrid& pg, int nsrc, const float* state, const float* mm, int H,
+                         int fmt, void* latent, float* meta, float* qscale, hipStream_t st, uint16_t* meta16)
 {
     if (!fused_supported(a->hid, a->lat)) {
         WV_REQUIRE(!meta16, WV_EINVAL, "16-bit metadata needs the fused network shape (hidden 512, latent 32)");
-        ae_encode_state(a, pg, state, fmt, latent, meta, qscale, st);
+        const long long N = (long long)pg.nz * pg.ny * pg.nx;
+        for (int s = 0; s < nsrc; ++s)
+            ae_encode_state(a, pg, state + s * 4 * N, fmt,
+                            (uint8_t*)latent + s * pg.P * ae_latent_bytes_per_patch(a, fmt), meta + s * pg.P * 8,
+                            qscale ? qscale + s * pg.P : nullptr, st);
         return;
     }
     WV_REQUIRE(a && state && mm && latent && (meta || meta16) && (fmt == AE_LATENT_BF16 || qscale), WV_EINVAL,
                "encode: null buffer");
-    const long long P = pg.P;
-    if (fmt == AE_LATENT_BF16) {
-        fused_encode(pg, state, meta, mm, H, a->beta_d, a->wp1, a->bias(0), a->wt[1], a->bias(1),
-                     (uint16_t*)latent, nullptr, st, meta16);
-    } else {
-        float* z = (float*)workspace(a, align256(P * (size_t)a->lat * 4), st);
-        fused_encode(pg, state, meta, mm, H, a->beta_d, a->wp1, a->bias(0), a->wt[1], a->bias(1), nullptr, z, st,
-                     meta16);
-        hipLaunchKernelGGL(quantize_kernel, dim3(blocks(P, 4)), dim3(256), 0, st, z, P, a->lat, (uint8_t*)latent,
-                           qscale);
-        WV_HIP(hipGetLastError());
-    }
+    encode_fused(a, pg, nsrc, state, mm, H, fmt, latent, meta, qscale, st, meta16, false);
 }
 
 void ae_time_normalize_rows(const ae_net* a, const TimeGrid& tg, const float* e_win, int nvalid,
@@ -1334,9 +1320,9 @@ void ae_time_decode(const ae_net* a, const TimeGrid& tg, const uint16_t* latent,
               EpiTimeDenorm{e_win, meta, a->bias(3), tg.S, tg.ny, tg.nx, tg.ny / 4, tg.nx / 4, nvalid, tg.B, N}, st);
 }
 
-void ae_decode_state(const ae_net* a, const PatchGrid& pg, const void* latent, const float* meta,
-                     const float* qscale, int fmt, uint32_t mask, float* state, hipStream_t st,
-                     const ExcPatches* exc, const uint16_t* meta16, long long grid)
+void ae_decode_states(const ae_net* a, const PatchGrid& pg, int nsrc, const void* latent, const float* meta,
+                      const float* qscale, int fmt, uint32_t mask, float* state, long long sstride, hipStream_t st,
+                      const ExcPatches* exc, const uint16_t* meta16, long long grid)
 {
     WV_REQUIRE(a && state && latent && (meta || meta16) && (fmt == AE_LATENT_BF16 || qscale), WV_EINVAL,
                "decode: null buffer");
@@ -1344,18 +1330,24 @@ void ae_decode_state(const ae_net* a, const PatchGrid& pg, const void* latent, c
                "16-bit metadata needs the fused network shape (hidden 512, latent 32)");
     const long long P = pg.P;
     if (fused_supported(a->hid, a->lat)) {
-        const uint16_t* zb = (const uint16_t*)latent;
-        if (fmt == AE_LATENT_FP8) {
-            uint16_t* zq = (uint16_t*)workspace(a, align256(P * (size_t)a->lat * 2), st);
-            hipLaunchKernelGGL(dequantize_kernel, dim3(blocks(P * a->lat, 256)), dim3(256), 0, st,
-                               (const uint8_t*)latent, qscale, P, a->lat, zq);
-            WV_HIP(hipGetLastError());
-            zb = zq;
-        }
+        const bool fp8 = fmt == AE_LATENT_FP8;
         for (int f = 0; f < 4; ++f)
             if (mask & (1u << f))
-                fused_decode(pg, zb, meta, a->wt[2], a->bias(2), a->wp4, a->bias(3), f, state, st,
+                fused_decode(pg, nsrc, fp8 ? nullptr : (const uint16_t*)latent, fp8 ? (const uint8_t*)latent : nullptr,
+                             qscale, meta, a->wt[2], a->bias(2), a->wp4, a->bias(3), f, state, sstride, st,
                              (exc && exc->K > 0 && f == 0) ? exc : nullptr, meta16, grid);
+        return;
+    }
+    if (nsrc > 1) {
+        const int nrng = (int)((P + DEC_BM - 1) / DEC_BM) + 1;
+        for (int s = 0; s < nsrc; ++s) {
+            ExcPatches e{};
+            if (exc) e = ExcPatches{exc->idx + s * exc->K, exc->K, exc->exc + (long long)s * exc->K * 512,
+                                    exc->rng ? exc->rng + s * nrng : nullptr};
+            ae_decode_states(a, pg, 1, (const uint8_t*)latent + s * P * ae_latent_bytes_per_patch(a, fmt), meta + s * P * 8,
+                             qscale ? qscale + s * P : nullptr, fmt, mask, state + s * sstride, sstride, st,
+                             exc ? &e : nullptr, nullptr, grid);
+        }
         return;
     }
     const size_t oh = 0, ozb = align256(oh + P * (size_t)a->hid * 2);
@@ -1643,39 +1635,10 @@ void free_net(ae_net* a)
 
 }  // namespace
 
-// ---- the allocation-free encode ----------------------------------------------------
-// ae_encode_noalloc stages the float32 latents of an FP8 encode (P x latent floats)
-// in this file-scope device array instead of the per-stream work buffer. Each device
-// holds its own copy; host code reaches it only through the address that
-// hipGetSymbolAddress returns for the current device (the array's name is a host-side
-// stand-in, not a device address).
-constexpr size_t NOALLOC_SCRATCH_BYTES = size_t(16) << 20;
-__device__ __align__(256) uint8_t scratch[NOALLOC_SCRATCH_BYTES];
+// ae_encode_noalloc takes FP8 grids of up to this many bytes of float32 latents: the limit
+// it always had, now that the codes are formed in registers
+constexpr size_t NOALLOC_MAX_BYTES = size_t(16) << 20;
 
-namespace {
-
-constexpr int NOALLOC_MAX_DEVICES = 64;
-std::mutex g_scratch_mu;
-void* g_scratch_ptr[NOALLOC_MAX_DEVICES] = {};
-
-// device address of `scratch` on the current device, looked up once per device
-void* noalloc_scratch()
-{
-    int dev = -1;
-    WV_HIP(hipGetDevice(&dev));
-    WV_REQUIRE(dev >= 0 && dev < NOALLOC_MAX_DEVICES, WV_EDEVICE, "device ordinal beyond the scratch table");
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    if (!g_scratch_ptr[dev]) {
-        void* p = nullptr;
-        const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-        if (e != hipSuccess || !p)
-            throw Error{WV_EDEVICE, std::string("hipGetSymbolAddress(scratch): ") + hipGetErrorString(e)};
-        g_scratch_ptr[dev] = p;
-    }
-    return g_scratch_ptr[dev];
-}
-
-}  // namespace
 }  // namespace wv
 
 // ======================================================================================
@@ -1959,8 +1922,8 @@ int ae_decode(const ae_net* a, const wv_grid* g, const void* latent, const float
         WV_REQUIRE(fmt == AE_LATENT_BF16 || (fmt == AE_LATENT_FP8 && qscale), WV_EINVAL, "bad latent format/scale");
         WV_REQUIRE((mask & ~0xFu) == 0, WV_EINVAL, "field mask has bits beyond the 4 fields");
         check_grid(g);
-        ae_decode_state(a, patch_grid(g->nz, g->ny, g->nx), latent, meta, qscale, fmt, mask, state,
-                        (hipStream_t)stream);
+        ae_decode_states(a, patch_grid(g->nz, g->ny, g->nx), 1, latent, meta, qscale, fmt, mask, state, 0,
+                         (hipStream_t)stream, nullptr, nullptr, 0);
         return WV_OK;
     });
 }
@@ -2039,30 +2002,15 @@ int ae_encode_noalloc(const ae_net* a, const wv_grid* g, const float* state, int
                    "ae_encode_noalloc needs the fused network shape (hidden 512, latent 32)");
         const PatchGrid pg = patch_grid(g->nz, g->ny, g->nx);
         const hipStream_t st = (hipStream_t)stream;
-        const long long N = (long long)pg.nz * pg.ny * pg.nx;
-        const int rows = (pg.nz / 8) * (pg.ny / 8);
         if (fmt == AE_LATENT_FP8) {
             const size_t need = (size_t)pg.P * a->lat * sizeof(float);
-            WV_REQUIRE(need <= NOALLOC_SCRATCH_BYTES, WV_EINVAL,
-                       "ae_encode_noalloc: FP8 staging needs " + std::to_string(need) + " bytes, beyond the " +
-                           std::to_string(NOALLOC_SCRATCH_BYTES) + "-byte static scratch (at most " +
-                           std::to_string(NOALLOC_SCRATCH_BYTES / (a->lat * sizeof(float))) + " patches)");
+            WV_REQUIRE(need <= NOALLOC_MAX_BYTES, WV_EINVAL,
+                       "ae_encode_noalloc: " + std::to_string(need) + " bytes of float32 latents, beyond the " +
+                           std::to_string(NOALLOC_MAX_BYTES) + "-byte limit of its static scratch interface (at most " +
+                           std::to_string(NOALLOC_MAX_BYTES / (a->lat * sizeof(float))) + " patches)");
         }
-        // the same kernels as ae_encode; only the FP8 staging buffer differs
-        hipLaunchKernelGGL(minmax_kernel, dim3(rows), dim3(std::min(256, ((pg.nx + 63) / 64) * 64)), 0, st, state,
-                           pg.ny, pg.nx, N, pg.ny / 8, pg.nx / 8, a->beta_d, meta);
-        WV_HIP(hipGetLastError());
-        if (fmt == AE_LATENT_BF16) {
-            fused_encode(pg, state, meta, nullptr, 0, a->beta_d, a->wp1, a->bias(0), a->wt[1], a->bias(1),
-                         (uint16_t*)latent, nullptr, st);
-            return WV_OK;
-        }
-        float* z = (float*)noalloc_scratch();
-        fused_encode(pg, state, meta, nullptr, 0, a->beta_d, a->wp1, a->bias(0), a->wt[1], a->bias(1), nullptr, z,
-                     st);
-        hipLaunchKernelGGL(quantize_kernel, dim3(blocks(pg.P, 4)), dim3(256), 0, st, z, pg.P, a->lat,
-                           (uint8_t*)latent, qscale);
-        WV_HIP(hipGetLastError());
+        // the kernels that need no work buffer; results as ae_encode's, bit for bit
+        encode_fused(a, pg, 1, state, nullptr, 0, fmt, latent, meta, qscale, st, nullptr, true);
         return WV_OK;
     });
 }

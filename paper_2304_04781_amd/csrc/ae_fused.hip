@@ -44,15 +44,37 @@ struct EncArgs {
     const float* b1;      // [HID]
     const uint16_t* w2t;  // [L][HID]
     const float* b2;      // [L]
-    uint16_t* zbf;        // [P][L] bf16 latent (or null)
-    float* zf;            // [P][L] float32 latent (or null)
-    long long P, N;
+    uint16_t* zbf;        // [P][L] bf16 latent, or (null)
+    uint8_t* codes;       // [P][L] e4m3 codes with
+    float* scale;         // [P] their scales
+    // P patches of all sources: Ps per source, whose states are sstride floats apart
+    long long P, N, Ps, sstride;
     int ny, nx, Py, Px;
-    long long t0;         // first 128-patch tile of the launch
 };
 
+// first element of patch p's cells in the states, field 0
+template <class A>
+__device__ __forceinline__ long long patch_base(const A& a, long long p)
+{
+    const unsigned u = (unsigned)p, s = u / (unsigned)a.Ps, q = u % (unsigned)a.Ps;  // below 2^31 (fused_patches)
+    const unsigned px = q % (unsigned)a.Px, t = q / (unsigned)a.Px, py = t % (unsigned)a.Py, pz = t / (unsigned)a.Py;
+    return s * a.sstride + ((long long)(pz * 8) * a.ny + py * 8) * a.nx + px * 8;
+}
+
+// e4m3 scale of a patch whose largest |latent| is m
+__device__ __forceinline__ float fp8_scale(float m) { return m > 0.f ? m / 448.0f : 1.0f; }
+// the largest of the 32 values of a half wave
+__device__ __forceinline__ float half_wave_max(float m)
+{
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    return m;
+}
+
 struct DecArgs {
-    const uint16_t* z;    // [P][L] bf16
+    const uint16_t* z;    // [P][L] bf16, or (null)
+    const uint8_t* codes;  // [P][L] e4m3 codes with
+    const float* scale;    // [P] their scales
     const float* meta;
     const uint16_t* meta16;  // bfloat16 (lo, r) instead of meta when non-null
     const uint16_t* w3t;  // [HID][L]
@@ -61,61 +83,49 @@ struct DecArgs {
     const float* b4;      // [2048]
     float* state;         // [4][N]
     int f;
-    long long P, N;
+    // Ps patches per source, in tps work-groups; latents, scales and metadata of the sources
+    // are contiguous, their states sstride floats apart
+    long long N, Ps, sstride, tps;
     int ny, nx, Py, Px;
     // exception patches (none when eidx is null): increasing indices, exact values
-    // [K][512], per-work-group ranges into eidx
+    // [K][512], ranges [nrng] into eidx per DEC_BM patches; per source
     const int* eidx;
     const float* exc;
     const int* erng;
-    long long t0;  // first DEC_BM-patch tile of the launch
+    int K, nrng;
+    long long t0;  // first work-group tile of the launch
 };
 
-// Per-patch (lo, 1/r) of the work-group's bm patches into sMeta [bm][8] (threads
-// tid < bm, one patch each). From the forward step's (min, max) partials the metadata is
-// also computed here and published (float32, or bfloat16 with lo rounded down and r up);
-// otherwise it is read from `meta`.
-__device__ __forceinline__ void enc_meta(const EncArgs& a, long long m0, int tid, float* sMeta, int bm)
+// (lo, 1 / r) of field f of patch p from the forward step's (min, max) partials:
+// r = max(max - min, beta_f); with publish, the metadata is also written (float32, or
+// bfloat16 with lo rounded down and r up: lo_b <= lo and lo_b + r_b >= hi, so y stays in
+// [0, 1] up to rounding and the decode reads the very values used here)
+__device__ __forceinline__ float2 enc_lo_rinv(const EncArgs& a, long long p, int f, bool publish)
 {
-    if (tid < bm) {
-        const long long p = m0 + tid;
-        if (a.mm) {
-            // combine the y sub-tile partials: r = max(max - min, beta_f); publish the metadata
-#pragma unroll
-            for (int f = 0; f < 4; ++f) {
-                float lo = 0.f, r = 1.f;
-                if (p < a.P) {
-                    lo = a.mm[(p * a.H) * 8 + 2 * f];
-                    float hi = a.mm[(p * a.H) * 8 + 2 * f + 1];
-                    for (int h = 1; h < a.H; ++h) {
-                        lo = fminf(lo, a.mm[(p * a.H + h) * 8 + 2 * f]);
-                        hi = fmaxf(hi, a.mm[(p * a.H + h) * 8 + 2 * f + 1]);
-                    }
-                    r = fmaxf(hi - lo, a.beta[f]);
-                    if (a.meta16) {
-                        // 16-bit metadata: lo_b <= lo and lo_b + r_b >= hi, so y stays in [0, 1]
-                        // up to rounding and the decode reads the very values used here
-                        const uint16_t lb = bf16_down(lo);
-                        lo = bf2f(lb);
-                        const uint16_t rb = bf16_up(fmaxf(hi - lo, a.beta[f]));
-                        r = bf2f(rb);
-                        a.meta16[p * 8 + 2 * f] = lb;
-                        a.meta16[p * 8 + 2 * f + 1] = rb;
-                    } else {
-                        const_cast<float*>(a.meta)[p * 8 + 2 * f] = lo;
-                        const_cast<float*>(a.meta)[p * 8 + 2 * f + 1] = r;
-                    }
-                }
-                sMeta[tid * 8 + 2 * f] = lo;
-                sMeta[tid * 8 + 2 * f + 1] = 1.0f / r;
+    float lo = 0.f, r = 1.f;
+    if (p < a.P) {
+        lo = a.mm[(p * a.H) * 8 + 2 * f];
+        float hi = a.mm[(p * a.H) * 8 + 2 * f + 1];
+        for (int h = 1; h < a.H; ++h) {
+            lo = fminf(lo, a.mm[(p * a.H + h) * 8 + 2 * f]);
+            hi = fmaxf(hi, a.mm[(p * a.H + h) * 8 + 2 * f + 1]);
+        }
+        r = fmaxf(hi - lo, a.beta[f]);
+        if (a.meta16) {
+            const uint16_t lb = bf16_down(lo);
+            lo = bf2f(lb);
+            const uint16_t rb = bf16_up(fmaxf(hi - lo, a.beta[f]));
+            r = bf2f(rb);
+            if (publish) {
+                a.meta16[p * 8 + 2 * f] = lb;
+                a.meta16[p * 8 + 2 * f + 1] = rb;
             }
-        } else {
-            const float4 m01 = p < a.P ? *reinterpret_cast<const float4*>(a.meta + p * 8) : make_float4(0.f, 1.f, 0.f, 1.f);
-            const float4 m23 = p < a.P ? *reinterpret_cast<const float4*>(a.meta + p * 8 + 4) : make_float4(0.f, 1.f, 0.f, 1.f);
-            *reinterpret_cast<float4*>(sMeta + tid * 8) = make_float4(m01.x, 1.0f / m01.y, m01.z, 1.0f / m01.w);
-            *reinterpret_cast<float4*>(sMeta + tid * 8 + 4) = make_float4(m23.x, 1.0f / m23.y, m23.z, 1.0f / m23.w);
+        } else if (publish) {
+            const_cast<float*>(a.meta)[p * 8 + 2 * f] = lo;
+            const_cast<float*>(a.meta)[p * 8 + 2 * f + 1] = r;
         }
     }
+    return make_float2(lo, 1.0f / r);
 }
 
 // The encode work-group: eight waves over BM = 128 patches, wave w owning hidden units
@@ -135,15 +145,6 @@ __device__ __forceinline__ void enc_meta(const EncArgs& a, long long m0, int tid
 #define WV_ENC_RD 3
 #endif
 constexpr int ENC_WD = WV_ENC_WD, ENC_RD = WV_ENC_RD;  // register ring depths (W1, raw rows): 2 or 3
-// Work-groups per encode launch (0: all tiles in one launch). An encode of more tiles is
-// queued as several launches in a row on its stream, so it holds at most this many CUs at
-// a time. The forward sweep needs one encode per step, and sliced encodes ran slower than
-// the steps they left CUs to (128 work-groups per launch: 300 us per encode, against 182
-// in one launch), so by default an encode is one launch.
-#ifndef WV_ENC_GRID
-#define WV_ENC_GRID 0
-#endif
-constexpr long long ENC_GRID = WV_ENC_GRID;
 constexpr int ENC_HLD = 64 + 8;  // bf16 row of a wave's hidden staging tile [16][ENC_HLD]
 constexpr int ENC_ZLD = 32 + 4;  // float row of the latent partial sums [BM][ENC_ZLD]
 constexpr int ENC_R_BYTES = 8 * 16 * ENC_HLD * 2;  // the largest use of the shared region
@@ -156,12 +157,12 @@ __global__ void __launch_bounds__(NT) encode_kernel(const EncArgs a)
     constexpr int TI = BM / 16;             // row tiles
     constexpr int A_HALF = TI * 64 * 8;     // bf16 per A buffer: [TI][64 lanes][8]
     static_assert(NT == 4 * BM, "one thread per raw row of a step");
-    static_assert(2 * A_HALF * 2 <= ENC_R_BYTES && BM * ENC_ZLD * 4 <= ENC_R_BYTES && BM * 8 * 4 <= ENC_R_BYTES,
-                  "the A buffers, the second layer's staging and the metadata share one region");
+    static_assert(2 * A_HALF * 2 <= ENC_R_BYTES && BM * ENC_ZLD * 4 <= ENC_R_BYTES,
+                  "the A buffers and the second layer's staging share one region");
     __shared__ __attribute__((aligned(16))) uint16_t sR[ENC_R_BYTES / 2];
     __shared__ __attribute__((aligned(16))) float2 sLR[4][BM];  // (lo, 1/r) per field and patch
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const long long m0 = (a.t0 + blockIdx.x) * BM;
+    const long long m0 = (long long)blockIdx.x * BM;
     const int fr = lane & 15, fq = (lane >> 4) * 8, cr = (lane >> 4) * 4;
 
     // thread (am, aq) loads and normalises y row aq (of the four of a k-step) of patch am:
@@ -170,10 +171,7 @@ __global__ void __launch_bounds__(NT) encode_kernel(const EncArgs a)
     const long long pa = m0 + am;
     const bool a_ok = pa < a.P;
     long long abase = 0;
-    if (a_ok) {
-        const long long px = pa % a.Px, py = (pa / a.Px) % a.Py, pz = pa / ((long long)a.Px * a.Py);
-        abase = ((pz * 8) * a.ny + py * 8 + aq) * a.nx + px * 8;
-    }
+    if (a_ok) abase = patch_base(a, pa) + aq * a.nx;
     const float* rsrc = a.state + abase;
     const long long plane = (long long)a.ny * a.nx;
     // k-step kk: field kk / 16, z level (kk % 16) / 2, y rows 4 (kk % 2) .. + 3. Steps past
@@ -203,20 +201,14 @@ __global__ void __launch_bounds__(NT) encode_kernel(const EncArgs a)
 #pragma unroll
     for (int q = 0; q < WD - 1; ++q) load_w(q, wb[q]);
 
-    {
-        float* sMeta = reinterpret_cast<float*>(sR);  // [BM][8], free again once sLR is filled
-        enc_meta(a, m0, tid, sMeta, BM);
-        __syncthreads();
-        if (tid < BM) {
-            const float4 m01 = *reinterpret_cast<const float4*>(sMeta + tid * 8);
-            const float4 m23 = *reinterpret_cast<const float4*>(sMeta + tid * 8 + 4);
-            sLR[0][tid] = make_float2(m01.x, m01.y);
-            sLR[1][tid] = make_float2(m01.z, m01.w);
-            sLR[2][tid] = make_float2(m23.x, m23.y);
-            sLR[3][tid] = make_float2(m23.z, m23.w);
-        }
-        __syncthreads();
+    // thread (field aq, patch am) forms (lo, 1 / r): from the partials, or from the metadata
+    if (a.mm) {
+        sLR[aq][am] = enc_lo_rinv(a, pa, aq, true);
+    } else {
+        const float2 m = a_ok ? *reinterpret_cast<const float2*>(a.meta + pa * 8 + 2 * aq) : make_float2(0.f, 1.f);
+        sLR[aq][am] = make_float2(m.x, 1.0f / m.y);
     }
+    __syncthreads();
     // A fragment (row tile i, lane l) holds patch 16 i + l % 16, k 8 (l / 16) .. + 7, i.e. y row
     // l / 16 of the step: thread (am, aq) writes lane am % 16 + 16 aq of tile am / 16
     const uint32_t amask = a_ok ? 0xFFFFFFFFu : 0u;
@@ -345,16 +337,246 @@ __global__ void __launch_bounds__(NT) encode_kernel(const EncArgs a)
 #pragma unroll
         for (int c = 0; c < 8; ++c) v[c] = sZ[zr * ENC_ZLD + zc + c] + a.b2[zc + c];
         if (a.zbf) {
-            uint16_t* o = a.zbf + p * L + zc;
+            *reinterpret_cast<uint4*>(a.zbf + p * L + zc) =
+                make_uint4(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]), f2bf2(v[4], v[5]), f2bf2(v[6], v[7]));
+        } else {
+            float m = 0.f;
 #pragma unroll
-            for (int c = 0; c < 8; ++c) o[c] = f2bf(v[c]);
-        }
-        if (a.zf) {
-            float* o = a.zf + p * L + zc;
+            for (int c = 0; c < 8; ++c) m = fmaxf(m, fabsf(v[c]));
+            m = fmaxf(m, __shfl_xor(m, 1, 64));  // the patch's four threads
+            m = fmaxf(m, __shfl_xor(m, 2, 64));
+            const float sc = fp8_scale(m);
+            uint32_t w[2] = {0u, 0u};
 #pragma unroll
-            for (int c = 0; c < 8; ++c) o[c] = v[c];
+            for (int c = 0; c < 8; ++c) w[c >> 2] |= (uint32_t)f2e4m3(v[c] / sc) << (8 * (c & 3));
+            *reinterpret_cast<uint2*>(a.codes + p * L + zc) = make_uint2(w[0], w[1]);
+            if ((tid & 3) == 0) a.scale[p] = sc;
         }
     }
+}
+
+// Encode of few patches. The tiled kernel above needs a work-group per 128 patches to amortise
+// its reads of W1 (2 MiB per work-group), so a state of a few thousand patches leaves most CUs
+// idle and takes one work-group's whole march (57 us for 420 patches). Here a work-group takes
+// 16 TI patches and 128 JW hidden units: the raw rows of its patches are all loaded at once
+// (64 TI registers), normalised and kept in LDS as the whole bfloat16 A operand in fragment
+// order, so the k loop has no barrier and waits only for its W1 fragments, RD k-steps ahead.
+// It is bound by those reads (64 B per clock and CU from L2: 3.4 us per 128 hidden units), hence
+// the split of the hidden units over work-groups while CUs are free. JW = 4 holds all 512
+// hidden units and sums the 8 partial latent blocks itself; with fewer, the blocks go to
+// zpart [8][P][L] and encode_finish_kernel sums them. Either way the additions are those of
+// the tiled kernel, in its order.
+template <int L, int TI, int JW>
+__global__ void __launch_bounds__(NT) encode_few_kernel(const EncArgs a, float* zpart)
+{
+    static_assert(L == 32 && (TI == 1 || TI == 2) && (JW == 1 || JW == 4), "tile shapes");
+    constexpr int M = 16 * TI;             // patches
+    constexpr int HS = 128 * JW;           // hidden units
+    constexpr int NG = HS / 64;            // their groups of 64, one partial latent block each
+    constexpr int NP = 8;                  // load passes: 256 rows of a patch, 8 waves x 4 rows each
+    constexpr int RD = JW == 4 ? 4 : 8;    // W1 ring
+    constexpr int HLD = HS + 8;            // bf16 row of the hidden layer
+    constexpr int ZLD = L + 4;
+    // A operand [64 k-steps][TI][64 lanes][8]; later the hidden layer and the partial blocks
+    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+    __shared__ float sMin[4][8][M], sMax[4][8][M];
+    __shared__ float2 sLR[4][M];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const long long m0 = (long long)blockIdx.x * M;
+    const int hg = blockIdx.y;
+    const int fr = lane & 15, fq = (lane >> 4) * 8, cr = (lane >> 4) * 4;
+
+    const uint16_t* wsrc = a.w1p + ((long long)((hg * 8 + wave) * JW) * 64 + lane) * 8;
+    bf16x8 wb[RD][JW];
+    auto load_w = [&](int kk, bf16x8(&d)[JW]) {
+#pragma unroll
+        for (int j = 0; j < JW; ++j)
+            d[j] = *reinterpret_cast<const bf16x8*>(wsrc + (long long)kk * (HID * KB) + j * 512);
+    };
+
+    // rows: pass q, wave w, lane l: row 32 q + 4 w + l / 16 (field q / 2) of patch l % 16 of
+    // each row tile; patches past P read patch 0 and are zeroed
+    float4 x[TI][NP][2];
+    bool ok[TI];
+#pragma unroll
+    for (int t = 0; t < TI; ++t) {
+        const long long pa = m0 + t * 16 + fr;
+        ok[t] = pa < a.P;
+        const float* src = a.state + (ok[t] ? patch_base(a, pa) : 0);
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const int r = 32 * (q & 1) + 4 * wave + (lane >> 4);  // row within the field
+            const float* s = src + (q >> 1) * a.N + ((long long)(r >> 3) * a.ny + (r & 7)) * a.nx;
+            x[t][q][0] = *reinterpret_cast<const float4*>(s);
+            x[t][q][1] = *reinterpret_cast<const float4*>(s + 4);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < RD; ++k) load_w(k, wb[k]);
+
+    if (a.mm) {
+        // (min, max) known: thread (field, patch) forms (lo, 1 / r); the first hidden group publishes
+        if (tid < 4 * M) {
+            const int f = tid / M, m = tid % M;
+            sLR[f][m] = enc_lo_rinv(a, m0 + m, f, hg == 0);
+        }
+    } else {
+#pragma unroll
+        for (int t = 0; t < TI; ++t)
+#pragma unroll
+            for (int f = 0; f < 4; ++f) {
+                float lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+                for (int q = 2 * f; q < 2 * f + 2; ++q)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const float4 v = x[t][q][h];
+                        lo = fminf(lo, fminf(fminf(v.x, v.y), fminf(v.z, v.w)));
+                        hi = fmaxf(hi, fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)));
+                    }
+#pragma unroll
+                for (int o = 16; o < 64; o <<= 1) {
+                    lo = fminf(lo, __shfl_xor(lo, o, 64));
+                    hi = fmaxf(hi, __shfl_xor(hi, o, 64));
+                }
+                if (lane < 16) {
+                    sMin[f][wave][t * 16 + lane] = lo;
+                    sMax[f][wave][t * 16 + lane] = hi;
+                }
+            }
+        __syncthreads();
+        if (tid < 4 * M) {
+            const int f = tid / M, m = tid % M;
+            float lo = sMin[f][0][m], hi = sMax[f][0][m];
+#pragma unroll
+            for (int w = 1; w < 8; ++w) {
+                lo = fminf(lo, sMin[f][w][m]);
+                hi = fmaxf(hi, sMax[f][w][m]);
+            }
+            const float r = fmaxf(hi - lo, a.beta[f]);
+            if (hg == 0 && m0 + m < a.P)
+                *reinterpret_cast<float2*>(const_cast<float*>(a.meta) + (m0 + m) * 8 + 2 * f) = make_float2(lo, r);
+            sLR[f][m] = make_float2(lo, 1.0f / r);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < TI; ++t) {
+        const uint32_t mask = ok[t] ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const float2 lr = sLR[q >> 1][t * 16 + fr];
+            const float l = lr.x, ri = lr.y;
+            const float4 u = x[t][q][0], v = x[t][q][1];
+            uint4 w;
+            w.x = f2bf2((u.x - l) * ri, (u.y - l) * ri) & mask;
+            w.y = f2bf2((u.z - l) * ri, (u.w - l) * ri) & mask;
+            w.z = f2bf2((v.x - l) * ri, (v.y - l) * ri) & mask;
+            w.w = f2bf2((v.z - l) * ri, (v.w - l) * ri) & mask;
+            *reinterpret_cast<uint4*>(smem + (((q * 8 + wave) * TI + t) * 64 + lane) * 8) = w;
+        }
+    }
+    __syncthreads();
+
+    f32x4 acc[TI][JW];
+#pragma unroll
+    for (int t = 0; t < TI; ++t)
+#pragma unroll
+        for (int j = 0; j < JW; ++j) acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 0; k0 < 64; k0 += RD) {
+#pragma unroll
+        for (int u = 0; u < RD; ++u) {
+            const int kk = k0 + u;
+            bf16x8 fa[TI];
+#pragma unroll
+            for (int t = 0; t < TI; ++t)
+                fa[t] = *reinterpret_cast<const bf16x8*>(smem + ((kk * TI + t) * 64 + lane) * 8);
+#pragma unroll
+            for (int t = 0; t < TI; ++t)
+#pragma unroll
+                for (int j = 0; j < JW; ++j)
+                    acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[t], wb[u][j], acc[t][j], 0, 0, 0);
+            load_w(min(kk + RD, 63), wb[u]);  // past the last k-step: the last one again
+        }
+    }
+    __syncthreads();  // A is read: the hidden layer [M][HLD] takes its place
+
+#pragma unroll
+    for (int j = 0; j < JW; ++j) {
+        const int c = (wave * JW + j) * 16 + fr;
+        const float bias = a.b1[hg * HS + c];
+#pragma unroll
+        for (int t = 0; t < TI; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) smem[(t * 16 + cr + r) * HLD + c] = f2bf(gelu(acc[t][j][r] + bias));
+    }
+    __syncthreads();
+    // partial latent blocks, one per group of 64 hidden units, row tile and half of the latents
+    constexpr int TASKS = NG * TI * 2;
+    float* sZ = reinterpret_cast<float*>(smem + M * HLD);  // [NG][M][ZLD] (JW = 4)
+    for (int task = wave; task < TASKS; task += 8) {
+        const int jj = task & 1, t = (task >> 1) % TI, g = (task >> 1) / TI;
+        f32x4 z = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const bf16x8 ah = *reinterpret_cast<const bf16x8*>(smem + (t * 16 + fr) * HLD + g * 64 + ks * 32 + fq);
+            const bf16x8 bw = *reinterpret_cast<const bf16x8*>(a.w2t + (long long)(jj * 16 + fr) * HID + hg * HS +
+                                                               g * 64 + ks * 32 + fq);
+            z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bw, z, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int m = t * 16 + cr + r;
+            if (JW == 4)
+                sZ[(g * M + m) * ZLD + jj * 16 + fr] = z[r];
+            else if (m0 + m < a.P)
+                zpart[((hg * NG + g) * a.P + m0 + m) * L + jj * 16 + fr] = z[r];
+        }
+    }
+    if constexpr (JW == 4) {
+        __syncthreads();
+        for (int e = tid; e < M * L; e += NT) {
+            const int m = e / L, c = e % L;
+            if (m0 + m >= a.P) break;
+            float v = sZ[m * ZLD + c];
+#pragma unroll
+            for (int g = 1; g < NG; ++g) v += sZ[(g * M + m) * ZLD + c];
+            v += a.b2[c];
+            if (a.zbf) {
+                a.zbf[(m0 + m) * L + c] = f2bf(v);
+            } else {
+                const float s = fp8_scale(half_wave_max(fabsf(v)));
+                a.codes[(m0 + m) * L + c] = f2e4m3(v / s);
+                if (c == 0) a.scale[m0 + m] = s;
+            }
+        }
+    }
+}
+
+// latents from the partial blocks of encode_few_kernel: the 8 blocks in order, then the bias;
+// bfloat16, or e4m3 codes with the patch's scale. A half wave per patch.
+__global__ void __launch_bounds__(256) encode_finish_kernel(const float* __restrict__ zpart, const float* __restrict__ b2,
+                                                            long long P, uint16_t* __restrict__ zbf,
+                                                            uint8_t* __restrict__ codes, float* __restrict__ scale)
+{
+    const long long e = blockIdx.x * 256LL + threadIdx.x;
+    const long long p = e >> 5;
+    const int c = (int)(e & 31);
+    if (p >= P) return;
+    float g[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) g[q] = zpart[(q * P + p) * 32 + c];
+    float v = g[0];
+#pragma unroll
+    for (int q = 1; q < 8; ++q) v += g[q];
+    v += b2[c];
+    if (zbf) {
+        zbf[e] = f2bf(v);
+        return;
+    }
+    const float s = fp8_scale(half_wave_max(fabsf(v)));
+    codes[e] = f2e4m3(v / s);
+    if (c == 0) scale[p] = s;
 }
 
 // Decode: DEC_NW waves per work-group of DEC_BM patches; wave w owns hidden units
@@ -377,11 +599,11 @@ __global__ void __launch_bounds__(NT) encode_kernel(const EncArgs a)
 constexpr int DEC_NW = WV_DEC_WAVES;
 constexpr int DEC_NT = DEC_NW * 64;
 
-template <int L>
+// BM: patches per work-group (16, 32 or DEC_BM)
+template <int L, int BM>
 __global__ void __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(WV_DEC_WPE > 0 ? WV_DEC_WPE : 1)))
     decode_kernel(const DecArgs a)
 {
-    constexpr int BM = DEC_BM;         // patches per work-group
     constexpr int IT = BM / 16;        // 16-row tiles
     constexpr int OPW = HID / DEC_NW;  // hidden units / outputs per wave
     constexpr int JT = OPW / 16;       // 16-wide column tiles per wave
@@ -396,8 +618,10 @@ __global__ void __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(WV_
     int* sExc = reinterpret_cast<int*>(sRg + BM);  // exception slot of each patch, or -1
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int fr = lane & 15, fq = (lane >> 4) * 8, cr = (lane >> 4) * 4, q = lane >> 4;
-    const long long tile = a.t0 + blockIdx.x;
-    const long long m0 = tile * BM;
+    const unsigned wg = (unsigned)a.t0 + blockIdx.x;
+    const long long src = wg / (unsigned)a.tps, tile = wg % (unsigned)a.tps;
+    const long long m0 = tile * BM;  // first patch within the source
+    const long long g0 = src * a.Ps;  // the source's first row of latents and metadata
     const bool has_exc = a.eidx != nullptr;
 
     if (tid < BM) {
@@ -405,15 +629,14 @@ __global__ void __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(WV_
         const long long p = m0 + tid;
         long long base = 0;
         float lo = 0.f, rg = 0.f;
-        if (p < a.P) {
-            const long long px = p % a.Px, py = (p / a.Px) % a.Py, pz = p / ((long long)a.Px * a.Py);
-            base = (pz * 8 * a.ny + py * 8) * a.nx + px * 8;
+        if (p < a.Ps) {
+            base = patch_base(a, g0 + p);
             if (a.meta16) {
-                lo = bf2f(a.meta16[p * 8 + 2 * a.f]);
-                rg = bf2f(a.meta16[p * 8 + 2 * a.f + 1]);
+                lo = bf2f(a.meta16[(g0 + p) * 8 + 2 * a.f]);
+                rg = bf2f(a.meta16[(g0 + p) * 8 + 2 * a.f + 1]);
             } else {
-                lo = a.meta[p * 8 + 2 * a.f];
-                rg = a.meta[p * 8 + 2 * a.f + 1];
+                lo = a.meta[(g0 + p) * 8 + 2 * a.f];
+                rg = a.meta[(g0 + p) * 8 + 2 * a.f + 1];
             }
         }
         sBase[tid] = base;
@@ -448,8 +671,17 @@ __global__ void __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(WV_
             for (int i = 0; i < IT; ++i) {
                 const long long p = m0 + i * 16 + fr;
                 bf16x8 az;
-                if (p < a.P) {
-                    az = *reinterpret_cast<const bf16x8*>(a.z + p * L + kk * KB + fq);
+                if (p < a.Ps && a.z) {
+                    az = *reinterpret_cast<const bf16x8*>(a.z + (g0 + p) * L + kk * KB + fq);
+                } else if (p < a.Ps) {
+                    const uint2 q8 = *reinterpret_cast<const uint2*>(a.codes + (g0 + p) * L + kk * KB + fq);
+                    const float sc = a.scale[g0 + p];
+                    uint4 w;
+                    w.x = f2bf2(e4m32f(q8.x & 0xFFu) * sc, e4m32f(q8.x >> 8 & 0xFFu) * sc);
+                    w.y = f2bf2(e4m32f(q8.x >> 16 & 0xFFu) * sc, e4m32f(q8.x >> 24) * sc);
+                    w.z = f2bf2(e4m32f(q8.y & 0xFFu) * sc, e4m32f(q8.y >> 8 & 0xFFu) * sc);
+                    w.w = f2bf2(e4m32f(q8.y >> 16 & 0xFFu) * sc, e4m32f(q8.y >> 24) * sc);
+                    az = __builtin_bit_cast(bf16x8, w);
                 } else {
                     const uint4 zero = make_uint4(0, 0, 0, 0);
                     az = *reinterpret_cast<const bf16x8*>(&zero);
@@ -471,10 +703,12 @@ __global__ void __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(WV_
     }
     __syncthreads();
     if (has_exc) {
-        const int e0 = a.erng[tile], e1 = a.erng[tile + 1];
+        // the ranges hold DEC_BM patches each: a smaller work-group takes its part of one
+        const int* rng = a.erng + src * a.nrng + tile * BM / DEC_BM;
+        const int e0 = rng[0], e1 = rng[1];
         for (int t = e0 + tid; t < e1; t += DEC_NT) {
-            const long long d = a.eidx[t] - m0;
-            if (d >= 0 && d < BM) sExc[d] = t;
+            const long long d = a.eidx[src * a.K + t] - m0;
+            if (d >= 0 && d < BM) sExc[d] = (int)(src * a.K) + t;
         }
     }
     // layer 4, rows of field f. A row m of tile i is patch 16 i + 4 (m % 4) + m / 4, so that the C rows
@@ -518,7 +752,7 @@ __global__ void __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(WV_
         #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int pl = i * 16 + 4 * r + q;
-            if (m0 + pl >= a.P) continue;
+            if (m0 + pl >= a.Ps) continue;
             const long long base = sBase[pl];
             const float lo = sLo[pl], rg = sRg[pl];
             const int slot = has_exc ? sExc[pl] : -1;
@@ -567,43 +801,109 @@ void fused_pack(const uint16_t* w, int rows, int K, uint16_t* out, hipStream_t s
     WV_HIP(hipGetLastError());
 }
 
-void fused_encode(const PatchGrid& pg, const float* state, float* meta, const float* mm, int H, const float* beta,
-                  const uint16_t* w1p, const float* b1, const uint16_t* w2t, const float* b2, uint16_t* zbf, float* zf,
-                  hipStream_t st, uint16_t* meta16)
+namespace {
+
+// patches of all sources: the kernels number them in 32 bits
+long long fused_patches(const PatchGrid& pg, int nsrc)
+{
+    WV_REQUIRE(pg.P * nsrc < (1LL << 31), WV_EINVAL, "too many patches in one codec call");
+    return pg.P * nsrc;
+}
+
+template <int TI, int JW>
+void launch_few(const EncArgs& a, float* zpart, hipStream_t st)
+{
+    const size_t sm = (size_t)64 * TI * 64 * 8 * 2;
+    allow_smem(encode_few_kernel<32, TI, JW>, sm);
+    const long long tiles = (a.P + 16 * TI - 1) / (16 * TI);
+    hipLaunchKernelGGL((encode_few_kernel<32, TI, JW>), dim3((unsigned)tiles, 4 / JW), dim3(NT), sm, st, a, zpart);
+    WV_HIP(hipGetLastError());
+}
+
+}  // namespace
+
+// The lines lie where one more round of work-groups over the 256 CUs sets in. ae_encode in
+// us per state, this kernel / the next: split 12.8 / 21.6 at 768 patches, 20.6 / 25.9 at 1728,
+// 39 / 31 at 4096; 16-patch work-groups 31 / 32 at 4096, 56 / 36 at 6144; 32-patch ones
+// 67 / 80 at 12288, 109 / 97 at 24576 (tiled).
+EncPlan fused_encode_plan(long long P, bool can_split)
+{
+    if (P <= 2048 && can_split) return ENC_FEW_SPLIT;
+    if (P <= 4096) return ENC_FEW;
+    if (P <= 16384) return ENC_FEW_PAIR;
+    return ENC_TILED;
+}
+
+void fused_encode(EncPlan plan, const PatchGrid& pg, int nsrc, const float* state, float* meta, const float* mm, int H,
+                  const float* beta, const uint16_t* w1p, const float* b1, const uint16_t* w2t, const float* b2,
+                  uint16_t* zbf, uint8_t* codes, float* scale, float* zpart, hipStream_t st, uint16_t* meta16)
 {
     WV_REQUIRE(!meta16 || mm, WV_EINVAL, "16-bit metadata is written from the step's (min, max) partials");
-    EncArgs a{state, meta, meta16, mm, H, beta, w1p, b1, w2t, b2, zbf, zf, pg.P, (long long)pg.nz * pg.ny * pg.nx,
-              pg.ny, pg.nx, pg.ny / 8, pg.nx / 8, 0};
-    const long long tiles = (pg.P + BM - 1) / BM;
-    const long long per = ENC_GRID > 0 ? ENC_GRID : tiles;
+    WV_REQUIRE(zbf || (codes && scale), WV_EINVAL, "encode: null latent buffer");
+    const long long N = (long long)pg.nz * pg.ny * pg.nx;
+    const EncArgs a{state, meta, meta16, mm, H, beta, w1p, b1, w2t, b2, zbf, codes, scale, fused_patches(pg, nsrc), N, pg.P, 4 * N,
+                    pg.ny, pg.nx, pg.ny / 8, pg.nx / 8};
+    switch (plan) {
+    case ENC_FEW_SPLIT:
+        WV_REQUIRE(zpart, WV_EINVAL, "encode: null work buffer");
+        launch_few<1, 1>(a, zpart, st);
+        hipLaunchKernelGGL(encode_finish_kernel, dim3((unsigned)((a.P * 32 + 255) / 256)), dim3(256), 0, st, zpart, b2,
+                           a.P, zbf, codes, scale);
+        break;
+    case ENC_FEW: launch_few<1, 4>(a, nullptr, st); break;
+    case ENC_FEW_PAIR: launch_few<2, 4>(a, nullptr, st); break;
+    default:
+        hipLaunchKernelGGL((encode_kernel<32, ENC_WD, ENC_RD>), dim3((unsigned)((a.P + BM - 1) / BM)), dim3(NT), 0, st,
+                           a);
+    }
+    WV_HIP(hipGetLastError());
+}
+
+namespace {
+
+template <int BMT>
+void launch_decode(DecArgs a, int nsrc, long long grid, hipStream_t st)
+{
+    const size_t sm = (size_t)BMT * (HID + HPAD) * 2 + (size_t)BMT * 20;
+    allow_smem(decode_kernel<32, BMT>, sm);
+    a.tps = (a.Ps + BMT - 1) / BMT;
+    const long long tiles = a.tps * nsrc;
+    const long long per = grid > 0 ? grid : tiles;
     for (a.t0 = 0; a.t0 < tiles; a.t0 += per) {
-        hipLaunchKernelGGL((encode_kernel<32, ENC_WD, ENC_RD>), dim3((unsigned)std::min(per, tiles - a.t0)), dim3(NT), 0,
-                           st, a);
+        hipLaunchKernelGGL((decode_kernel<32, BMT>), dim3((unsigned)std::min(per, tiles - a.t0)), dim3(DEC_NT), sm, st,
+                           a);
         WV_HIP(hipGetLastError());
     }
 }
 
-void fused_decode(const PatchGrid& pg, const uint16_t* z, const float* meta, const uint16_t* w3t, const float* b3,
-                  const uint16_t* w4p, const float* b4, int f, float* state, hipStream_t st, const ExcPatches* exc,
-                  const uint16_t* meta16, long long grid)
+}  // namespace
+
+void fused_decode(const PatchGrid& pg, int nsrc, const uint16_t* z, const uint8_t* codes, const float* scale,
+                  const float* meta, const uint16_t* w3t, const float* b3, const uint16_t* w4p, const float* b4, int f,
+                  float* state, long long sstride, hipStream_t st, const ExcPatches* exc, const uint16_t* meta16,
+                  long long grid)
 {
-    static_assert(DEC_BM % 16 == 0 && DEC_BM <= 512, "decode work-groups hold whole 16-patch tiles");
-    DecArgs a{z, meta, meta16, w3t, b3, w4p, b4, state, f, pg.P, (long long)pg.nz * pg.ny * pg.nx, pg.ny, pg.nx,
-              pg.ny / 8, pg.nx / 8, nullptr, nullptr, nullptr, 0};
+    static_assert(DEC_BM % 32 == 0 && DEC_BM <= 512, "decode work-groups hold whole 16-patch tiles");
+    WV_REQUIRE(z || (codes && scale), WV_EINVAL, "decode: null latents");
+    const long long N = (long long)pg.nz * pg.ny * pg.nx;
+    DecArgs a{z, codes, scale, meta, meta16, w3t, b3, w4p, b4, state, f, N, pg.P, sstride, 0, pg.ny, pg.nx,
+              pg.ny / 8, pg.nx / 8, nullptr, nullptr, nullptr, 0, 0, 0};
     if (exc && exc->K > 0) {
         WV_REQUIRE(exc->idx && exc->exc && exc->rng, WV_EINVAL, "decode: null exception buffer");
         a.eidx = exc->idx;
         a.exc = exc->exc;
         a.erng = exc->rng;
+        a.K = exc->K;
+        a.nrng = (int)((pg.P + DEC_BM - 1) / DEC_BM) + 1;
     }
-    const size_t sm = (size_t)DEC_BM * (HID + HPAD) * 2 + (size_t)DEC_BM * 20;
-    allow_smem(decode_kernel<32>, sm);
-    const long long tiles = (pg.P + DEC_BM - 1) / DEC_BM;
-    const long long per = grid > 0 ? grid : tiles;
-    for (a.t0 = 0; a.t0 < tiles; a.t0 += per) {
-        hipLaunchKernelGGL(decode_kernel<32>, dim3((unsigned)std::min(per, tiles - a.t0)), dim3(DEC_NT), sm, st, a);
-        WV_HIP(hipGetLastError());
-    }
+    // Work-groups of fewer patches while that fills more CUs (each reads 512 KiB of W4 from L2):
+    // us per decode of e for 16 / 32 / 64 patches: 8.3 / 10.5 / 16.2 at 216 patches, 10.8 / 12.2 /
+    // 17.8 at 4096, 15.9 / 13.4 / 18.5 at 6144, 25.3 / 21.1 / 20.7 at 12288.
+    const long long P = fused_patches(pg, nsrc);
+    const int bm = P <= 4096 ? 16 : P <= 8192 ? 32 : DEC_BM;
+    if (bm == 16) launch_decode<16>(a, nsrc, 0, st);
+    else if (bm == 32) launch_decode<32>(a, nsrc, 0, st);
+    else launch_decode<DEC_BM>(a, nsrc, grid, st);
 }
 
 }  // namespace wv

@@ -57,13 +57,15 @@ long long ae_latent_bytes_per_patch(const ae_net* net, int fmt);
 // Compress one state [4][N] into latent [P][L] (+ meta [P][4][2], qscale [P] for FP8).
 void ae_encode_state(const ae_net* net, const PatchGrid& pg, const float* state, int fmt,
                      void* latent, float* meta, float* qscale, hipStream_t st);
-// Compress with the per-patch (min, max) partials [P][H][4][2] computed by the
-// forward step (no separate pass over the state for the normalisation).
+// Compress nsrc states (4 N floats apart) with the per-patch (min, max) partials
+// [nsrc][P][H][4][2] computed by the forward step (no separate pass over the states for the
+// normalisation) into contiguous latents, metadata and scales.
 // meta16 (optional): bfloat16 (lo, r) written instead of meta, lo rounded down and
 // r up to bfloat16 before the normalisation uses them.
-void ae_encode_state_mm(const ae_net* net, const PatchGrid& pg, const float* state, const float* mm, int H, int fmt,
-                        void* latent, float* meta, float* qscale, hipStream_t st, uint16_t* meta16 = nullptr);
-// Exception patches of one stored state: K patch indices in increasing order,
+void ae_encode_states_mm(const ae_net* net, const PatchGrid& pg, int nsrc, const float* state, const float* mm, int H,
+                         int fmt, void* latent, float* meta, float* qscale, hipStream_t st,
+                         uint16_t* meta16 = nullptr);
+// Exception patches of a stored state, per source: K patch indices in increasing order,
 // their exact e values [K][512] ((lz, ly, lx) order), and rng [ceil(P/DEC_BM) + 1]:
 // the exceptions of patches [DEC_BM b, DEC_BM b + DEC_BM) are idx[rng[b] .. rng[b+1]).
 struct ExcPatches {
@@ -76,12 +78,12 @@ struct ExcPatches {
 #define WV_DEC_BM 64
 #endif
 constexpr int DEC_BM = WV_DEC_BM;  // patches per decode work-group
-// Decompress the fields in field_mask into state [4][N]; with exc, the e values of
-// its patches are the exact ones.
-// meta16 (optional): bfloat16 (lo, r) read instead of meta.
-void ae_decode_state(const ae_net* net, const PatchGrid& pg, const void* latent, const float* meta,
-                     const float* qscale, int fmt, uint32_t field_mask, float* state, hipStream_t st,
-                     const ExcPatches* exc = nullptr, const uint16_t* meta16 = nullptr, long long grid = 0);
+// Decompress the fields in field_mask of nsrc states (sstride floats apart, field f at
+// + f N) from contiguous latents and metadata; with exc, the e values of its patches are
+// the exact ones. meta16 (optional): bfloat16 (lo, r) read instead of meta.
+void ae_decode_states(const ae_net* net, const PatchGrid& pg, int nsrc, const void* latent, const float* meta,
+                      const float* qscale, int fmt, uint32_t field_mask, float* state, long long sstride,
+                      hipStream_t st, const ExcPatches* exc, const uint16_t* meta16, long long grid);
 
 // Fused inference kernels (hidden width 512, latent 32): meta must already hold
 // the per-patch (min, range) of the state for encode.
@@ -90,18 +92,27 @@ bool fused_supported(int hid, int lat);
 // order [K/32][rows/16][64 lanes][8]: lane l of block (ks, r) holds row 16 r + l % 16,
 // k = 32 ks + 8 (l / 16) .. +7, so one k-step of a row range is contiguous.
 void fused_pack(const uint16_t* w, int rows, int K, uint16_t* out, hipStream_t st);
-// meta: input (min, range), or output when the partial (min, max) table mm
-// [P][H][4][2] of the forward step is given (then r = max(max - min, beta_f)).
+// Encode kernels by the number of patches (of all sources); the split one needs the work
+// buffer zpart [8][P][32]
+enum EncPlan { ENC_TILED = 0, ENC_FEW_SPLIT = 1, ENC_FEW = 2, ENC_FEW_PAIR = 3 };
+inline bool encode_splits(EncPlan p) { return p == ENC_FEW_SPLIT; }
+EncPlan fused_encode_plan(long long P, bool can_split);
+// nsrc states 4 N floats apart, everything else contiguous over the sources. meta: output,
+// from the partial (min, max) table mm [P][H][4][2] of the forward step when given
+// (r = max(max - min, beta_f)), else from the state; ENC_TILED without mm takes meta as its
+// input. Latents: zbf, or codes and scale (zbf null).
 // w1p: W1^T packed by fused_pack; w4p: W4^T packed by fused_pack.
-void fused_encode(const PatchGrid& pg, const float* state, float* meta, const float* mm, int H, const float* beta,
-                  const uint16_t* w1p, const float* b1, const uint16_t* w2t, const float* b2, uint16_t* zbf, float* zf,
-                  hipStream_t st, uint16_t* meta16 = nullptr);
-// exc (field 0 only): exception patches written with their exact values.
+void fused_encode(EncPlan plan, const PatchGrid& pg, int nsrc, const float* state, float* meta, const float* mm, int H,
+                  const float* beta, const uint16_t* w1p, const float* b1, const uint16_t* w2t, const float* b2,
+                  uint16_t* zbf, uint8_t* codes, float* scale, float* zpart, hipStream_t st, uint16_t* meta16);
+// latents z, or codes and scale (z null); exc (field 0 only): exception patches written with
+// their exact values.
 // grid > 0: the decode is queued as launches of at most grid work-groups, one after the
 // other on st, so it holds fewer CUs at a time (0: one launch).
-void fused_decode(const PatchGrid& pg, const uint16_t* z, const float* meta, const uint16_t* w3t, const float* b3,
-                  const uint16_t* w4p, const float* b4, int f, float* state, hipStream_t st,
-                  const ExcPatches* exc = nullptr, const uint16_t* meta16 = nullptr, long long grid = 0);
+void fused_decode(const PatchGrid& pg, int nsrc, const uint16_t* z, const uint8_t* codes, const float* scale,
+                  const float* meta, const uint16_t* w3t, const float* b3, const uint16_t* w4p, const float* b4, int f,
+                  float* state, long long sstride, hipStream_t st, const ExcPatches* exc, const uint16_t* meta16,
+                  long long grid);
 
 // Exception patches: the K largest-e-range patches of one compressed state are
 // kept exactly. Ranges are compared by key = bits(r_e) >> EXC_BIN_SHIFT (bins 2^-5
@@ -109,17 +120,15 @@ void fused_decode(const PatchGrid& pg, const uint16_t* z, const float* meta, con
 // win.
 constexpr int EXC_BIN_SHIFT = 18;
 constexpr int EXC_NBIN = 1 << (32 - EXC_BIN_SHIFT);
-// selection from meta [P][4][2] into idx [K] (increasing patch order); a single
-// work-group kernel, cheap to overlap with other work
-void exceptions_select(const PatchGrid& pg, const float* meta, int K, int* idx, hipStream_t st,
-                       const uint16_t* meta16 = nullptr);
-// copy the e values of the selected patches to exc [K][512]
+// selection from meta [P][4][2] into idx [K] (increasing patch order) and the ranges
+// rng [ceil(P/bm) + 1] (rng[b] = number of idx entries below patch bm b); a single
+// work-group kernel, cheap to overlap with other work. Few patches (exceptions_fused) are
+// also copied by it: exc [K][512] from state
+inline bool exceptions_fused(int K) { return K <= 64; }
+void exceptions_select(const PatchGrid& pg, const float* state, const float* meta, int K, int* idx, int bm, int* rng,
+                       float* exc, hipStream_t st, const uint16_t* meta16);
+// copy the e values of the selected patches to exc [K][512] (not exceptions_fused)
 void exceptions_gather(const PatchGrid& pg, const float* state, int K, const int* idx, float* exc, hipStream_t st);
-// both
-void exceptions_store(const PatchGrid& pg, const float* state, const float* meta, int K, int* idx, float* exc,
-                      hipStream_t st, const uint16_t* meta16 = nullptr);
-// rng [ceil(P/bm) + 1]: rng[b] = number of idx entries below patch bm b
-void exceptions_ranges(const PatchGrid& pg, int K, const int* idx, int bm, int* rng, hipStream_t st);
 // Write the stored e values back into an e field [N].
 void exceptions_restore(const PatchGrid& pg, float* e, int K, const int* idx, const float* exc, hipStream_t st);
 

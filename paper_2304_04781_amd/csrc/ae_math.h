@@ -1,5 +1,5 @@
 // Scalar numerics shared by the autoencoder kernels (training and inference):
-// bfloat16 rounding, the GELU activation and its derivative.
+// bfloat16 and e4m3 rounding, the GELU activation and its derivative.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -34,6 +34,33 @@ __device__ __forceinline__ uint16_t bf16_up(float x)
 {
     const uint32_t u = __float_as_uint(x);
     return (uint16_t)((u >> 16) + (((u >> 31) == 0u && (u & 0xFFFFu) != 0u) ? 1u : 0u));
+}
+
+// OCP E4M3FN, round to nearest even, saturating at 448
+__device__ __forceinline__ uint8_t f2e4m3(float x)
+{
+    const uint32_t sign = (__float_as_uint(x) >> 24) & 0x80u;
+    const float a = fabsf(x);
+    uint32_t code;
+    if (a >= 448.0f) {
+        code = 0x7E;
+    } else {
+        const int e = (int)((__float_as_uint(a) >> 23) & 0xFF) - 127;
+        if (e < -6) {
+            code = (uint32_t)rintf(a * 512.0f);  // subnormal quantum 2^-9
+        } else {
+            const float q = rintf(ldexpf(a, 3 - e));  // in [8, 16]
+            code = (uint32_t)((e + 7) << 3) + ((uint32_t)q - 8u);
+        }
+        if (code > 0x7E) code = 0x7E;
+    }
+    return (uint8_t)(code | sign);
+}
+__device__ __forceinline__ float e4m32f(uint8_t c)
+{
+    const int E = (c >> 3) & 0xF, m = c & 7;
+    const float v = E == 0 ? (float)m * 0.001953125f : ldexpf(1.0f + (float)m * 0.125f, E - 7);
+    return (c & 0x80) ? -v : v;
 }
 
 // erf(x) by the rational-exponential approximation of Abramowitz & Stegun 7.1.26

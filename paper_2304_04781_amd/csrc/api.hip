@@ -681,16 +681,14 @@ void encode_state_into(wv_ctx* c, LatStore& L, int n, const float* state, hipStr
 {
     const PatchGrid pg = patch_grid(c->g.nz, c->g.ny, c->g.nx);
     const int te = c->tm.begin(TM_ENCODE, st);
-    for (int s = 0; s < c->S; ++s) {
-        if (mm)
-            ae_encode_state_mm(c->ae, pg, state + s * 4 * c->N, mm + (long long)s * c->P * c->H * 8, c->H,
-                               ae_fmt(c->mode), lat_slot(c, L, n - 1, s), meta_slot(c, L, n - 1, s),
-                               qs_slot(c, L, n - 1, s), st, meta16_slot(c, L, n - 1, s));
-        else {
-            WV_REQUIRE(!c->m16, WV_EINVAL, "16-bit metadata needs the step's (min, max) partials");
+    if (mm) {
+        ae_encode_states_mm(c->ae, pg, c->S, state, mm, c->H, ae_fmt(c->mode), lat_slot(c, L, n - 1, 0),
+                            meta_slot(c, L, n - 1, 0), qs_slot(c, L, n - 1, 0), st, meta16_slot(c, L, n - 1, 0));
+    } else {
+        WV_REQUIRE(!c->m16, WV_EINVAL, "16-bit metadata needs the step's (min, max) partials");
+        for (int s = 0; s < c->S; ++s)
             ae_encode_state(c->ae, pg, state + s * 4 * c->N, ae_fmt(c->mode), lat_slot(c, L, n - 1, s),
                             meta_slot(c, L, n - 1, s), qs_slot(c, L, n - 1, s), st);
-        }
     }
     c->tm.end(te, st);
 }
@@ -703,9 +701,9 @@ void exceptions_into(wv_ctx* c, LatStore& L, int n, const float* state, hipStrea
     const int tx = c->tm.begin(TM_EXC_SELECT, st);
     for (int s = 0; s < c->S; ++s) {
         const long long q = (long long)(n - 1) * c->S + s;
-        exceptions_store(pg, state + s * 4 * c->N, meta_slot(c, L, n - 1, s), c->K, L.exc_idx + q * c->K,
-                         L.exc + q * c->K * 512, st, meta16_slot(c, L, n - 1, s));
-        exceptions_ranges(pg, c->K, L.exc_idx + q * c->K, DEC_BM, rng_slot(c, L, q), st);
+        exceptions_select(pg, state + s * 4 * c->N, meta_slot(c, L, n - 1, s), c->K, L.exc_idx + q * c->K, DEC_BM,
+                          rng_slot(c, L, q), L.exc + q * c->K * 512, st, meta16_slot(c, L, n - 1, s));
+        exceptions_gather(pg, state + s * 4 * c->N, c->K, L.exc_idx + q * c->K, L.exc + q * c->K * 512, st);
     }
     c->tm.end(tx, st);
 }
@@ -768,21 +766,39 @@ void wait_event(hipStream_t st, hipEvent_t ev)
     WV_HIP(hipStreamWaitEvent(st, ev, 0));
 }
 
+// Work queued on `to` after the work queued on `from` so far (nothing to do on one stream)
+void order_after(hipStream_t to, hipStream_t from, hipEvent_t ev)
+{
+    if (to == from) return;
+    WV_HIP(hipEventRecord(ev, from));
+    wait_event(to, ev);
+}
+
 // 1: autoencoder stores and decodes run on the side streams, beside the stencil
 // steps; 2: only the exception selection and copy do; 0: everything on the main
 // stream in order. With several sources the stencil launch holds S times the
 // work-groups and the side-stream kernels starve beside it (an 8-source 512^2 x 256
 // decode ran 10x slower than alone), so such contexts use mode 2.
+// States of few patches are stored and read in order on the main stream too: their kernels
+// are shorter than the event records and cross-stream waits (gradient of 48^3 x 240 steps, 216
+// patches: 11.2 ms in order, 17.5 beside; 80^3 x 100, 1000 patches: 9.3 and 7.7).
 #ifndef WV_OVERLAP
 #define WV_OVERLAP 1
 #endif
+#ifndef WV_OVERLAP_MIN_P
+#define WV_OVERLAP_MIN_P 512
+#endif
 hipStream_t side_stream(wv_ctx* c, int which)
 {
+    if (is_ae(c->mode) && c->P * c->S <= WV_OVERLAP_MIN_P) return c->st;
     const int mode = (WV_OVERLAP == 1 && c->S > 1) ? 2 : WV_OVERLAP;
     if (which == 2) return mode == 1 ? c->side3 : c->st;
     if (which) return mode >= 1 ? c->side2 : c->st;
     return mode == 1 ? c->side : c->st;
 }
+
+// whether part of a state's store runs beside the main stream (its end is in ev_stored then)
+bool store_side(wv_ctx* c) { return side_stream(c, c->K > 0 ? 1 : 0) != c->st; }
 
 // Autoencoder store of x_j (1 <= j <= T-1) written by the forward step just
 // launched on the main stream, with its min/max partials in mm: encode on `side`,
@@ -792,26 +808,19 @@ void store_state_async(wv_ctx* c, int j, const float* state, const float* mm)
     const PatchGrid pg = patch_grid(c->g.nz, c->g.ny, c->g.nx);
     const int b = j % 3;
     hipStream_t s1 = side_stream(c, 0), s2 = side_stream(c, 1);
-    WV_HIP(hipEventRecord(c->ev_step[b], c->st));
-    wait_event(s1, c->ev_step[b]);
-    const int te = c->tm.begin(TM_ENCODE, s1);
-    for (int s = 0; s < c->S; ++s)
-        ae_encode_state_mm(c->ae, pg, state + s * 4 * c->N, mm + (long long)s * c->P * c->H * 8, c->H,
-                           ae_fmt(c->mode), lat_slot(c, c->fs, j - 1, s), meta_slot(c, c->fs, j - 1, s),
-                           qs_slot(c, c->fs, j - 1, s), s1, meta16_slot(c, c->fs, j - 1, s));
-    c->tm.end(te, s1);
+    order_after(s1, c->st, c->ev_step[b]);
+    encode_state_into(c, c->fs, j, state, s1, mm);
     if (c->K <= 0) {
-        WV_HIP(hipEventRecord(c->ev_stored[b], s1));
+        if (s1 != c->st) WV_HIP(hipEventRecord(c->ev_stored[b], s1));
         return;
     }
-    WV_HIP(hipEventRecord(c->ev_enc[b], s1));
-    wait_event(s2, c->ev_enc[b]);
+    order_after(s2, s1, c->ev_enc[b]);
     const int tx = c->tm.begin(TM_EXC_SELECT, s2);
     for (int s = 0; s < c->S; ++s) {
         const long long q = (long long)(j - 1) * c->S + s;
-        exceptions_select(pg, meta_slot(c, c->fs, j - 1, s), c->K, c->fs.exc_idx + q * c->K, s2,
+        exceptions_select(pg, state + s * 4 * c->N, meta_slot(c, c->fs, j - 1, s), c->K, c->fs.exc_idx + q * c->K,
+                          DEC_BM, rng_slot(c, c->fs, q), c->fs.exc + q * c->K * 512, s2,
                           meta16_slot(c, c->fs, j - 1, s));
-        exceptions_ranges(pg, c->K, c->fs.exc_idx + q * c->K, DEC_BM, rng_slot(c, c->fs, q), s2);
     }
     c->tm.end(tx, s2);
     const int tg = c->tm.begin(TM_EXC_GATHER, s2);
@@ -821,7 +830,7 @@ void store_state_async(wv_ctx* c, int j, const float* state, const float* mm)
                           s2);
     }
     c->tm.end(tg, s2);
-    WV_HIP(hipEventRecord(c->ev_stored[b], s2));
+    if (s2 != c->st) WV_HIP(hipEventRecord(c->ev_stored[b], s2));
 }
 
 // make the main stream wait for everything queued on the side streams
@@ -855,17 +864,14 @@ void decode_state(wv_ctx* c, const LatStore& L, int n, uint32_t mask, float* out
 {
     WV_REQUIRE(n >= 1 && n <= c->T - 1, WV_ESTATE, "stored state index out of range");
     const PatchGrid pg = patch_grid(c->g.nz, c->g.ny, c->g.nx);
-    for (int s = 0; s < c->S; ++s) {
-        // the exception patches of e are written with their exact values by the decode
-        const long long q = (long long)(n - 1) * c->S + s;
-        const ExcPatches ex{L.exc_idx + q * c->K, c->K, L.exc + q * c->K * 512,
-                            c->K > 0 ? rng_slot(c, L, q) : nullptr};
-        const int td = c->tm.begin(TM_DECODE, st);
-        ae_decode_state(c->ae, pg, lat_slot(c, L, n - 1, s), meta_slot(c, L, n - 1, s), qs_slot(c, L, n - 1, s),
-                        ae_fmt(c->mode), mask, out + s * stride, st, c->K > 0 ? &ex : nullptr,
-                        meta16_slot(c, L, n - 1, s), grid);
-        c->tm.end(td, st);
-    }
+    // the exception patches of e are written with their exact values by the decode
+    const long long q = (long long)(n - 1) * c->S;
+    const ExcPatches ex{L.exc_idx + q * c->K, c->K, L.exc + q * c->K * 512, c->K > 0 ? rng_slot(c, L, q) : nullptr};
+    const int td = c->tm.begin(TM_DECODE, st);
+    ae_decode_states(c->ae, pg, c->S, lat_slot(c, L, n - 1, 0), meta_slot(c, L, n - 1, 0), qs_slot(c, L, n - 1, 0),
+                     ae_fmt(c->mode), mask, out, stride, st, c->K > 0 ? &ex : nullptr, meta16_slot(c, L, n - 1, 0),
+                     grid);
+    c->tm.end(td, st);
 }
 
 // decode e^n of every source from the forward AE store into ebuf slot b on stream st
@@ -936,21 +942,25 @@ void pipe_start(wv_ctx* c, long long grid = 0)
 {
     ensure_adj(c);
     c->pipe_grid = grid;
+    if (side_stream(c, 0) == c->st) return;
     for (int b = 0; b < NEB; ++b) WV_HIP(hipEventRecord(c->ev_free[b], c->st));
 }
 void pipe_issue(wv_ctx* c, int n, int b)
 {
     hipStream_t s1 = side_stream(c, 0);
-    wait_event(s1, c->ev_free[b]);
+    if (s1 != c->st) wait_event(s1, c->ev_free[b]);
     decode_e(c, n, b, s1, c->pipe_grid);
-    WV_HIP(hipEventRecord(c->ev_ready[b], s1));
+    if (s1 != c->st) WV_HIP(hipEventRecord(c->ev_ready[b], s1));
 }
 const float* pipe_take(wv_ctx* c, int b)
 {
-    wait_event(c->st, c->ev_ready[b]);
+    if (side_stream(c, 0) != c->st) wait_event(c->st, c->ev_ready[b]);
     return ebuf_slot(c, b);
 }
-void pipe_release(wv_ctx* c, int b) { WV_HIP(hipEventRecord(c->ev_free[b], c->st)); }
+void pipe_release(wv_ctx* c, int b)
+{
+    if (side_stream(c, 0) != c->st) WV_HIP(hipEventRecord(c->ev_free[b], c->st));
+}
 
 float* other_work(wv_ctx* c, const float* cur) { return cur == c->work[0] ? c->work[1] : c->work[0]; }
 
@@ -1046,7 +1056,7 @@ float* forward_sweep(wv_ctx* c, float* traces, const std::vector<int>* snap, flo
         if (ae) {
             out = c->work[j % 3];
             // the buffer and min/max slot held x_{j-3}: its store must be done
-            if (j - 3 >= 1 && j - 3 <= c->T - 1) wait_event(c->st, c->ev_stored[j % 3]);
+            if (j - 3 >= 1 && j - 3 <= c->T - 1 && store_side(c)) wait_event(c->st, c->ev_stored[j % 3]);
         } else {
             out = (snap && (*snap)[j] > 0) ? c->slot_ptr((*snap)[j]) : other_work(c, cur);
         }

@@ -61,9 +61,49 @@ __device__ __forceinline__ unsigned bin_of(const float* meta, const uint16_t* me
     return u >> BIN_SHIFT;
 }
 
+// What follows the list (patches only, st.rng non-null): the decode's range table and, when
+// st.exc is given, the e values of the K patches.
+struct SelectTail {
+    int* rng;            // [nb + 1]
+    int bm, nb;
+    const float* state;  // e field
+    float* exc;          // [K][512]
+    int ny, nx, Py, Px;
+};
+
+__device__ __forceinline__ long long patch_cell(int p, int l, int ny, int nx, int Py, int Px)
+{
+    const int px = p % Px, py = (p / Px) % Py, pz = p / (Px * Py);
+    const long long z = pz * 8 + (l >> 6), y = py * 8 + ((l >> 3) & 7), x = px * 8 + (l & 7);
+    return (z * ny + y) * nx + x;
+}
+
+__device__ __forceinline__ void select_tail(int P, int K, const int* out, const SelectTail& st)
+{
+    if (!st.rng) return;
+    const int tid = threadIdx.x;
+    __syncthreads();  // the list, written by this work-group, is read back
+    // rng[b] = lower bound of patch bm b in the increasing list
+    for (int b2 = tid; b2 <= st.nb; b2 += SEL_THREADS) {
+        const long long target = (long long)b2 * st.bm;
+        int lo = 0, hi = K;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (out[mid] < target) lo = mid + 1;
+            else hi = mid;
+        }
+        st.rng[b2] = lo;
+    }
+    if (!st.exc) return;
+    for (int e = tid; e < K * 512; e += SEL_THREADS) {
+        const int p = out[e >> 9];
+        if (p >= 0 && p < P) st.exc[e] = st.state[patch_cell(p, e & 511, st.ny, st.nx, st.Py, st.Px)];
+    }
+}
+
 __global__ void __launch_bounds__(SEL_THREADS) select_kernel(const float* __restrict__ meta,
                                                              const uint16_t* __restrict__ meta16, int ms, int P, int K,
-                                                             int* __restrict__ out)
+                                                             int* out, const SelectTail st)
 {
     constexpr int BPT = NBIN / SEL_THREADS;  // bins per thread, highest bins to thread 0
     constexpr int KPT = SEL_CHUNK / SEL_THREADS;
@@ -169,6 +209,54 @@ __global__ void __launch_bounds__(SEL_THREADS) select_kernel(const float* __rest
         eqs += s_tot[1];
         __syncthreads();  // skey and s_tot are rewritten by the next chunk
     }
+    select_tail(P, K, out, st);
+}
+
+// The same list for few patches (P <= SEL_FEW): the first wave holds 16 keys per lane
+// (patch 64 q + lane in slot q), finds the bin of the K-th largest by bisection over the bin
+// numbers, counting with ballots, and lists in patch order with the ballots' prefix counts:
+// no barrier, no histogram. The histogram kernel clears and scans 16384 bins whatever P
+// (12 to 17 us for 216 to 1000 patches).
+constexpr int SEL_FEW = 1024;
+__global__ void __launch_bounds__(SEL_THREADS) select_few_kernel(const float* __restrict__ meta,
+                                                                 const uint16_t* __restrict__ meta16, int ms, int P,
+                                                                 int K, int* out, const SelectTail st)
+{
+    constexpr int NQ = SEL_FEW / 64;
+    if (threadIdx.x < 64) {
+        const int lane = threadIdx.x;
+        int key[NQ];  // bins are below 2^14; slots past P hold -1
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int p = q * 64 + lane;
+            key[q] = p < P ? (int)bin_of(meta, meta16, ms, p) : -1;
+        }
+        auto count_from = [&](int b) {  // keys in bins >= b
+            int n = 0;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) n += __popcll(__ballot(key[q] >= b));
+            return n;
+        };
+        int lo = 0, hi = NBIN;  // count_from(lo) >= K > count_from(hi)
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (count_from(mid) >= K) lo = mid;
+            else hi = mid;
+        }
+        const int rem = K - count_from(lo + 1);  // how many of bin lo, in patch order
+        const unsigned long long below = (1ull << lane) - 1;
+        int pos = 0, eqs = 0;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const unsigned long long eq = __ballot(key[q] == lo);
+            const bool pick = key[q] > lo || (key[q] == lo && eqs + __popcll(eq & below) < rem);
+            const unsigned long long picked = __ballot(pick);
+            if (pick) out[pos + __popcll(picked & below)] = q * 64 + lane;
+            pos += __popcll(picked);
+            eqs += __popcll(eq);
+        }
+    }
+    select_tail(P, K, out, st);
 }
 
 // exc[k][l] = e of patch idx[k] at local cell l (one block per patch)
@@ -178,9 +266,7 @@ __global__ void gather_kernel(const float* __restrict__ state, int ny, int nx, i
     const int k = blockIdx.x, l = threadIdx.x;
     const int p = idx[k];
     if (p < 0 || p >= P) return;
-    const int px = p % Px, py = (p / Px) % Py, pz = p / (Px * Py);
-    const long long z = pz * 8 + (l >> 6), y = py * 8 + ((l >> 3) & 7), x = px * 8 + (l & 7);
-    exc[(long long)k * 512 + l] = state[(z * ny + y) * nx + x];
+    exc[(long long)k * 512 + l] = state[patch_cell(p, l, ny, nx, Py, Px)];
 }
 
 __global__ void scatter_kernel(float* __restrict__ e, int ny, int nx, int Py, int Px, int P,
@@ -189,9 +275,7 @@ __global__ void scatter_kernel(float* __restrict__ e, int ny, int nx, int Py, in
     const int k = blockIdx.x, l = threadIdx.x;
     const int p = idx[k];
     if (p < 0 || p >= P) return;
-    const int px = p % Px, py = (p / Px) % Py, pz = p / (Px * Py);
-    const long long z = pz * 8 + (l >> 6), y = py * 8 + ((l >> 3) & 7), x = px * 8 + (l & 7);
-    e[(z * ny + y) * nx + x] = exc[(long long)k * 512 + l];
+    e[patch_cell(p, l, ny, nx, Py, Px)] = exc[(long long)k * 512 + l];
 }
 
 // time scheme: exc[k][t*64 + cell] = e of block idx[k] of source s at level t (the
@@ -231,53 +315,31 @@ __global__ void time_scatter_kernel(float* __restrict__ e_win, int S, int s, int
     *reinterpret_cast<float4*>(dst + nx) = *reinterpret_cast<const float4*>(src + 4);
 }
 
-// rng[b] = lower bound of patch bm b in the increasing list idx [K]
-__global__ void ranges_kernel(const int* __restrict__ idx, int K, int bm, int nb, int* __restrict__ rng)
-{
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b > nb) return;
-    const long long target = (long long)b * bm;
-    int lo = 0, hi = K;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (idx[mid] < target) lo = mid + 1;
-        else hi = mid;
-    }
-    rng[b] = lo;
-}
-
 }  // namespace
 
-void exceptions_select(const PatchGrid& pg, const float* meta, int K, int* idx, hipStream_t st,
-                       const uint16_t* meta16)
+void exceptions_select(const PatchGrid& pg, const float* state, const float* meta, int K, int* idx, int bm, int* rng,
+                       float* exc, hipStream_t st, const uint16_t* meta16)
 {
     if (K <= 0) return;
     WV_REQUIRE(K <= pg.P, WV_EINVAL, "more exception patches than patches");
     WV_REQUIRE(pg.P < (1LL << 31), WV_EINVAL, "too many patches for the exception selector");
-    hipLaunchKernelGGL(select_kernel, dim3(1), dim3(SEL_THREADS), 0, st, meta, meta16, 8, (int)pg.P, K, idx);
+    WV_REQUIRE(rng && exc && state, WV_EINVAL, "null exception buffer");
+    // 64 patches of 2 KiB take the selecting work-group about 2 us more; a launch of its own
+    // for 4 patches took 4 (and the range table 5)
+    const SelectTail tail{rng, bm, (int)((pg.P + bm - 1) / bm), state, exceptions_fused(K) ? exc : nullptr,
+                          pg.ny, pg.nx, pg.ny / 8, pg.nx / 8};
+    if (pg.P <= SEL_FEW)
+        hipLaunchKernelGGL(select_few_kernel, dim3(1), dim3(SEL_THREADS), 0, st, meta, meta16, 8, (int)pg.P, K, idx, tail);
+    else
+        hipLaunchKernelGGL(select_kernel, dim3(1), dim3(SEL_THREADS), 0, st, meta, meta16, 8, (int)pg.P, K, idx, tail);
     WV_HIP(hipGetLastError());
 }
 
 void exceptions_gather(const PatchGrid& pg, const float* state, int K, const int* idx, float* exc, hipStream_t st)
 {
-    if (K <= 0) return;
+    if (K <= 0 || exceptions_fused(K)) return;
     hipLaunchKernelGGL(gather_kernel, dim3(K), dim3(512), 0, st, state, pg.ny, pg.nx, pg.ny / 8, pg.nx / 8, (int)pg.P,
                        idx, exc);
-    WV_HIP(hipGetLastError());
-}
-
-void exceptions_store(const PatchGrid& pg, const float* state, const float* meta, int K, int* idx, float* exc,
-                      hipStream_t st, const uint16_t* meta16)
-{
-    if (K <= 0) return;
-    exceptions_select(pg, meta, K, idx, st, meta16);
-    exceptions_gather(pg, state, K, idx, exc, st);
-}
-
-void exceptions_ranges(const PatchGrid& pg, int K, const int* idx, int bm, int* rng, hipStream_t st)
-{
-    const int nb = (int)((pg.P + bm - 1) / bm);
-    hipLaunchKernelGGL(ranges_kernel, dim3((nb + 1 + 255) / 256), dim3(256), 0, st, idx, K, bm, nb, rng);
     WV_HIP(hipGetLastError());
 }
 
@@ -295,7 +357,8 @@ void time_exceptions_store(const TimeGrid& tg, const float* e_win, int s, int nv
     if (K <= 0) return;
     WV_REQUIRE(K <= tg.B, WV_EINVAL, "more exception vectors than blocks");
     WV_REQUIRE(tg.B < (1LL << 31), WV_EINVAL, "too many blocks for the exception selector");
-    hipLaunchKernelGGL(select_kernel, dim3(1), dim3(SEL_THREADS), 0, st, meta, nullptr, 2, (int)tg.B, K, idx);
+    hipLaunchKernelGGL(select_kernel, dim3(1), dim3(SEL_THREADS), 0, st, meta, nullptr, 2, (int)tg.B, K, idx,
+                       SelectTail{});
     const long long N = (long long)tg.nz * tg.ny * tg.nx;
     hipLaunchKernelGGL(time_gather_kernel, dim3(K), dim3(256), 0, st, e_win, tg.S, s, tg.ny, tg.nx, N, tg.ny / 4,
                        tg.nx / 4, tg.B, nvalid, idx, exc);
