@@ -326,7 +326,11 @@ struct wv_ctx {
     float* prior_c0 = nullptr;
     float* prior_w = nullptr;    // A (c - c0) or A dc
     float* nvec = nullptr;       // [8][N]: g, trial g, trial c, p, r, d, H d, M r
-    float* pvec = nullptr;       // [4][N]: the inner CG of the elliptic solves
+    float* pvec = nullptr;       // [5][N]: the inner CG of the elliptic solves
+    double* cg_part = nullptr;   // its partial dots
+    CgState* cg_state = nullptr;
+    CgState* cg_host = nullptr;  // pinned [2]: the state after the last two batches
+    hipEvent_t ev_cg[2] = {};
 
     long long state_floats() const { return 4LL * N * S; }
     float* slot_ptr(int b) const { return slots + (long long)(b - 1) * state_floats(); }
@@ -1330,6 +1334,11 @@ int wv_destroy(wv_ctx* c)
     dev_free(c->partial);
     dev_free(c->dscal);
     dev_free(c->dflag);
+    dev_free(c->cg_part);
+    dev_free(c->cg_state);
+    if (c->cg_host) (void)hipHostFree(c->cg_host);
+    for (hipEvent_t e : c->ev_cg)
+        if (e) (void)hipEventDestroy(e);
     delete c;
     return WV_OK;
 }
@@ -1946,35 +1955,70 @@ void prior_hv(wv_ctx* c, const float* dc, float* Hdc)
 }
 
 // conjugate gradients on A x = b from x = 0 (A symmetric positive definite) until
-// |r| <= rtol |b| or maxit iterations, with the inner work vectors pvec[1..3];
+// |r| <= rtol |b| or maxit iterations, with the inner work vectors pvec[1..4];
 // returns the iterations, *rel the final relative residual
+//
+// The iterations are queued CG_BATCH at a time, one batch ahead of the host's look at the
+// state that the previous one left: the GPU never waits for the host, and the launches queued
+// past the last iteration return at once.
+constexpr int CG_BATCH = 8;
 int prior_solve(wv_ctx* c, const float* b, float* x, double rtol, int maxit, double* rel_out)
 {
     const long long N = c->N;
-    if (!c->pvec) c->pvec = dev_alloc<float>(4 * (size_t)N);
-    float* r = c->pvec + N;
-    float* d = c->pvec + 2 * N;
-    float* Ad = c->pvec + 3 * N;
-    launch_fill(x, N, 0.f, c->st);
-    launch_copy(r, b, N, c->st);
-    launch_copy(d, r, N, c->st);
-    double rr = dot_host(c, r, r);
-    const double bn = std::sqrt(rr);
-    int it = 0;
-    double rel = bn > 0.0 ? 1.0 : 0.0;
-    while (rel > rtol && it < maxit) {
-        apply_prior(c, d, nullptr, Ad, 1.0, false);
-        const double a = rr / dot_host(c, d, Ad);
-        launch_axpby(x, d, a, 1.0, N, c->st);
-        launch_axpby(r, Ad, -a, 1.0, N, c->st);
-        const double rr_new = dot_host(c, r, r);
-        ++it;
-        rel = std::sqrt(rr_new) / bn;
-        launch_axpby(d, r, 1.0, rr_new / rr, N, c->st);
-        rr = rr_new;
+    if (!c->pvec) c->pvec = dev_alloc<float>(5 * (size_t)N);
+    if (!c->cg_host) WV_HIP(hipHostMalloc((void**)&c->cg_host, 2 * sizeof(CgState), hipHostMallocDefault));
+    if (!c->ev_cg[0])
+        for (hipEvent_t& e : c->ev_cg) WV_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    const double h2 = c->g.dx * c->g.dx;
+    CgParams p{};
+    cg_plan(p, c->g.nz, c->g.ny, c->g.nx, c->prior_alpha, c->prior_theta[0] / h2, c->prior_theta[1] / h2,
+            c->prior_theta[2] / h2);
+    WV_REQUIRE(!p.wide || ((uintptr_t)x | (uintptr_t)c->pvec) % 16 == 0, WV_EINVAL, "misaligned work vectors");
+    if (!c->cg_part) {
+        c->cg_part = dev_alloc<double>(2 * (size_t)p.nb_r + p.nb_d);
+        c->cg_state = dev_alloc<CgState>(1);
     }
-    if (rel_out) *rel_out = rel;
-    return it;
+    float* const dir[2] = {c->pvec + 2 * N, c->pvec + 4 * N};
+    double* const part[2] = {c->cg_part, c->cg_part + p.nb_r};
+    p.x = x;
+    p.r = c->pvec + N;
+    p.Ad = c->pvec + 3 * N;
+    p.part_d = c->cg_part + 2 * p.nb_r;
+    p.st = c->cg_state;
+    p.rtol = rtol;
+    p.part_r = part[0];
+    launch_cg_init(p, b, c->st);
+    int queued = 0;
+    for (int batch = 0;; ++batch) {
+        const bool last = queued == maxit;
+        for (int q = 0; q < CG_BATCH && queued < maxit; ++q, ++queued) {
+            p.it = queued;
+            p.part_r = part[queued & 1];
+            p.part_next = part[(queued + 1) & 1];
+            p.d_in = dir[queued & 1];
+            p.d_out = dir[(queued + 1) & 1];
+            launch_cg_iteration(p, c->st);
+        }
+        if (queued == maxit && !last) {
+            p.it = queued;
+            p.part_r = part[queued & 1];
+            launch_cg_check(p, c->st);
+        }
+        if (!last) {
+            WV_HIP(hipMemcpyAsync(c->cg_host + (batch & 1), c->cg_state, sizeof(CgState), hipMemcpyDeviceToHost, c->st));
+            WV_HIP(hipEventRecord(c->ev_cg[batch & 1], c->st));
+        }
+        if (batch == 0) continue;
+        const int prev = (batch - 1) & 1;
+        WV_HIP(hipEventSynchronize(c->ev_cg[prev]));
+        const CgState s = c->cg_host[prev];
+        if (s.done || last) {
+            // the batch queued ahead copies into the other slot: done before the buffers are reused
+            if (!last) WV_HIP(hipEventSynchronize(c->ev_cg[batch & 1]));
+            if (rel_out) *rel_out = s.rel;
+            return s.it;
+        }
+    }
 }
 
 // z = (dx^dims A A)^-1 r, the prior covariance (two elliptic solves)
@@ -1982,7 +2026,7 @@ constexpr double PREC_RTOL = 1e-6;
 constexpr int PREC_MAXIT = 1000;
 void prior_covariance(wv_ctx* c, const float* r, float* z)
 {
-    if (!c->pvec) c->pvec = dev_alloc<float>(4 * (size_t)c->N);
+    if (!c->pvec) c->pvec = dev_alloc<float>(5 * (size_t)c->N);
     float* y = c->pvec;
     prior_solve(c, r, y, PREC_RTOL, PREC_MAXIT, nullptr);
     launch_axpby(y, y, 1.0 / cell_volume(c), 0.0, c->N, c->st);

@@ -8,6 +8,8 @@
 // All of these kernels stream their vectors once; they are HBM-bound and cost
 // microseconds beside the solves of a gradient or a Hessian-vector product.
 
+#include <algorithm>
+
 #include "wv_internal.h"
 
 namespace wv {
@@ -104,6 +106,238 @@ __global__ void dot_finalize(const double* __restrict__ partial, int n, double* 
     if (threadIdx.x == 0) out[0] = t;
 }
 
+// ---- conjugate gradients on A x = b with the scalars on the device ---------------------
+// One iteration is two launches, each streaming its vectors once:
+//   direction: d' = r + beta d (into the other direction buffer), A d' and its dot with d';
+//   update:    x += alpha d', r -= alpha A d', and r.r.
+// 40 B per cell and iteration (a launch per vector operation moved 60 and cost two host
+// round trips; 256^3: 260 us per iteration, 125 now). Every work-group sums the partial dots of
+// the launch before, in a fixed order, so no launch of its own reduces them; work-group 0
+// keeps the scalars. Once converged, the launches already queued return at once.
+
+// sum of n partials by the whole work-group, in a fixed order; every thread gets it
+__device__ inline double block_total(const double* __restrict__ partial, int n)
+{
+    __shared__ double total;
+    double acc = 0.0;
+    for (int q = threadIdx.x; q < n; q += DB) acc += partial[q];
+    const double t = dblock_sum(acc);
+    if (threadIdx.x == 0) total = t;
+    __syncthreads();
+    const double r = total;
+    __syncthreads();
+    return r;
+}
+
+// x = 0, r = b and the partials of b.b
+__global__ void __launch_bounds__(DB) cg_init_kernel(const float* __restrict__ b, float* __restrict__ x,
+                                                    float* __restrict__ r, long long n, double* __restrict__ part_r,
+                                                    CgState* __restrict__ st)
+{
+    double acc = 0.0;
+    for (long long q = blockIdx.x * (long long)DB + threadIdx.x; q < n; q += (long long)gridDim.x * DB) {
+        const float v = b[q];
+        x[q] = 0.f;
+        r[q] = v;
+        acc += (double)v * (double)v;
+    }
+    const double t = dblock_sum(acc);
+    if (threadIdx.x == 0) {
+        part_r[blockIdx.x] = t;
+        if (blockIdx.x == 0) st->done = 0;
+    }
+}
+
+// The scalars at the start of iteration `it` (r.r = rr): sets *beta and tells whether the
+// solve goes on. The state's two r.r slots take turns, so that work-group 0 does not
+// overwrite the one that the others still read.
+__device__ inline bool cg_scalars(const CgParams& c, double rr, float* beta)
+{
+    CgState* st = c.st;
+    const double bn = c.it == 0 ? sqrt(rr) : st->bn;
+    const double rel = c.it == 0 ? (bn > 0.0 ? 1.0 : 0.0) : sqrt(rr) / bn;
+    *beta = c.it == 0 ? 0.f : (float)(rr / st->rr[(c.it + 1) & 1]);
+    const bool go = rel > c.rtol;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (c.it == 0) st->bn = bn;
+        st->rr[c.it & 1] = rr;
+        st->rel = rel;
+        st->it = c.it;
+        if (!go) st->done = 1;
+    }
+    return go;
+}
+
+// the scalars alone, after the last iteration
+__global__ void __launch_bounds__(DB) cg_check_kernel(const CgParams c)
+{
+    if (c.st->done) return;
+    float beta;
+    (void)cg_scalars(c, block_total(c.part_r, c.nb_r), &beta);
+}
+
+// A work-group holds CG_TY rows of CG_TX lanes (VX cells each) and marches over kc levels; d'
+// of the level sits in LDS with a one-cell ring (whose d' the ring's threads form anew), the
+// levels below and above in registers. The next level's r and d are loaded while one is
+// computed. Boundary faces carry no flux.
+constexpr int CG_TX = 32, CG_TY = 8;
+template <int VX>
+__global__ void __launch_bounds__(DB) cg_direction_kernel(const CgParams c)
+{
+    // the products fused with an addition are written out, as in prior_kernel and axpby_kernel
+#pragma clang fp contract(off)
+    static_assert(CG_TX * CG_TY == DB, "one thread per lane of a row");
+    constexpr int W = CG_TX * VX;
+    __shared__ __attribute__((aligned(16))) float sD[2][CG_TY + 2][W + 8];  // cell x at column x + 4
+    if (c.st->done) return;
+    float beta;
+    if (!cg_scalars(c, block_total(c.part_r, c.nb_r), &beta)) return;
+
+    const int tx = threadIdx.x % CG_TX, ty = threadIdx.x / CG_TX;
+    const int txx = blockIdx.x % c.tiles_x, tyy = (blockIdx.x / c.tiles_x) % c.tiles_y;
+    const int cz = blockIdx.x / (c.tiles_x * c.tiles_y);
+    const int i = txx * W + tx * VX, j = tyy * CG_TY + ty;
+    const bool inside = i < c.nx && j < c.ny;  // VX divides nx
+    const int k0 = cz * c.kc, k1 = min(c.nz, k0 + c.kc);
+    const long long plane = (long long)c.ny * c.nx;
+    const long long cell = inside ? (long long)j * c.nx + i : 0;
+    // ring: the rows before and after the tile (threads of its first and last row), the columns
+    // beside it (its first and last lane); absent ones read their own cell, unused
+    const bool row_lo = ty == 0, row_hi = ty == CG_TY - 1;
+    const bool has_row = inside && (row_lo ? j > 0 : row_hi && j + 1 < c.ny);
+    const long long rcell = has_row ? (long long)(row_lo ? j - 1 : j + 1) * c.nx + i : cell;
+    const bool col_lo = tx == 0, col_hi = tx == CG_TX - 1;
+    const bool has_col = inside && (col_lo ? i > 0 : col_hi && i + VX < c.nx);
+    const long long ecell = has_col ? (long long)j * c.nx + (col_lo ? i - 1 : i + VX) : cell;
+    const bool first = c.it == 0;
+    auto dir = [&](float r, float d) { return first ? r : r + beta * d; };
+    struct Lev {
+        float r[VX], d[VX];
+    };
+    auto load = [&](long long at, Lev& v) {
+        if constexpr (VX == 4) {
+            const float4 a = *reinterpret_cast<const float4*>(c.r + at), b = *reinterpret_cast<const float4*>(c.d_in + at);
+            v.r[0] = a.x; v.r[1] = a.y; v.r[2] = a.z; v.r[3] = a.w;
+            v.d[0] = b.x; v.d[1] = b.y; v.d[2] = b.z; v.d[3] = b.w;
+        } else {
+            v.r[0] = c.r[at];
+            v.d[0] = c.d_in[at];
+        }
+    };
+    float lo[VX], cur[VX];
+    Lev nxt, row;
+    float er, ed;
+    {
+        Lev a, b;
+        load(cell + (long long)max(k0 - 1, 0) * plane, a);
+        load(cell + (long long)k0 * plane, b);
+        load(cell + (long long)min(k0 + 1, c.nz - 1) * plane, nxt);
+        load(rcell + (long long)k0 * plane, row);
+        er = c.r[ecell + (long long)k0 * plane];
+        ed = c.d_in[ecell + (long long)k0 * plane];
+#pragma unroll
+        for (int u = 0; u < VX; ++u) {
+            lo[u] = dir(a.r[u], a.d[u]);
+            cur[u] = dir(b.r[u], b.d[u]);
+        }
+    }
+    double acc = 0.0;
+    for (int k = k0; k < k1; ++k) {
+        float(*s)[W + 8] = sD[k & 1];
+        float hi[VX];
+#pragma unroll
+        for (int u = 0; u < VX; ++u) {
+            hi[u] = dir(nxt.r[u], nxt.d[u]);
+            s[ty + 1][tx * VX + u + 4] = cur[u];
+        }
+        if (row_lo || row_hi) {
+            const int y = row_lo ? 0 : CG_TY + 1;
+#pragma unroll
+            for (int u = 0; u < VX; ++u) s[y][tx * VX + u + 4] = dir(row.r[u], row.d[u]);
+        }
+        if (col_lo || col_hi) s[ty + 1][col_lo ? 3 : W + 4] = dir(er, ed);
+        __syncthreads();  // the other buffer serves the next level: one barrier per level
+        const long long at = (long long)k * plane;
+        if (k + 1 < k1) {
+            load(cell + (long long)min(k + 2, c.nz - 1) * plane, nxt);
+            load(rcell + at + plane, row);
+            er = c.r[ecell + at + plane];
+            ed = c.d_in[ecell + at + plane];
+        }
+        float out[VX];
+#pragma unroll
+        for (int u = 0; u < VX; ++u) {
+            const int x = tx * VX + u + 4;
+            const float w = cur[u];
+            float flux = 0.f;
+            if (k > 0) flux = __builtin_fmaf(c.cz, lo[u] - w, flux);
+            if (k < c.nz - 1) flux = __builtin_fmaf(c.cz, hi[u] - w, flux);
+            if (j > 0) flux = __builtin_fmaf(c.cy, s[ty][x] - w, flux);
+            if (j < c.ny - 1) flux = __builtin_fmaf(c.cy, s[ty + 2][x] - w, flux);
+            if (i + u > 0) flux = __builtin_fmaf(c.cx, s[ty + 1][x - 1] - w, flux);
+            if (i + u < c.nx - 1) flux = __builtin_fmaf(c.cx, s[ty + 1][x + 1] - w, flux);
+            out[u] = c.alpha * (w - flux);
+            if (inside) acc = fma((double)w, (double)out[u], acc);
+        }
+        if (inside) {
+            if constexpr (VX == 4) {
+                *reinterpret_cast<float4*>(c.d_out + cell + at) = make_float4(cur[0], cur[1], cur[2], cur[3]);
+                *reinterpret_cast<float4*>(c.Ad + cell + at) = make_float4(out[0], out[1], out[2], out[3]);
+            } else {
+                c.d_out[cell + at] = cur[0];
+                c.Ad[cell + at] = out[0];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < VX; ++u) {
+            lo[u] = cur[u];
+            cur[u] = hi[u];
+        }
+    }
+    const double t = dblock_sum(acc);
+    if (threadIdx.x == 0) c.part_d[blockIdx.x] = t;
+}
+
+template <int VX>
+__global__ void __launch_bounds__(DB) cg_update_kernel(const CgParams c)
+{
+#pragma clang fp contract(off)
+    if (c.st->done) return;
+    const double dAd = block_total(c.part_d, c.nb_d);
+    const double a = c.st->rr[c.it & 1] / dAd;
+    const float alpha = (float)a, nalpha = (float)-a;
+    double acc = 0.0;
+    const long long n = c.n / VX;
+    for (long long q = blockIdx.x * (long long)DB + threadIdx.x; q < n; q += (long long)gridDim.x * DB) {
+        float x[VX], r[VX], d[VX], Ad[VX];
+        if constexpr (VX == 4) {
+            const float4 vx = reinterpret_cast<const float4*>(c.x)[q], vr = reinterpret_cast<const float4*>(c.r)[q];
+            const float4 vd = reinterpret_cast<const float4*>(c.d_out)[q], va = reinterpret_cast<const float4*>(c.Ad)[q];
+            x[0] = vx.x; x[1] = vx.y; x[2] = vx.z; x[3] = vx.w;
+            r[0] = vr.x; r[1] = vr.y; r[2] = vr.z; r[3] = vr.w;
+            d[0] = vd.x; d[1] = vd.y; d[2] = vd.z; d[3] = vd.w;
+            Ad[0] = va.x; Ad[1] = va.y; Ad[2] = va.z; Ad[3] = va.w;
+        } else {
+            x[0] = c.x[q]; r[0] = c.r[q]; d[0] = c.d_out[q]; Ad[0] = c.Ad[q];
+        }
+#pragma unroll
+        for (int u = 0; u < VX; ++u) {
+            x[u] = __builtin_fmaf(alpha, d[u], x[u]);
+            r[u] = __builtin_fmaf(nalpha, Ad[u], r[u]);
+            acc = fma((double)r[u], (double)r[u], acc);
+        }
+        if constexpr (VX == 4) {
+            reinterpret_cast<float4*>(c.x)[q] = make_float4(x[0], x[1], x[2], x[3]);
+            reinterpret_cast<float4*>(c.r)[q] = make_float4(r[0], r[1], r[2], r[3]);
+        } else {
+            c.x[q] = x[0];
+            c.r[q] = r[0];
+        }
+    }
+    const double t = dblock_sum(acc);
+    if (threadIdx.x == 0) c.part_next[blockIdx.x] = t;
+}
+
 }  // namespace
 
 void launch_prior(const float* u, const float* u0, float* out, int nz, int ny, int nx, double alpha, double cz,
@@ -132,6 +366,55 @@ void launch_dot(const float* a, const float* b, long long n, double* partial, in
 {
     hipLaunchKernelGGL(dot_kernel, dim3(nblocks), dim3(DB), 0, st, a, b, n, partial);
     hipLaunchKernelGGL(dot_finalize, dim3(1), dim3(DB), 0, st, partial, nblocks, d_out);
+    WV_HIP(hipGetLastError());
+}
+
+void cg_plan(CgParams& c, int nz, int ny, int nx, double alpha, double cz, double cy, double cx)
+{
+    c.nz = nz;
+    c.ny = ny;
+    c.nx = nx;
+    c.n = (long long)nz * ny * nx;
+    c.alpha = (float)alpha;
+    c.cz = (float)cz;
+    c.cy = (float)cy;
+    c.cx = (float)cx;
+    c.wide = nx % 4 == 0;
+    const int w = CG_TX * (c.wide ? 4 : 1);
+    c.tiles_x = (nx + w - 1) / w;
+    c.tiles_y = (ny + CG_TY - 1) / CG_TY;
+    // chunks of levels until about CG_BLOCKS work-groups (4 per CU), at least one level each:
+    // more of them read more chunk ends and sum more partials, fewer leave CUs idle (a draw at
+    // 256^3 / 101 x 118 x 131 in ms: 14.3 / 2.08 with 512, 14.5 / 1.97 with 1024, 14.7 / 2.15
+    // with 2048, 15.5 / 2.49 with 4096)
+    const long long tiles = (long long)c.tiles_x * c.tiles_y;
+    const int chunks = (int)std::max<long long>(1, std::min<long long>(nz, CG_BLOCKS / tiles));
+    c.kc = (nz + chunks - 1) / chunks;
+    c.nb_d = (int)(tiles * ((nz + c.kc - 1) / c.kc));
+    c.nb_r = (int)std::max<long long>(1, std::min<long long>(CG_BLOCKS, (c.n + 4 * DB - 1) / (4 * DB)));
+}
+
+void launch_cg_init(const CgParams& c, const float* b, hipStream_t st)
+{
+    hipLaunchKernelGGL(cg_init_kernel, dim3(c.nb_r), dim3(DB), 0, st, b, c.x, c.r, c.n, c.part_r, c.st);
+    WV_HIP(hipGetLastError());
+}
+
+void launch_cg_iteration(const CgParams& c, hipStream_t st)
+{
+    if (c.wide) {
+        hipLaunchKernelGGL(cg_direction_kernel<4>, dim3(c.nb_d), dim3(DB), 0, st, c);
+        hipLaunchKernelGGL(cg_update_kernel<4>, dim3(c.nb_r), dim3(DB), 0, st, c);
+    } else {
+        hipLaunchKernelGGL(cg_direction_kernel<1>, dim3(c.nb_d), dim3(DB), 0, st, c);
+        hipLaunchKernelGGL(cg_update_kernel<1>, dim3(c.nb_r), dim3(DB), 0, st, c);
+    }
+    WV_HIP(hipGetLastError());
+}
+
+void launch_cg_check(const CgParams& c, hipStream_t st)
+{
+    hipLaunchKernelGGL(cg_check_kernel, dim3(1), dim3(DB), 0, st, c);
     WV_HIP(hipGetLastError());
 }
 

@@ -130,4 +130,32 @@ void launch_lincomb(float* out, const float* x, double a, const float* y, long l
 void launch_dot(const float* a, const float* b, long long n, double* partial, int nblocks, double* d_out,
                 hipStream_t st);
 
+// conjugate gradients on the prior operator, scalars on the device (inverse.hip)
+struct CgState {
+    double rr[2];  // r.r of the even and odd iterations
+    double bn;     // |b|
+    double rel;    // |r| / |b| at the start of iteration it
+    int it, done;
+};
+constexpr int CG_BLOCKS = 1024;  // work-groups aimed at per launch
+struct CgParams {
+    int nz, ny, nx;
+    long long n;
+    float alpha, cz, cy, cx;
+    int tiles_x, tiles_y, kc;
+    bool wide;               // four cells per lane (nx divisible by 4)
+    int nb_d, nb_r;          // work-groups of the direction and the update launch
+    float *x, *r, *Ad;
+    const float* d_in;       // the direction before this iteration, and this one's
+    float* d_out;
+    double *part_d, *part_r, *part_next;  // partials of d.Ad, of r.r, and of the next r.r
+    CgState* st;
+    double rtol;
+    int it;
+};
+void cg_plan(CgParams& c, int nz, int ny, int nx, double alpha, double cz, double cy, double cx);
+void launch_cg_init(const CgParams& c, const float* b, hipStream_t st);
+void launch_cg_iteration(const CgParams& c, hipStream_t st);
+void launch_cg_check(const CgParams& c, hipStream_t st);
+
 }  // namespace wv
