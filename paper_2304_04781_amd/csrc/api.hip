@@ -222,6 +222,10 @@ struct wv_ctx {
     float* tab = nullptr;  // wzc wzf wyc wyf wxc wxf
     float *wzc = nullptr, *wzf = nullptr, *wyc = nullptr, *wyf = nullptr, *wxc = nullptr, *wxf = nullptr;
     Tiling tl;
+    // 2D grids that step several levels per launch: their receivers by region
+    bool plane = false;
+    int* pl_ptr = nullptr;
+    int2* pl_ent = nullptr;
 
     int* src_kji = nullptr;      // [S][3]
     float* src_w = nullptr;      // source stencil weights
@@ -494,6 +498,50 @@ void inc_step(wv_ctx* c, const float* in, float* out, int n, const float* en, lo
     a.enstride = enstride;
     const int t = c->tm.begin(TM_INC, c->st);
     launch_step(MODE_INC, c->has_y, a, c->S, c->st);
+    c->tm.end(t, c->st);
+}
+
+static_assert(PL_STEPS == WV_ACC_BLOCK, "a launch of adjoint steps is one accumulation block");
+
+// nsteps steps of a 2D grid from level n (forward, incremental) or down from level k (adjoint)
+PlaneArgs plane_args(const wv_ctx* c, const float* in, float* out, int tidx, int nsteps)
+{
+    PlaneArgs a{};
+    a.nz = c->g.nz;
+    a.nx = c->g.nx;
+    a.sstride = 4 * c->N;
+    a.dtdx = (float)(c->g.dt / c->g.dx);
+    a.dt = (float)c->g.dt;
+    a.wzc = c->wzc; a.wzf = c->wzf; a.wyc = c->wyc; a.wxc = c->wxc; a.wxf = c->wxf;
+    a.m = c->m;
+    a.in = in;
+    a.out = out;
+    a.nsteps = nsteps;
+    a.tidx = tidx;
+    a.nt = c->T;
+    a.src_kji = c->src_kji;
+    a.src_radius = c->src_radius;
+    a.src_w = c->src_w;
+    a.wavelet = c->wavelet;
+    a.rec_ptr = c->pl_ptr;
+    a.rec_ent = c->pl_ent;
+    a.nrec = c->R;
+    return a;
+}
+
+// forward steps n .. n + ns - 1 of a 2D grid; traces (nullptr: not recorded); the new e of
+// the first nextra steps also to e_extra, S N apart
+void plane_fwd(wv_ctx* c, const float* in, float* out, int n, int ns, float* traces, float* e_extra = nullptr,
+               int nextra = 0)
+{
+    PlaneArgs a = plane_args(c, in, out, n, ns);
+    a.traces = traces;
+    if (!traces) a.nrec = 0;
+    a.e_extra = e_extra;
+    a.xlevel = (long long)c->S * c->N;
+    a.nextra = nextra;
+    const int t = c->tm.begin(TM_FWD, c->st);
+    launch_plane(MODE_FWD, a, c->S, c->st);
     c->tm.end(t, c->st);
 }
 
@@ -1031,6 +1079,40 @@ void run_guard(wv_ctx* c)
     c->degraded = !(worst <= c->guard_tol);
 }
 
+// forward_sweep of a 2D grid, up to PL_STEPS steps per launch: a launch ends at every state
+// that is needed whole (snapshots, captures, and x_{T-1} with snapshots)
+float* plane_forward_sweep(wv_ctx* c, float* traces, const std::vector<int>* snap, float* capture, int every,
+                           float** last, const std::vector<int>* ecap_idx, float* ecap)
+{
+    launch_fill(c->work[0], c->state_floats(), 0.f, c->st);
+    float* cur = c->work[0];
+    float* prev = cur;
+    const int ncap = (capture && every > 0) ? (c->T - 1) / every : 0;
+    auto snapped = [&](int j) { return snap && ((*snap)[j] > 0 || j == c->T - 1); };
+    auto captured = [&](int j) { return ncap > 0 && j % every == 0 && j / every <= ncap; };
+    for (int n = 0; n < c->T;) {
+        const int end = std::min(n + PL_STEPS, c->T);
+        int j = n + 1;
+        while (j < end && !snapped(j) && !captured(j) && !(ecap_idx && (*ecap_idx)[j] >= 0)) ++j;
+        float* out = (snap && (*snap)[j] > 0) ? c->slot_ptr((*snap)[j]) : other_work(c, cur);
+        const bool full = c->mode == WV_STORE_FULL;  // e^{n+1} .. e^j, at most e^{T-1}, into the history
+        plane_fwd(c, cur, out, n, j - n, traces, full ? c->ehist + (long long)n * c->S * c->N : nullptr,
+                  full ? std::min(j, c->T - 1) - n : 0);
+        if (captured(j))
+            WV_HIP(hipMemcpyAsync(capture + (long long)(j / every - 1) * c->state_floats(), out,
+                                  sizeof(float) * c->state_floats(), hipMemcpyDeviceToDevice, c->st));
+        if (ecap_idx && (*ecap_idx)[j] >= 0)
+            for (int s = 0; s < c->S; ++s)
+                launch_copy(ecap + ((long long)(*ecap_idx)[j] * c->S + s) * c->N, out + s * 4 * c->N, c->N, c->st);
+        prev = cur;
+        cur = out;
+        n = j;
+    }
+    c->last_fwd_steps = c->T;
+    if (last) *last = cur;
+    return prev;
+}
+
 // Forward sweep over T steps from the zero state. Records traces, fills the FULL/AE
 // store, writes checkpoint snapshots (snap[n] = slot of x_n or 0), captures.
 // Returns the buffer holding x_{T-1}; *last receives the one holding x_T.
@@ -1045,6 +1127,7 @@ float* forward_sweep(wv_ctx* c, float* traces, const std::vector<int>* snap, flo
         c->ts.cur_w = -1;
         c->tdelta_ok = false;
     }
+    if (c->plane) return plane_forward_sweep(c, traces, snap, capture, every, last, ecap_idx, ecap);
     // autoencoder stores run beside the steps (x_j in work[j % 3])
     const bool ae = is_ae(c->mode) && c->mmpart && c->has_y;
     if (ae && !c->work[2]) c->work[2] = dev_alloc<float>(c->state_floats());
@@ -1121,6 +1204,22 @@ void reverse_sweep(wv_ctx* c, const float* resid, const std::vector<RevAction>* 
         }
         return;
     }
+    if (!acts && c->plane) {
+        // full storage of a 2D grid: one accumulation block per launch
+        for (int k = c->T - 1; k >= 1; k -= PL_STEPS) {
+            PlaneArgs a = plane_args(c, ain, aout, k, std::min(PL_STEPS, k));
+            a.resid = resid;
+            a.estride = c->N;
+            a.elevel = -(long long)c->S * c->N;
+            a.e = c->ehist + (long long)(k - 1) * c->S * c->N;
+            a.acc = c->acc;
+            const int t = c->tm.begin(TM_ADJ, c->st);
+            launch_plane(MODE_ADJ, a, c->S, c->st);
+            c->tm.end(t, c->st);
+            std::swap(ain, aout);
+        }
+        return;
+    }
     if (!acts) {
         for (int k = c->T - 1; k >= 1; --k) {
             long long stride;
@@ -1144,7 +1243,13 @@ void reverse_sweep(wv_ctx* c, const float* resid, const std::vector<RevAction>* 
             }
         } else if (A.kind == 0) {
             const bool to_slot = q + 1 < acts->size() && (*acts)[q + 1].kind == 1;
-            for (int t = 0; t < A.b; ++t) {
+            for (int t = 0; c->plane && t < A.b; t += PL_STEPS) {
+                const int ns = std::min(PL_STEPS, A.b - t);
+                float* out = (to_slot && t + ns == A.b) ? c->slot_ptr((*acts)[q + 1].b) : other_work(c, cur);
+                plane_fwd(c, cur, out, A.a + t, ns, nullptr);
+                cur = out;
+            }
+            for (int t = 0; !c->plane && t < A.b; ++t) {
                 float* out = (to_slot && t == A.b - 1) ? c->slot_ptr((*acts)[q + 1].b) : other_work(c, cur);
                 fwd_step(c, cur, out, A.a + t, nullptr);
                 cur = out;
@@ -1258,6 +1363,18 @@ int wv_create(const wv_grid* grid, const int32_t* h_src, const int32_t* h_rec, v
         check_pts(rec, "receiver");
         build_tables(c.get());
         c->tl = make_tiling(g.nz, g.ny, g.nx, g.nsrc, rec);
+        c->plane = plane_supported(g.nz, g.ny, g.nx, g.nsrc);
+        if (c->plane) {
+            std::vector<int> ptr;
+            std::vector<std::pair<int, int>> ent;
+            region_receivers(g.nz, g.nx, PL_CZ, PL_CX, PL_STEPS, rec, ptr, ent);
+            c->pl_ptr = dev_alloc<int>(ptr.size());
+            WV_HIP(hipMemcpy(c->pl_ptr, ptr.data(), sizeof(int) * ptr.size(), hipMemcpyHostToDevice));
+            std::vector<int2> e2;
+            for (const auto& q : ent) e2.push_back(make_int2(q.first, q.second));
+            c->pl_ent = dev_alloc<int2>(e2.size());
+            if (!e2.empty()) WV_HIP(hipMemcpy(c->pl_ent, e2.data(), sizeof(int2) * e2.size(), hipMemcpyHostToDevice));
+        }
         c->src_kji = dev_alloc<int>(src.size());
         WV_HIP(hipMemcpy(c->src_kji, src.data(), sizeof(int) * src.size(), hipMemcpyHostToDevice));
         const float one = 1.0f;
@@ -1325,6 +1442,8 @@ int wv_destroy(wv_ctx* c)
                 if (e) (void)hipEventDestroy(e);
     dev_free(c->tab);
     dev_free(c->src_kji);
+    dev_free(c->pl_ptr);
+    dev_free(c->pl_ent);
     dev_free(c->src_w);
     for (float** p : {&c->m, &c->c_last, &c->wavelet, &c->work[0], &c->work[1], &c->adj[0], &c->adj[1],
                       &c->incb[0], &c->incb[1], &c->incb[2], &c->acc, &c->blk, &c->ebuf, &c->dm, &c->traces,
@@ -1736,6 +1855,28 @@ float* inc_forward_sweep(wv_ctx* c, const float* cdev, const float* dc, const st
     if (ckpt) {
         launch_fill(c->work[0], c->state_floats(), 0.f, c->st);
         cur = c->work[0];
+    }
+    if (c->plane && !ckpt) {
+        // full storage of a 2D grid, up to PL_STEPS steps per launch
+        for (int n = 0; n < c->T; n += PL_STEPS) {
+            PlaneArgs a = plane_args(c, din, dout, n, std::min(PL_STEPS, c->T - n));
+            a.traces = c->dtr;
+            a.dm = c->dm;
+            a.estride = c->N;
+            a.elevel = (long long)c->S * c->N;
+            a.e = c->ehist + (long long)(n - 1) * c->S * c->N;  // e^0 = 0 is not read (en0)
+            a.en0 = n > 0;
+            if (keep_full) {
+                a.e_extra = c->dehist + (long long)n * c->S * c->N;
+                a.xlevel = (long long)c->S * c->N;
+                a.nextra = std::min(n + a.nsteps, c->T - 1) - n;
+            }
+            const int t = c->tm.begin(TM_INC, c->st);
+            launch_plane(MODE_INC, a, c->S, c->st);
+            c->tm.end(t, c->st);
+            std::swap(din, dout);
+        }
+        return nullptr;
     }
     for (int n = 0; n < c->T; ++n) {
         const float* en;

@@ -58,4 +58,29 @@ void bucket_receivers(int nz, int bx, int by, int tiles_x, int tiles_y, const st
     }
 }
 
+void region_receivers(int nz, int nx, int cz, int cx, int h, const std::vector<int>& rec_kji, std::vector<int>& ptr,
+                      std::vector<std::pair<int, int>>& ent)
+{
+    WV_REQUIRE(nz >= 1 && nx >= 1 && cz >= 1 && cx >= 1 && h >= 0 && rec_kji.size() % 3 == 0, WV_EINVAL,
+               "region_receivers: bad sizes");
+    const int tz = (nz + cz - 1) / cz, tx = (nx + cx - 1) / cx;
+    const int n = (int)(rec_kji.size() / 3);
+    std::vector<std::vector<std::pair<int, int>>> per((size_t)tz * tx);
+    for (int q = 0; q < n; ++q) {
+        const int k = rec_kji[3 * q], i = rec_kji[3 * q + 2];
+        WV_REQUIRE(k >= 0 && k < nz && i >= 0 && i < nx, WV_EINVAL, "region_receivers: receiver outside the grid");
+        // the tiles whose region holds the cell: within h cells of it
+        for (int a = std::max(k - h, 0) / cz; a <= std::min((k + h) / cz, tz - 1); ++a)
+            for (int b = std::max(i - h, 0) / cx; b <= std::min((i + h) / cx, tx - 1); ++b)
+                per[(size_t)a * tx + b].push_back({(k - (a * cz - h)) * (cx + 2 * h) + i - (b * cx - h), q});
+    }
+    ptr.assign(1, 0);
+    ent.clear();
+    for (auto& v : per) {
+        std::sort(v.begin(), v.end());
+        ent.insert(ent.end(), v.begin(), v.end());
+        ptr.push_back((int)ent.size());
+    }
+}
+
 }  // namespace wv

@@ -7,6 +7,7 @@
 #include <cstddef>
 #include <cstdint>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "wavecomp.h"
@@ -66,5 +67,12 @@ static_assert(sizeof(RecEnt) == 16, "RecEnt is copied to the device as an int4")
 // Indices must lie inside the nz x (tiles_y by) x (tiles_x bx) box (WV_EINVAL otherwise).
 void bucket_receivers(int nz, int bx, int by, int tiles_x, int tiles_y, const std::vector<int>& rec_kji,
                       std::vector<int>& ptr, std::vector<RecEnt>& ent);
+
+// Receivers (k, j, i triples; j ignored) of overlapping regions of a 2D grid: work-group
+// tile t = (k / cz) tiles_x + i / cx covers rows [cz tz - h, cz tz + cz + h) and columns
+// [cx tx - h, cx tx + cx + h); its receivers are ent[ptr[t] .. ptr[t + 1]), as (row (cx + 2 h) +
+// column within the region, receiver), in that order.
+void region_receivers(int nz, int nx, int cz, int cx, int h, const std::vector<int>& rec_kji, std::vector<int>& ptr,
+                      std::vector<std::pair<int, int>>& ent);
 
 }  // namespace wv

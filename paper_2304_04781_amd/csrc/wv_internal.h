@@ -95,6 +95,49 @@ void launch_step(int mode, bool has_y, const StepArgs& a, int nsrc, hipStream_t 
 Tiling make_tiling(int nz, int ny, int nx, int nsrc, const std::vector<int>& rec_kji);
 void free_tiling(Tiling& t);
 
+// ---- several steps of a 2D grid per launch (plane.hip) --------------------------------
+
+constexpr int PL_STEPS = 8;            // steps per launch at most: one accumulation block of the adjoint
+constexpr int PL_CZ = 8, PL_CX = 16;   // core cells of a work-group
+constexpr int PL_MAX_WGS = 4096;       // larger grids step by step
+struct PlaneArgs {
+    int nz, nx;
+    long long sstride;
+    float dtdx, dt;
+    const float *wzc, *wzf, *wyc, *wxc, *wxf;
+    const float* m;
+    const float* in;
+    float* out;
+    int nsteps;
+    // level of the first step: n (forward, incremental; the next ones n + 1, ...) or k
+    // (adjoint; k - 1, ...), the index into traces, residual and wavelet rows
+    int tidx, nt;
+    const int* src_kji;
+    int src_radius;
+    const float* src_w;
+    const float* wavelet;
+    // receivers whose face lies in a work-group's region (halo included): entries
+    // [rec_ptr[tile] .. rec_ptr[tile + 1]) of (cell of the region, receiver), in that order
+    const int* rec_ptr;
+    const int2* rec_ent;
+    int nrec;
+    float* traces;
+    const float* resid;
+    // history e of the first step's level (adjoint e^k, incremental e^n; en0 false: that one
+    // is e^0 = 0), elevel floats to the next step's, estride between sources
+    const float* e;
+    long long estride, elevel;
+    int en0;
+    float* acc;             // adjoint: [S][2][N]; a launch is one accumulation block
+    const float* dm;        // incremental
+    float* e_extra;         // new e of the first nextra steps, xlevel floats apart
+    long long xlevel;
+    int nextra;
+};
+bool plane_supported(int nz, int ny, int nx, int nsrc);
+// one launch of a.nsteps steps: MODE_FWD, MODE_INC or MODE_ADJ
+void launch_plane(int mode, const PlaneArgs& a, int nsrc, hipStream_t st);
+
 // ---- reductions / elementwise -------------------------------------------------------
 
 void launch_square(const float* c, float* m, long long n, hipStream_t st);
