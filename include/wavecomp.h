@@ -499,8 +499,9 @@ int wv_stats(const wv_ctx* ctx, int64_t* h_forward_steps, double* h_guard_err, i
  * clears the totals. */
 int wv_set_timing(wv_ctx* ctx, int32_t every);
 
-/* Mean duration in microseconds and number of timed launches since the last
- * wv_set_timing, for one class: 0 forward stencil step, 1 adjoint stencil step,
+/* Mean duration in microseconds and number of timed calls since the last
+ * wv_set_timing, for one class (a launch that takes several stencil steps counts as
+ * so many, each with its share of the duration): 0 forward stencil step, 1 adjoint stencil step,
  * 2 incremental-forward stencil step, 3 compression of one state (all sources),
  * 4 decompression of e of one level, all sources (exception patches exact),
  * 5 selection of the exception patches of one state, 6 a separate exception

@@ -71,7 +71,7 @@ struct KernelTimer {
     double sum_ms[NCLS] = {};
     long long cnt[NCLS] = {};
     struct Rec {
-        int cls;
+        int cls, steps;  // steps the launch takes: totals and counts are per step
         hipEvent_t a, b;
     };
     std::vector<hipEvent_t> pool;
@@ -96,18 +96,18 @@ struct KernelTimer {
             float ms = 0.f;
             WV_HIP(hipEventElapsedTime(&ms, r.a, r.b));
             sum_ms[r.cls] += ms;
-            cnt[r.cls] += 1;
+            cnt[r.cls] += r.steps;
             pool.push_back(r.a);
             pool.push_back(r.b);
         }
         recs.clear();
     }
     // returns the record index to close with end(), or -1 when this launch is not sampled
-    int begin(int cls, hipStream_t st)
+    int begin(int cls, hipStream_t st, int steps = 1)
     {
         if (every <= 0 || (seen[cls]++ % every) != 0) return -1;
         if (recs.size() >= 4096) collect();
-        Rec r{cls, get(), get()};
+        Rec r{cls, steps, get(), get()};
         WV_HIP(hipEventRecord(r.a, st));
         recs.push_back(r);
         return (int)recs.size() - 1;
@@ -163,7 +163,7 @@ constexpr unsigned SYNC_EVENT_FLAGS = WV_SYNC_EVENT_FLAGS;
 
 // decoded-e slots: the decode of a state runs up to NEB - 1 steps ahead of its use
 #ifndef WV_NEB
-#define WV_NEB 3
+#define WV_NEB 4
 #endif
 constexpr int NEB = WV_NEB;
 // Work-groups per decode launch in the reverse sweep of a gradient (0: one launch). A
@@ -176,6 +176,10 @@ constexpr int NEB = WV_NEB;
 #define WV_REV_DEC_GRID 384
 #endif
 constexpr long long REV_DEC_GRID = WV_REV_DEC_GRID;
+#ifndef WV_PAIR_DEC_GRID
+#define WV_PAIR_DEC_GRID 0
+#endif
+constexpr long long PAIR_DEC_GRID = WV_PAIR_DEC_GRID;  // the same beside steps in pairs
 
 // Latent store of the states x_1 .. x_{T-1} of every source (AE modes): latents,
 // per-patch metadata, FP8 scales and the exact e values of the exception patches
@@ -226,6 +230,11 @@ struct wv_ctx {
     bool plane = false;
     int* pl_ptr = nullptr;
     int2* pl_ent = nullptr;
+    // 3D grids that take two steps per launch where a sweep allows: their receivers by row
+    PairPlan pair{};
+    int* pr_ptr = nullptr;
+    int* pr_lev = nullptr;
+    int2* pr_ent = nullptr;
 
     int* src_kji = nullptr;      // [S][3]
     float* src_w = nullptr;      // source stencil weights
@@ -501,6 +510,105 @@ void inc_step(wv_ctx* c, const float* in, float* out, int n, const float* en, lo
     c->tm.end(t, c->st);
 }
 
+int* upload_ints(const std::vector<int>& v)
+{
+    int* d = dev_alloc<int>(v.size());
+    if (!v.empty()) WV_HIP(hipMemcpy(d, v.data(), sizeof(int) * v.size(), hipMemcpyHostToDevice));
+    return d;
+}
+int2* upload_pairs(const std::vector<std::pair<int, int>>& v)
+{
+    std::vector<int2> h;
+    for (const auto& q : v) h.push_back(make_int2(q.first, q.second));
+    int2* d = dev_alloc<int2>(h.size());
+    if (!h.empty()) WV_HIP(hipMemcpy(d, h.data(), sizeof(int2) * h.size(), hipMemcpyHostToDevice));
+    return d;
+}
+
+// the two steps tidx and tidx2 = tidx +- 1 of a 3D grid
+PairArgs pair_args(const wv_ctx* c, const float* in, float* out, int tidx, int tidx2)
+{
+    PairArgs a{};
+    a.nz = c->g.nz;
+    a.ny = c->g.ny;
+    a.nx = c->g.nx;
+    a.N = c->N;
+    a.sstride = 4 * c->N;
+    a.dtdx = (float)(c->g.dt / c->g.dx);
+    a.dt = (float)c->g.dt;
+    a.wzc = c->wzc; a.wzf = c->wzf; a.wyc = c->wyc; a.wyf = c->wyf; a.wxc = c->wxc; a.wxf = c->wxf;
+    a.m = c->m;
+    a.in = in;
+    a.out = out;
+    a.tiles_x = c->pair.tiles_x;
+    a.tiles_y = c->pair.tiles_y;
+    a.chunks_z = c->pair.chunks;
+    a.kc = c->pair.kc;
+    a.flip = (tidx >> 1) & 1;
+    a.tidx = tidx;
+    a.tidx2 = tidx2;
+    a.nt = c->T;
+    a.src_kji = c->src_kji;
+    a.src_radius = c->src_radius;
+    a.src_w = c->src_w;
+    a.wavelet = c->wavelet;
+    a.rec_ptr = c->pr_ptr;
+    a.rec_lev = c->pr_lev;
+    a.rec_ent = c->pr_ent;
+    a.nrec = c->R;
+    return a;
+}
+
+// forward steps n and n + 1; traces (nullptr: not recorded); x1, x2: the new e also there
+void pair_fwd(wv_ctx* c, const float* in, float* out, int n, float* traces, float* x1 = nullptr, float* x2 = nullptr)
+{
+    PairArgs a = pair_args(c, in, out, n, n + 1);
+    a.traces = traces;
+    if (!traces) a.nrec = 0;
+    a.x1 = x1;
+    a.x2 = x2;
+    const int t = c->tm.begin(TM_FWD, c->st, 2);
+    launch_pair(MODE_FWD, c->pair, a, c->S, c->st);
+    c->tm.end(t, c->st);
+}
+
+// incremental steps n and n + 1 with the forward e of both levels; x1, x2: the new e also there
+void pair_inc(wv_ctx* c, const float* in, float* out, int n, const float* e1, const float* e2, long long estride,
+              float* dtraces, float* x1, float* x2)
+{
+    PairArgs a = pair_args(c, in, out, n, n + 1);
+    a.traces = dtraces;
+    a.dm = c->dm;
+    a.e1 = e1;
+    a.e2 = e2;
+    a.estride = estride;
+    a.x1 = x1;
+    a.x2 = x2;
+    const int t = c->tm.begin(TM_INC, c->st, 2);
+    launch_pair(MODE_INC, c->pair, a, c->S, c->st);
+    c->tm.end(t, c->st);
+}
+
+// adjoint steps k and k - 1 (positions j and j + 1 of their sweep), consuming e^k and e^{k-1}
+void pair_adj(wv_ctx* c, const float* in, float* out, int k, const float* resid, const float* e1, const float* e2,
+              long long estride, long long j)
+{
+    PairArgs a = pair_args(c, in, out, k, k - 1);
+    a.resid = resid;
+    a.e1 = e1;
+    a.e2 = e2;
+    a.estride = estride;
+    a.acc = c->acc;
+    a.blk = c->blk;
+    const int p1 = acc_phase(j, k), p2 = acc_phase(j + 1, k - 1);
+    a.first = p1 == ACC_FIRST;
+    a.closes = p2 == ACC_LAST;
+    const int t = c->tm.begin(TM_ADJ, c->st, 2);
+    launch_pair(MODE_ADJ, c->pair, a, c->S, c->st);
+    c->tm.end(t, c->st);
+}
+static_assert(WV_ACC_BLOCK % 2 == 0, "a pair of adjoint steps lies within one accumulation block");
+
 static_assert(PL_STEPS == WV_ACC_BLOCK, "a launch of adjoint steps is one accumulation block");
 
 // nsteps steps of a 2D grid from level n (forward, incremental) or down from level k (adjoint)
@@ -540,7 +648,7 @@ void plane_fwd(wv_ctx* c, const float* in, float* out, int n, int ns, float* tra
     a.e_extra = e_extra;
     a.xlevel = (long long)c->S * c->N;
     a.nextra = nextra;
-    const int t = c->tm.begin(TM_FWD, c->st);
+    const int t = c->tm.begin(TM_FWD, c->st, a.nsteps);
     launch_plane(MODE_FWD, a, c->S, c->st);
     c->tm.end(t, c->st);
 }
@@ -1136,7 +1244,37 @@ float* forward_sweep(wv_ctx* c, float* traces, const std::vector<int>* snap, flo
     float* prev = cur;
     const int ncap = (capture && every > 0) ? (c->T - 1) / every : 0;
     const long long mm_stride = (long long)c->S * c->P * c->H * 8;
+    // two steps per launch where x_{n+1} is not needed whole: no snapshot (x_{T-1} among them) or
+    // capture of it, no encode
+    auto needed = [&](int j) {
+        return (snap && ((*snap)[j] > 0 || j == c->T - 1)) || (ncap > 0 && j % every == 0 && j / every <= ncap) ||
+               (ecap_idx && (*ecap_idx)[j] >= 0);
+    };
     for (int n = 0; n < c->T; ++n) {
+        if (c->pair.use && !ae && !is_ae(c->mode) && n + 2 <= c->T && !needed(n + 1)) {
+            auto slot = [&](int j) -> float* {
+                return j > c->T - 1 ? nullptr : is_time(c->mode) ? time_slot(c, c->ts, j)
+                       : c->mode == WV_STORE_FULL ? c->ehist + (long long)(j - 1) * c->S * c->N : nullptr;
+            };
+            float* out = (snap && (*snap)[n + 2] > 0) ? c->slot_ptr((*snap)[n + 2]) : other_work(c, cur);
+            float* x1 = slot(n + 1);
+            pair_fwd(c, cur, out, n, traces, x1, slot(n + 2));
+            prev = cur;
+            cur = out;
+            for (int j = n + 1; j <= n + 2; ++j) store_state(c, c->fs, j, out);
+            ++n;
+            if (needed(n + 1)) {
+                const int j = n + 1;
+                if (ncap > 0 && j % every == 0 && j / every <= ncap)
+                    WV_HIP(hipMemcpyAsync(capture + (long long)(j / every - 1) * c->state_floats(), out,
+                                          sizeof(float) * c->state_floats(), hipMemcpyDeviceToDevice, c->st));
+                if (ecap_idx && (*ecap_idx)[j] >= 0)
+                    for (int s = 0; s < c->S; ++s)
+                        launch_copy(ecap + ((long long)(*ecap_idx)[j] * c->S + s) * c->N, out + s * 4 * c->N, c->N,
+                                    c->st);
+            }
+            continue;
+        }
         const int j = n + 1;  // this step writes x_j
         const bool store = j <= c->T - 1;
         float* out;
@@ -1192,6 +1330,26 @@ void reverse_sweep(wv_ctx* c, const float* resid, const std::vector<RevAction>* 
         adj_step(c, ain, aout, k, resid, ek, stride, acc_phase(done++, k));
         std::swap(ain, aout);
     };
+    if (!acts && is_ae(c->mode) && c->pair.use) {
+        // two steps per launch; e^{k-2} and e^{k-3} are decoded beside the steps k and k - 1
+        static_assert(NEB >= 4, "two pairs of decoded states");
+        pipe_start(c, PAIR_DEC_GRID);
+        for (int n = c->T - 1; n >= std::max(1, c->T - 2); --n) pipe_issue(c, n, n % NEB);
+        for (int k = c->T - 1; k >= 1; k -= 2) {
+            for (int n = k - 2; n >= std::max(1, k - 3); --n) pipe_issue(c, n, n % NEB);
+            if (k >= 2) {
+                const float* e1 = pipe_take(c, k % NEB);
+                pair_adj(c, ain, aout, k, resid, e1, pipe_take(c, (k - 1) % NEB), c->N, done);
+                std::swap(ain, aout);
+                done += 2;
+                pipe_release(c, (k - 1) % NEB);
+            } else {
+                adjoint_k(k, pipe_take(c, k % NEB), c->N);
+            }
+            pipe_release(c, k % NEB);
+        }
+        return;
+    }
     if (!acts && is_ae(c->mode)) {
         // e^{k-2} is decoded beside the adjoint steps k and k - 1, in launches of at most
         // REV_DEC_GRID work-groups
@@ -1213,7 +1371,7 @@ void reverse_sweep(wv_ctx* c, const float* resid, const std::vector<RevAction>* 
             a.elevel = -(long long)c->S * c->N;
             a.e = c->ehist + (long long)(k - 1) * c->S * c->N;
             a.acc = c->acc;
-            const int t = c->tm.begin(TM_ADJ, c->st);
+            const int t = c->tm.begin(TM_ADJ, c->st, a.nsteps);
             launch_plane(MODE_ADJ, a, c->S, c->st);
             c->tm.end(t, c->st);
             std::swap(ain, aout);
@@ -1221,38 +1379,72 @@ void reverse_sweep(wv_ctx* c, const float* resid, const std::vector<RevAction>* 
         return;
     }
     if (!acts) {
-        for (int k = c->T - 1; k >= 1; --k) {
+        // full storage and time compression; two levels per launch while both lie in one window
+        // (the next window's decode may overwrite the buffer of the one before)
+        for (int k = c->T - 1; k >= 1;) {
             long long stride;
             const float* e = load_e(c, k, &stride);
-            adjoint_k(k, e, stride);
+            if (c->pair.use && k >= 2 && done % 2 == 0 && !(is_time(c->mode) && (k - 1) % TWIN == 0)) {
+                pair_adj(c, ain, aout, k, resid, e, load_e(c, k - 1, &stride), stride, done);
+                std::swap(ain, aout);
+                done += 2;
+                k -= 2;
+            } else {
+                adjoint_k(k, e, stride);
+                --k;
+            }
         }
         return;
     }
+    // Checkpointing. Delivered states are taken two at a time where the grid steps in pairs: the
+    // first one (held) keeps its buffer until the second is there, so the recomputation between
+    // them uses a third work buffer.
     float* cur = xtm1;
     long long extra = 0;
+    const float* held = nullptr;
+    int held_k = 0;
+    if (c->pair.use && !c->work[2]) c->work[2] = dev_alloc<float>(c->state_floats());
+    auto next_work = [&](const float* from) {
+        for (float* w : {c->work[0], c->work[1], c->work[2]})
+            if (w != from && w != held) return w;
+        return c->work[2];  // not reached with three buffers; with two, nothing is held
+    };
     for (size_t q = first; q < acts->size(); ++q) {
         const RevAction& A = (*acts)[q];
         if (A.kind == 3) {
-            if (A.a >= 1) adjoint_k(A.a, cur, 4 * c->N);
+            if (A.a < 1) continue;
+            if (held) {
+                pair_adj(c, ain, aout, held_k, resid, held, cur, 4 * c->N, done);
+                std::swap(ain, aout);
+                done += 2;
+                held = nullptr;
+            } else if (c->pair.use && A.a >= 2 && done % 2 == 0) {
+                held = cur;
+                held_k = A.a;
+            } else {
+                adjoint_k(A.a, cur, 4 * c->N);
+            }
         } else if (A.kind == 2) {
             if (A.b == 0) {
-                launch_fill(c->work[0], c->state_floats(), 0.f, c->st);
-                cur = c->work[0];
+                cur = next_work(nullptr);
+                launch_fill(cur, c->state_floats(), 0.f, c->st);
             } else {
                 cur = c->slot_ptr(A.b);
             }
         } else if (A.kind == 0) {
             const bool to_slot = q + 1 < acts->size() && (*acts)[q + 1].kind == 1;
-            for (int t = 0; c->plane && t < A.b; t += PL_STEPS) {
-                const int ns = std::min(PL_STEPS, A.b - t);
-                float* out = (to_slot && t + ns == A.b) ? c->slot_ptr((*acts)[q + 1].b) : other_work(c, cur);
-                plane_fwd(c, cur, out, A.a + t, ns, nullptr);
+            for (int t = 0; t < A.b;) {
+                const int ns = c->plane ? std::min(PL_STEPS, A.b - t) : c->pair.use && t + 2 <= A.b ? 2 : 1;
+                float* out = (to_slot && t + ns == A.b) ? c->slot_ptr((*acts)[q + 1].b) : next_work(cur);
+                if (out == held) {  // the held state's slot is taken for another one: its step goes alone
+                    adjoint_k(held_k, held, 4 * c->N);
+                    held = nullptr;
+                }
+                if (c->plane) plane_fwd(c, cur, out, A.a + t, ns, nullptr);
+                else if (ns == 2) pair_fwd(c, cur, out, A.a + t, nullptr);
+                else fwd_step(c, cur, out, A.a + t, nullptr);
                 cur = out;
-            }
-            for (int t = 0; !c->plane && t < A.b; ++t) {
-                float* out = (to_slot && t == A.b - 1) ? c->slot_ptr((*acts)[q + 1].b) : other_work(c, cur);
-                fwd_step(c, cur, out, A.a + t, nullptr);
-                cur = out;
+                t += ns;
             }
             extra += A.b;
         }
@@ -1368,12 +1560,17 @@ int wv_create(const wv_grid* grid, const int32_t* h_src, const int32_t* h_rec, v
             std::vector<int> ptr;
             std::vector<std::pair<int, int>> ent;
             region_receivers(g.nz, g.nx, PL_CZ, PL_CX, PL_STEPS, rec, ptr, ent);
-            c->pl_ptr = dev_alloc<int>(ptr.size());
-            WV_HIP(hipMemcpy(c->pl_ptr, ptr.data(), sizeof(int) * ptr.size(), hipMemcpyHostToDevice));
-            std::vector<int2> e2;
-            for (const auto& q : ent) e2.push_back(make_int2(q.first, q.second));
-            c->pl_ent = dev_alloc<int2>(e2.size());
-            if (!e2.empty()) WV_HIP(hipMemcpy(c->pl_ent, e2.data(), sizeof(int2) * e2.size(), hipMemcpyHostToDevice));
+            c->pl_ptr = upload_ints(ptr);
+            c->pl_ent = upload_pairs(ent);
+        }
+        c->pair = pair_plan(g.nz, g.ny, g.nx, g.nsrc);
+        if (c->pair.use) {
+            std::vector<int> ptr, lev;
+            std::vector<std::pair<int, int>> ent;
+            row_receivers(g.nz, g.ny, g.nx, rec, ptr, lev, ent);
+            c->pr_ptr = upload_ints(ptr);
+            c->pr_lev = upload_ints(lev);
+            c->pr_ent = upload_pairs(ent);
         }
         c->src_kji = dev_alloc<int>(src.size());
         WV_HIP(hipMemcpy(c->src_kji, src.data(), sizeof(int) * src.size(), hipMemcpyHostToDevice));
@@ -1444,6 +1641,9 @@ int wv_destroy(wv_ctx* c)
     dev_free(c->src_kji);
     dev_free(c->pl_ptr);
     dev_free(c->pl_ent);
+    dev_free(c->pr_ptr);
+    dev_free(c->pr_lev);
+    dev_free(c->pr_ent);
     dev_free(c->src_w);
     for (float** p : {&c->m, &c->c_last, &c->wavelet, &c->work[0], &c->work[1], &c->adj[0], &c->adj[1],
                       &c->incb[0], &c->incb[1], &c->incb[2], &c->acc, &c->blk, &c->ebuf, &c->dm, &c->traces,
@@ -1871,16 +2071,52 @@ float* inc_forward_sweep(wv_ctx* c, const float* cdev, const float* dc, const st
                 a.xlevel = (long long)c->S * c->N;
                 a.nextra = std::min(n + a.nsteps, c->T - 1) - n;
             }
-            const int t = c->tm.begin(TM_INC, c->st);
+            const int t = c->tm.begin(TM_INC, c->st, a.nsteps);
             launch_plane(MODE_INC, a, c->S, c->st);
             c->tm.end(t, c->st);
             std::swap(din, dout);
         }
         return nullptr;
     }
+    // two steps per launch where the incremental states themselves are not stored whole
+    const bool pairs = c->pair.use && !ckpt && !keep_delta;
+    int decoded = 0;  // levels up to here are decoded or queued (autoencoder stores, in pairs)
     for (int n = 0; n < c->T; ++n) {
         const float* en;
         long long stride;
+        // (the time store's buffers hold one window for the steps and one ahead)
+        if (pairs && n + 2 <= c->T && !(is_time(c->mode) && n > 0 && n % TWIN == 0)) {
+            auto slot = [&](int j) -> float* {
+                return j > c->T - 1 ? nullptr : keep_time ? time_slot(c, c->tds, j)
+                       : keep_full ? c->dehist + (long long)(j - 1) * c->S * c->N : nullptr;
+            };
+            const float* e2;
+            stride = c->N;
+            if (pipe) {
+                // e^{n+2} and e^{n+3} are decoded beside the steps n and n + 1
+                for (; decoded < std::min(n + 3, c->T - 1); ++decoded) pipe_issue(c, decoded + 1, (decoded + 1) % NEB);
+                en = n == 0 ? ebuf_slot(c, 0) : pipe_take(c, n % NEB);
+                e2 = pipe_take(c, (n + 1) % NEB);
+            } else {
+                en = n == 0 ? ebuf_slot(c, 0) : load_e(c, n, &stride, +1);
+                e2 = load_e(c, n + 1, &stride, +1);
+            }
+            float* x1 = slot(n + 1);
+            pair_inc(c, din, dout, n, en, e2, stride, c->dtr, x1, slot(n + 2));
+            if (pipe)
+                for (int q = n; q <= n + 1; ++q) pipe_release(c, q % NEB);
+            std::swap(din, dout);
+            if (keep_time)
+                for (int j = n + 1; j <= n + 2; ++j) time_store_level(c, c->tds, j);
+            ++n;
+            continue;
+        }
+        if (pairs && pipe) {  // the last step of an odd number
+            for (; decoded < std::min(n, c->T - 1); ++decoded) pipe_issue(c, decoded + 1, (decoded + 1) % NEB);
+            inc_step(c, din, dout, n, n == 0 ? ebuf_slot(c, 0) : pipe_take(c, n % NEB), c->N, c->dtr);
+            std::swap(din, dout);
+            continue;
+        }
         if (ckpt) {
             en = cur;
             stride = 4 * c->N;

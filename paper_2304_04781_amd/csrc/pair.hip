@@ -1,0 +1,461 @@
+// Two leapfrog steps of a 3D grid per launch.
+//
+// A step of a large grid is bound by its bytes (forward 36 per cell, adjoint 49), each field
+// read and written once. Two steps in one pass read and write the fields once for both. A
+// work-group of 16 waves holds PR_ROWS rows of the (y, x) plane at one level, four cells per
+// lane, and marches in z with the second step one level behind the first: when the first
+// step has reached level K, the second is done at K - 1. Column data stay in registers; rows
+// exchange P and v_y through LDS (both steps' rows in one go, two buffers, one barrier per
+// level), columns through the lanes of a row. Two rows at either side of the tile and two levels
+// at either end of a chunk are stepped again by their neighbours (x: a lane at either side,
+// where a row is wider than a work-group). The same arithmetic, operation for operation, as
+// stencil.hip's kernel for one step, whose equations apply.
+
+#include <algorithm>
+
+#include "wv_internal.h"
+
+namespace wv {
+
+namespace {
+
+constexpr int VX = 4;
+constexpr int NT = 768, NW = NT / 64;
+
+template <class T>
+__device__ __forceinline__ T ldu(const T* p, long long idx)
+{
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Wold-style-cast"
+    return ((const __attribute__((address_space(4))) T*)p)[idx];
+#pragma clang diagnostic pop
+}
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+// the 16-byte buffer load by its intrinsic's name: this compiler lowers
+// __builtin_amdgcn_raw_buffer_load_b128 to a single dword, copied into all four
+__device__ f32x4 raw_buffer_load_x4(__amdgpu_buffer_rsrc_t rsrc, int voffset, int soffset,
+                                    int aux) __asm("llvm.amdgcn.raw.ptr.buffer.load.v4f32");
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const float* base, unsigned bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), (short)0, (int)bytes, 0x00020000);
+}
+// four cells at a level base plus a byte offset within the plane; every dword at or past
+// `bytes` reads 0 and stores nothing
+__device__ __forceinline__ f32x4 ld4(const float* base, unsigned bytes, unsigned off)
+{
+    return raw_buffer_load_x4(plane_rsrc(base, bytes), (int)off, 0, 0);
+}
+template <int AUX>
+__device__ __forceinline__ void st1(float v, float* base, unsigned bytes, unsigned off)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), plane_rsrc(base, bytes), (int)off, 0, AUX);
+}
+constexpr int AUX_NT = 2;  // non-temporal (not read again by this launch)
+// TAIL: rows end within a lane: its cells past the row (noff of them) are not stored
+template <bool TAIL, int AUX>
+__device__ __forceinline__ void st4(f32x4 v, float* base, unsigned bytes, unsigned off, int nvalid)
+{
+    if (!TAIL || nvalid == VX) {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), plane_rsrc(base, bytes), (int)off, 0, AUX);
+    } else {
+#pragma unroll
+        for (int u = 0; u < VX - 1; ++u)
+            if (u < nvalid) st1<AUX>(v[u], base, bytes, off + 4 * u);
+    }
+}
+// the value of the lane before / after this one (whole wave; the first / last lane gets 0)
+__device__ __forceinline__ float lane_from_left(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x138, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float lane_from_right(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x130, 0xF, 0xF, true));
+}
+
+// LXW lanes per row (64 / LXW rows per wave)
+template <int LXW, int MODE, bool TAIL, bool EX>
+__global__ void __launch_bounds__(NT) pair_step_kernel(const PairArgs a)
+{
+    // every product that is fused with an addition is written as an fma
+#pragma clang fp contract(off)
+    constexpr bool ADJ = MODE == MODE_ADJ;
+    constexpr int ROWS = NW * 64 / LXW;
+    constexpr int CORE = ROWS - 4;
+    __shared__ f32x4 sX[2][4][ROWS][LXW];  // P and v_y of the first step's level, then of the second's
+
+    const int nblk = a.tiles_x * a.tiles_y * a.chunks_z;
+    int b = blockIdx.x;
+    {   // each XCD takes a contiguous range, visited backwards on every other launch
+        const int x = b & 7, q = nblk >> 3, r = nblk & 7, n = q + (x < r);
+        b >>= 3;
+        if (a.flip) b = n - 1 - b;
+        b += x * q + min(x, r);
+    }
+    const int txx = b % a.tiles_x, tyy = (b / a.tiles_x) % a.tiles_y, cz = b / (a.tiles_x * a.tiles_y);
+    const int s = blockIdx.y;
+    const int tid = threadIdx.x, lane = tid % LXW, row = tid / LXW;
+    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    const int j = tyy * CORE - 2 + row;
+    const int i = (a.tiles_x == 1 ? 0 : txx * (LXW - 2) * VX - VX) + lane * VX;
+    const bool inside = j >= 0 && j < ny && i >= 0 && i < nx;
+    const bool core = inside && row >= 2 && row < ROWS - 2 && (a.tiles_x == 1 || (lane >= 1 && lane < LXW - 1));
+    const int nvalid = TAIL ? min(VX, nx - i) : VX;  // of an inside lane
+    const int k0 = cz * a.kc, k1 = min(nz, k0 + a.kc);
+    const long long plane = (long long)ny * nx, N = a.N;
+
+    const float* __restrict__ inA = a.in + s * a.sstride;
+    float* __restrict__ outA = a.out + s * a.sstride;
+    const float* __restrict__ e1 = a.e1 + s * a.estride;
+    const float* __restrict__ e2 = a.e2 + s * a.estride;
+    float* __restrict__ acc = ADJ ? a.acc + s * 2 * N : nullptr;
+    float* __restrict__ blk = ADJ ? a.blk + s * N : nullptr;
+
+    const int jc = inside ? j : 0, ic = inside ? i : 0;
+    const bool has_y1 = j + 1 < ny;
+    float wyc = a.wyc[jc], wyf = a.wyf[jc], wyf1 = a.wyf[has_y1 && inside ? j + 1 : 0];
+    f32x4 wxc, wxf;
+#pragma unroll
+    for (int u = 0; u < VX; ++u) {
+        wxc[u] = a.wxc[min(ic + u, nx - 1)];
+        wxf[u] = a.wxf[min(ic + u, nx - 1)];
+    }
+    // P and W outside the grid are 0: whole lanes by `inside`, cells past the row's end by TAIL
+    auto in_row = [&](int u) { return TAIL ? inside && u < nvalid : inside; };
+
+    const unsigned pb4 = (unsigned)plane * 4u;
+    const unsigned o_c = inside ? (unsigned)(j * nx + i) * 4u : pb4;
+    const unsigned o_k = core ? o_c : pb4;
+
+    auto face_new = [&](float S, float V, float dP) -> float {
+        return ADJ ? __builtin_fmaf(S, V, -(a.dtdx * dP)) : S * __builtin_fmaf(a.dtdx, dP, V);
+    };
+    auto face_new_add = [&](float S, float V, float dP, float add) -> float {
+        return ADJ ? __builtin_fmaf(S, V, -(a.dtdx * dP)) + add : S * (__builtin_fmaf(a.dtdx, dP, V) + add);
+    };
+    auto face_w = [&](float S, float Vn) -> float { return ADJ ? S * Vn : Vn; };
+    // the potential of an inside cell, 0 elsewhere
+    auto pot = [&](float wz, int u, float A, float m, float dm, float e) -> float {
+        float p;
+        if (MODE == MODE_FWD) p = m * A;
+        else if (MODE == MODE_INC) p = __builtin_fmaf(m, A, dm * e);
+        else p = (wz * (wyc * wxc[u])) * A;
+        return in_row(u) ? p : 0.f;
+    };
+    // the first receiver entry of row (kk, j) at column i or later
+    auto first_rec = [&](int kk) {
+        int lo = a.rec_ptr[(long long)kk * ny + j], hi = a.rec_ptr[(long long)kk * ny + j + 1];
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (a.rec_ent[mid].x < i) lo = mid + 1;
+            else hi = mid;
+        }
+        return lo;
+    };
+    // extra term of the v_z faces of level kk in the step with time index t (source, residuals)
+    int sk = 0, sj = 0, si = 0, R = 0;
+    if (MODE == MODE_FWD) {
+        sk = a.src_kji[3 * s];
+        sj = a.src_kji[3 * s + 1];
+        si = a.src_kji[3 * s + 2];
+        R = a.src_radius;
+    }
+    const bool src_row = MODE == MODE_FWD && inside && abs(j - sj) <= R && i + VX - 1 >= si - R && i <= si + R;
+    auto extra = [&](int kk, int t) -> f32x4 {
+        f32x4 add{0.f, 0.f, 0.f, 0.f};
+        if (kk >= nz) return add;
+        if (MODE == MODE_FWD) {
+            if (abs(kk - sk) <= R && src_row) {
+                const float bsrc = a.dt * a.wavelet[(long long)s * a.nt + t];
+#pragma unroll
+                for (int u = 0; u < VX; ++u)
+                    if (abs(i + u - si) <= R)
+                        add[u] = bsrc * a.src_w[((kk - sk + R) * (2 * R + 1) + j - sj + R) * (2 * R + 1) + i + u - si + R];
+            }
+        } else if (ADJ && a.nrec > 0 && ldu(a.rec_lev, kk) != 0 && inside) {
+            const float* rs = a.resid + ((long long)s * a.nt + t) * a.nrec;
+            const int q1 = a.rec_ptr[(long long)kk * ny + j + 1];
+            for (int q = first_rec(kk); q < q1; ++q) {  // the entries of a cell are in receiver order
+                const int2 e = a.rec_ent[q];
+                if (e.x >= i + VX) break;
+                const float r = rs[e.y];
+#pragma unroll
+                for (int u = 0; u < VX; ++u) add[u] = e.x == i + u ? add[u] + r : add[u];
+            }
+        }
+        return add;
+    };
+    // traces of level k in the step with time index t from the v_z faces of the core
+    auto record = [&](int k, int t, const f32x4& v) {
+        if (ADJ || a.nrec == 0 || ldu(a.rec_lev, k) == 0 || !core) return;
+        float* tr = a.traces + ((long long)s * a.nt + t) * a.nrec;
+        const int q1 = a.rec_ptr[(long long)k * ny + j + 1];
+        for (int q = first_rec(k); q < q1; ++q) {
+            const int2 e = a.rec_ent[q];
+            const int d = e.x - i;
+            if (d >= VX) break;
+            tr[e.y] = d == 0 ? v[0] : d == 1 ? v[1] : d == 2 ? v[2] : v[3];
+        }
+    };
+
+    struct Col {
+        f32x4 A, m, Vz, dm, e;
+    };
+    auto load_col = [&](int kk, Col& c) {
+        const long long lo = (long long)min(max(kk, 0), nz - 1) * plane;
+        c.A = ld4(inA + lo, pb4, o_c);
+        c.m = ld4(a.m + lo, pb4, o_c);
+        c.Vz = ld4(inA + N + lo, pb4, o_c);
+        if (MODE == MODE_INC) {
+            c.dm = ld4(a.dm + lo, pb4, o_c);
+            c.e = ld4(e1 + lo, pb4, o_c);
+        }
+    };
+    struct Pln {
+        f32x4 Vy, Vx;
+    };
+    auto load_pln = [&](int kk, Pln& p) {
+        const long long lo = (long long)min(max(kk, 0), nz - 1) * plane;
+        p.Vy = ld4(inA + 2 * N + lo, pb4, o_c);
+        p.Vx = ld4(inA + 3 * N + lo, pb4, o_c);
+    };
+    // one level of one step: in-plane faces from P and its neighbours, then the divergence d
+    auto level = [&](float wzc, const f32x4& P, const f32x4& Pm, const f32x4& Pp, f32x4& Vy, const f32x4& Vyp, f32x4& Vx,
+                     const f32x4& Wz0, const f32x4& Wz1) -> f32x4 {
+#pragma clang fp contract(off)
+        f32x4 d;
+#pragma unroll
+        for (int u = 0; u < VX; ++u) {
+            const float S = wzc * (wyf * wxc[u]), S1 = wzc * (wyf1 * wxc[u]);
+            const float W1 = face_w(S1, face_new(S1, Vyp[u], Pp[u] - P[u]));
+            Vy[u] = face_new(S, Vy[u], P[u] - Pm[u]);
+            d[u] = Wz1[u] - Wz0[u];
+            d[u] += (has_y1 ? W1 : 0.f) - face_w(S, Vy[u]);
+        }
+        const float left0 = lane_from_left(P[VX - 1]);
+        const float left = lane == 0 ? 0.f : left0;
+        float W[VX + 1];
+#pragma unroll
+        for (int u = 0; u < VX; ++u) {
+            const float S = wzc * (wyc * wxf[u]);
+            Vx[u] = face_new(S, Vx[u], P[u] - (u ? P[u - 1] : left));
+            W[u] = face_w(S, Vx[u]);
+            if (TAIL) W[u] = in_row(u) ? W[u] : 0.f;
+        }
+        const float right = lane_from_right(W[0]);
+        W[VX] = i + VX < nx ? right : 0.f;
+#pragma unroll
+        for (int u = 0; u < VX; ++u) d[u] += W[u + 1] - W[u];
+        return d;
+    };
+
+    const int Kb = max(k0 - 1, 0);
+    f32x4 P, A, m, dm, v1;             // first step at level K: v1 its new v_z face
+    f32x4 P2, A2, m2, dm2, Vy2, Vx2;   // second step's operands at level K - 1
+    f32x4 v2, t2;                      // its new v_z face at K - 1; the gradient partial after the first step
+    const f32x4 zero{0.f, 0.f, 0.f, 0.f};
+    P2 = A2 = m2 = dm2 = Vy2 = Vx2 = v2 = t2 = zero;
+    Col cb[2];
+    Pln pb[2];
+    {
+        Col c0, cl;
+        load_col(Kb, c0);
+        load_col(Kb - 1, cl);
+        load_col(Kb + 1, cb[1]);
+        load_pln(Kb, pb[0]);
+        const f32x4 add = extra(Kb, a.tidx);
+        const float wz0 = ldu(a.wzc, Kb), wzl = ldu(a.wzc, max(Kb - 1, 0)), wzf = ldu(a.wzf, Kb);
+        A = c0.A;
+        m = c0.m;
+        if (MODE == MODE_INC) dm = c0.dm;
+#pragma unroll
+        for (int u = 0; u < VX; ++u) {
+            P[u] = pot(wz0, u, c0.A[u], c0.m[u], c0.dm[u], c0.e[u]);
+            const float Pl = Kb > 0 ? pot(wzl, u, cl.A[u], cl.m[u], cl.dm[u], cl.e[u]) : 0.f;
+            v1[u] = face_new_add(wzf * (wyc * wxc[u]), c0.Vz[u], P[u] - Pl, add[u]);
+        }
+    }
+    const int rm = max(row - 1, 0), rp = min(row + 1, ROWS - 1);  // clamped rows only reach halo cells
+    // iteration K: cn = column K + 1, pc = plane K (its v_y, v_x)
+    auto iterate = [&](const int K, const Col& cn, Col& cnn, const Pln& pc, Pln& pn) {
+#pragma clang fp contract(off)
+        // the (y, x) factor products are formed anew at each level (the empty asm keeps them from
+        // being hoisted): held across levels they would cost 16 registers
+        asm volatile("" : "+v"(wyc), "+v"(wyf), "+v"(wyf1));
+        const bool first_on = K < nz;                       // the first step exists at K
+        const bool core1 = K >= k0 && K < k1;               // ... in the chunk
+        const int k = K - 1;
+        const bool second_on = k >= k0 && k < k1;
+        const long long lK = (long long)min(K, nz - 1) * plane, lk = (long long)max(k, 0) * plane;
+        f32x4 ek1 = zero, ek2 = zero, b1 = zero, ac = zero, cp = zero;
+        if (ADJ) {
+            if (core1) {
+                ek1 = ld4(e1 + lK, pb4, o_k);
+                if (!a.first) b1 = ld4(blk + lK, pb4, o_k);
+            }
+        }
+        f32x4 en2 = zero;
+        if (MODE == MODE_INC && first_on) en2 = ld4(e2 + lK, pb4, o_c);
+        load_col(min(K + 2, k1 + 1), cnn);
+        load_pln(min(K + 1, k1), pn);
+
+        f32x4(&x)[4][ROWS][LXW] = sX[K & 1];
+        x[0][row][lane] = P;
+        x[1][row][lane] = pc.Vy;
+        x[2][row][lane] = P2;
+        x[3][row][lane] = Vy2;
+        __syncthreads();
+        const float wzcK = ldu(a.wzc, min(K, nz - 1)), wzck = ldu(a.wzc, max(k, 0));
+        const float wzfK = ldu(a.wzf, min(K, nz - 1)), wzfn = ldu(a.wzf, min(K + 1, nz - 1)), wzfk = ldu(a.wzf, max(k, 0));
+        const float wzcn = ldu(a.wzc, min(K + 1, nz - 1));
+
+        // ---- first step at K
+        f32x4 nP = zero, nv1 = zero, nA = zero, nVy = pc.Vy, nVx = pc.Vx, nP2 = zero;
+        f32x4 t1 = zero;
+        if (first_on) {
+            const f32x4 add = extra(K + 1, a.tidx);
+            f32x4 W0, W1;
+            const bool up = K + 1 < nz;
+#pragma unroll
+            for (int u = 0; u < VX; ++u) {
+                nP[u] = up ? pot(wzcn, u, cn.A[u], cn.m[u], cn.dm[u], cn.e[u]) : 0.f;
+                const float S = wzfn * (wyc * wxc[u]);
+                const float v = face_new_add(S, cn.Vz[u], nP[u] - P[u], add[u]);
+                nv1[u] = up ? v : 0.f;
+                W1[u] = up ? face_w(S, v) : 0.f;
+                W0[u] = face_w(wzfK * (wyc * wxc[u]), v1[u]);
+            }
+            const f32x4 d = level(wzcK, P, x[0][rm][lane], x[0][rp][lane], nVy, x[1][rp][lane], nVx, W0, W1);
+#pragma unroll
+            for (int u = 0; u < VX; ++u) {
+                const float Se = wzcK * (wyc * wxc[u]);
+                nA[u] = ADJ ? __builtin_fmaf(Se, A[u], -((a.dtdx * m[u]) * d[u])) : Se * __builtin_fmaf(a.dtdx, d[u], A[u]);
+                if (ADJ) t1[u] = __builtin_fmaf(ek1[u], d[u], b1[u]);
+                nP2[u] = pot(wzcK, u, nA[u], m[u], dm[u], en2[u]);
+            }
+            if (core1) {
+                record(K, a.tidx, v1);
+                if (EX && a.x1) st4<TAIL, AUX_NT>(nA, a.x1 + s * N + lK, pb4, o_k, nvalid);
+            }
+        }
+        // ---- second step: its v_z face at K, then the cells of k = K - 1
+        __builtin_amdgcn_sched_barrier(0);  // the sums' operands are loaded here, not held across the first step
+        if (ADJ && second_on) {
+            m2 = ld4(a.m + lk, pb4, o_k);
+            ek2 = ld4(e2 + lk, pb4, o_k);
+            if (a.closes) {
+                ac = ld4(acc + lk, pb4, o_k);
+                cp = ld4(acc + N + lk, pb4, o_k);
+            }
+        }
+        f32x4 nv2 = zero;
+        if (first_on && K >= k0) {
+            const f32x4 add = extra(K, a.tidx2);
+#pragma unroll
+            for (int u = 0; u < VX; ++u)
+                nv2[u] = face_new_add(wzfK * (wyc * wxc[u]), v1[u], nP2[u] - (K > 0 ? P2[u] : 0.f), add[u]);
+        }
+        if (second_on) {
+            f32x4 W0, W1;
+#pragma unroll
+            for (int u = 0; u < VX; ++u) {
+                W0[u] = face_w(wzfk * (wyc * wxc[u]), v2[u]);
+                W1[u] = first_on ? face_w(wzfK * (wyc * wxc[u]), nv2[u]) : 0.f;
+            }
+            f32x4 Vy = Vy2, Vx = Vx2, Ao, sum, com;
+            const f32x4 d = level(wzck, P2, x[2][rm][lane], x[2][rp][lane], Vy, x[3][rp][lane], Vx, W0, W1);
+#pragma unroll
+            for (int u = 0; u < VX; ++u) {
+                const float Se = wzck * (wyc * wxc[u]);
+                if (ADJ) {
+                    Ao[u] = __builtin_fmaf(Se, A2[u], -((a.dtdx * m2[u]) * d[u]));
+                    const float term = __builtin_fmaf(ek2[u], d[u], t2[u]);
+                    const float y = term - cp[u];
+                    const float t = ac[u] + y;
+                    com[u] = (t - ac[u]) - y;
+                    sum[u] = a.closes ? t : term;
+                } else {
+                    Ao[u] = Se * __builtin_fmaf(a.dtdx, d[u], A2[u]);
+                }
+            }
+            st4<TAIL, AUX_NT>(Ao, outA + lk, pb4, o_k, nvalid);
+            st4<TAIL, AUX_NT>(v2, outA + N + lk, pb4, o_k, nvalid);
+            st4<TAIL, AUX_NT>(Vy, outA + 2 * N + lk, pb4, o_k, nvalid);
+            st4<TAIL, AUX_NT>(Vx, outA + 3 * N + lk, pb4, o_k, nvalid);
+            if (EX && a.x2) st4<TAIL, AUX_NT>(Ao, a.x2 + s * N + lk, pb4, o_k, nvalid);
+            if (ADJ) {
+                if (a.closes) {
+                    st4<TAIL, 0>(sum, acc + lk, pb4, o_k, nvalid);
+                    st4<TAIL, 0>(com, acc + N + lk, pb4, o_k, nvalid);
+                } else {
+                    st4<TAIL, 0>(sum, blk + lk, pb4, o_k, nvalid);
+                }
+            }
+            record(k, a.tidx2, v2);
+        }
+        v2 = nv2;
+        P2 = nP2;
+        A2 = nA;
+        if (!ADJ) m2 = m;
+        Vy2 = nVy;
+        Vx2 = nVx;
+        t2 = t1;
+        P = nP;
+        v1 = nv1;
+        A = cn.A;
+        m = cn.m;
+        if (MODE == MODE_INC) dm = cn.dm;
+    };
+    int K = Kb;
+    for (; K + 1 <= k1; K += 2) {
+        iterate(K, cb[1], cb[0], pb[0], pb[1]);
+        iterate(K + 1, cb[0], cb[1], pb[1], pb[0]);
+    }
+    if (K <= k1) iterate(K, cb[1], cb[0], pb[0], pb[1]);
+}
+
+}  // namespace
+
+PairPlan pair_plan(int nz, int ny, int nx, int nsrc)
+{
+    PairPlan p{};
+    if (ny < 2) return p;
+    p.lxw = nx <= 128 ? 32 : 64;
+    const int rows = NW * 64 / p.lxw;
+    p.core_y = rows - 4;
+    p.tiles_x = nx <= p.lxw * VX ? 1 : (nx + (p.lxw - 2) * VX - 1) / ((p.lxw - 2) * VX);
+    p.tiles_y = (ny + p.core_y - 1) / p.core_y;
+    if (p.tiles_x > 1 && nx % VX != 0) return p;  // overlapping x tiles hold whole lanes
+    // one work-group fills a CU: chunks until one round of them over 256 CUs, of at least
+    // PR_MIN_KC levels (four more are read and two more stepped per chunk)
+    const long long tiles = (long long)p.tiles_x * p.tiles_y * nsrc;
+    const int rounds = (int)((tiles * ((nz + PR_MAX_KC - 1) / PR_MAX_KC) + 255) / 256);
+    int chunks = (int)std::max<long long>(1, rounds * 256LL / tiles);
+    chunks = std::min(chunks, std::max(1, nz / PR_MIN_KC));
+    p.kc = (nz + chunks - 1) / chunks;
+    p.chunks = (nz + p.kc - 1) / p.kc;
+    p.use = (long long)nz * ny * nx * nsrc >= PR_MIN_CELLS;
+    return p;
+}
+
+template <int LXW, int MODE, bool EX>
+static void launch_one(const PairArgs& a, const dim3& grid, hipStream_t st)
+{
+    if (a.nx % VX != 0)
+        hipLaunchKernelGGL((pair_step_kernel<LXW, MODE, true, EX>), grid, dim3(NT), 0, st, a);
+    else
+        hipLaunchKernelGGL((pair_step_kernel<LXW, MODE, false, EX>), grid, dim3(NT), 0, st, a);
+}
+
+void launch_pair(int mode, const PairPlan& p, const PairArgs& a, int nsrc, hipStream_t st)
+{
+    const dim3 grid(p.tiles_x * p.tiles_y * p.chunks, nsrc);
+    const bool wide = p.lxw == 64;
+    if (mode == MODE_ADJ) wide ? launch_one<64, MODE_ADJ, false>(a, grid, st) : launch_one<32, MODE_ADJ, false>(a, grid, st);
+    else if (mode == MODE_INC) wide ? launch_one<64, MODE_INC, true>(a, grid, st) : launch_one<32, MODE_INC, true>(a, grid, st);
+    else wide ? launch_one<64, MODE_FWD, true>(a, grid, st) : launch_one<32, MODE_FWD, true>(a, grid, st);
+    WV_HIP(hipGetLastError());
+}
+
+}  // namespace wv

@@ -83,4 +83,28 @@ void region_receivers(int nz, int nx, int cz, int cx, int h, const std::vector<i
     }
 }
 
+void row_receivers(int nz, int ny, int nx, const std::vector<int>& rec_kji, std::vector<int>& ptr,
+                   std::vector<int>& lev, std::vector<std::pair<int, int>>& ent)
+{
+    WV_REQUIRE(nz >= 1 && ny >= 1 && nx >= 1 && rec_kji.size() % 3 == 0, WV_EINVAL, "row_receivers: bad sizes");
+    const int n = (int)(rec_kji.size() / 3);
+    std::vector<std::pair<long long, std::pair<int, int>>> all;
+    lev.assign(nz, 0);
+    for (int q = 0; q < n; ++q) {
+        const int k = rec_kji[3 * q], j = rec_kji[3 * q + 1], i = rec_kji[3 * q + 2];
+        WV_REQUIRE(k >= 0 && k < nz && j >= 0 && j < ny && i >= 0 && i < nx, WV_EINVAL,
+                   "row_receivers: receiver outside the grid");
+        all.push_back({(long long)k * ny + j, {i, q}});
+        ++lev[k];
+    }
+    std::sort(all.begin(), all.end());
+    ptr.assign((size_t)nz * ny + 1, 0);
+    ent.clear();
+    for (const auto& v : all) {
+        ++ptr[v.first + 1];
+        ent.push_back(v.second);
+    }
+    for (size_t r = 1; r < ptr.size(); ++r) ptr[r] += ptr[r - 1];
+}
+
 }  // namespace wv

@@ -75,4 +75,9 @@ void bucket_receivers(int nz, int bx, int by, int tiles_x, int tiles_y, const st
 void region_receivers(int nz, int nx, int cz, int cx, int h, const std::vector<int>& rec_kji, std::vector<int>& ptr,
                       std::vector<std::pair<int, int>>& ent);
 
+// Receivers (k, j, i triples) by grid row: row k ny + j holds ent[ptr[row] .. ptr[row + 1]) as
+// (i, receiver), in that order; lev[k] = receivers of level k.
+void row_receivers(int nz, int ny, int nx, const std::vector<int>& rec_kji, std::vector<int>& ptr,
+                   std::vector<int>& lev, std::vector<std::pair<int, int>>& ent);
+
 }  // namespace wv

@@ -138,6 +138,49 @@ bool plane_supported(int nz, int ny, int nx, int nsrc);
 // one launch of a.nsteps steps: MODE_FWD, MODE_INC or MODE_ADJ
 void launch_plane(int mode, const PlaneArgs& a, int nsrc, hipStream_t st);
 
+// ---- two steps of a 3D grid per launch (pair.hip) ---------------------------------------
+
+#ifndef WV_PR_MIN_CELLS
+#define WV_PR_MIN_CELLS (1LL << 20)
+#endif
+constexpr long long PR_MIN_CELLS = WV_PR_MIN_CELLS;  // smaller grids step by step
+constexpr int PR_MIN_KC = 4, PR_MAX_KC = 32;
+struct PairPlan {
+    bool use;
+    int lxw, core_y, tiles_x, tiles_y, kc, chunks;
+};
+PairPlan pair_plan(int nz, int ny, int nx, int nsrc);
+struct PairArgs {
+    int nz, ny, nx;
+    long long N, sstride;
+    float dtdx, dt;
+    const float *wzc, *wzf, *wyc, *wyf, *wxc, *wxf;
+    const float* m;
+    const float* in;
+    float* out;
+    int tiles_x, tiles_y, chunks_z, kc;
+    int flip;                // visiting order of the work-groups (stencil.hip)
+    int tidx, tidx2, nt;     // index of the two steps into traces, residual and wavelet rows
+    const int* src_kji;
+    int src_radius;
+    const float* src_w;
+    const float* wavelet;
+    // receivers by grid row: entries [rec_ptr[k ny + j] .. rec_ptr[k ny + j + 1]) of (i, receiver),
+    // in that order; rec_lev[k] = receivers of level k
+    const int *rec_ptr, *rec_lev;
+    const int2* rec_ent;
+    int nrec;
+    float* traces;
+    const float* resid;
+    const float *e1, *e2;    // adjoint: e of the two steps' levels; incremental likewise
+    long long estride;
+    float *acc, *blk;
+    int first, closes;       // adjoint: the pair starts / ends an accumulation block
+    const float* dm;
+    float *x1, *x2;          // forward, incremental: the new e of each step also here [S][N] (null: no)
+};
+void launch_pair(int mode, const PairPlan& p, const PairArgs& a, int nsrc, hipStream_t st);
+
 // ---- reductions / elementwise -------------------------------------------------------
 
 void launch_square(const float* c, float* m, long long n, hipStream_t st);
