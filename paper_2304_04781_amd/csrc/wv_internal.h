@@ -141,9 +141,12 @@ void launch_plane(int mode, const PlaneArgs& a, int nsrc, hipStream_t st);
 // ---- two steps of a 3D grid per launch (pair.hip) ---------------------------------------
 
 #ifndef WV_PR_MIN_CELLS
-#define WV_PR_MIN_CELLS (1LL << 20)
+#define WV_PR_MIN_CELLS (3LL << 18)
 #endif
-constexpr long long PR_MIN_CELLS = WV_PR_MIN_CELLS;  // smaller grids step by step
+// smaller grids step by step: too few work-groups of the pair to fill the GPU. A gradient by step /
+// by pair: 64^3 checkpointed 1.49 / 2.09 ms, 96^3 3.17 / 3.11 and bf16 latents 7.43 / 6.63,
+// 128^3 checkpointed 5.24 / 4.37, 256^3 with bf16 latents 62.6 / 55.0
+constexpr long long PR_MIN_CELLS = WV_PR_MIN_CELLS;
 constexpr int PR_MIN_KC = 4, PR_MAX_KC = 32;
 struct PairPlan {
     bool use;
