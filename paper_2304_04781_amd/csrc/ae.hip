@@ -64,7 +64,7 @@ struct Frag {
     unsigned m[NC];
 };
 
-// an epilogue with kTile = true takes the whole C tile from LDS: tile(m0, n0, rows, cols, C, ldc)
+// an epilogue with kTile = true takes the whole C tile from LDS: tile(m0, n0, rows, cols, C, ldc, bm, split)
 template <class E, class = void>
 struct EpiHasTile {
     static constexpr bool value = false;
@@ -73,6 +73,20 @@ template <class E>
 struct EpiHasTile<E, std::void_t<decltype(E::kTile)>> {
     static constexpr bool value = E::kTile;
 };
+
+// Where an epilogue's C tile in LDS (row stride BN + 4 floats) holds (row, col): blocks of 8
+// columns are exchanged by the row's group of 8, so that 8 columns x 8 row groups, the
+// elements a wave of the transposed store reads at once, lie in 64 different banks
+// (unswizzled the 8 row groups share 2). Rows are still read in aligned float4s.
+template <int BN>
+__device__ __forceinline__ int tile_col(int row, int col)
+{
+    return col ^ (((row >> 3) & (BN >= 64 ? 7 : 3)) * 8);
+}
+__device__ __forceinline__ int tile_col(int row, int col, int ldc)
+{
+    return col ^ (((row >> 3) & (ldc >= 68 ? 7 : 3)) * 8);
+}
 
 // per-thread loader state of one work-group's tile rows, set before the k loop: the
 // source row of each of its chunks (clamped to a valid row past the last one, with its
@@ -157,10 +171,19 @@ __global__ void __launch_bounds__(256) gemm_kernel(int M, int N, int K, int k_pe
     // mod 8) takes a contiguous run of tiles, so that reuse stays within one L2
     const int ntn = (N + BN - 1) / BN;
     const int ntiles = ntn * ((M + BM - 1) / BM);
-    int bid = blockIdx.x;
-    if (ntiles % 8 == 0) bid = (bid % 8) * (ntiles / 8) + bid / 8;
+    // A product split 8 ways over its depth gives each XCD one split instead: all its tiles read
+    // the same depth range, 1/8 of both operands (512 x 2048 x 4096: 2.5 MB per L2, else 9 MB;
+    // 21.5 -> 19.9 us).
+    int bid = blockIdx.x, split = blockIdx.z;
+    if (gridDim.z == 8) {
+        const int lin = bid + (int)gridDim.x * split;
+        split = lin & 7;
+        bid = lin >> 3;
+    } else if (ntiles % 8 == 0) {
+        bid = (bid % 8) * (ntiles / 8) + bid / 8;
+    }
     const int m0 = (bid / ntn) * BM, n0 = (bid % ntn) * BN;
-    const int kb = blockIdx.z * k_per_split;
+    const int kb = split * k_per_split;
     const int ke = min(K, kb + k_per_split);
 
     f32x4 acc[TM][TN];
@@ -240,9 +263,12 @@ __global__ void __launch_bounds__(256) gemm_kernel(int M, int N, int K, int k_pe
 #pragma unroll
             for (int b = 0; b < TN; ++b)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) C[(wm0 + a * 16 + cr + r) * LDC + wn0 + b * 16 + cc] = acc[a][b][r];
+                for (int r = 0; r < 4; ++r) {
+                    const int row = wm0 + a * 16 + cr + r;
+                    C[row * LDC + tile_col<BN>(row, wn0 + b * 16 + cc)] = acc[a][b][r];
+                }
         __syncthreads();
-        epi.tile(m0, n0, min(BM, M - m0), min(BN, N - n0), C, LDC, BM);
+        epi.tile(m0, n0, min(BM, M - m0), min(BN, N - n0), C, LDC, BM, split);
         return;
     }
 #pragma unroll
@@ -253,7 +279,7 @@ __global__ void __launch_bounds__(256) gemm_kernel(int M, int N, int K, int k_pe
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int row = m0 + wm0 + a * 16 + cr + r;
-                if (row < M && col < N) epi(row, col, acc[a][b][r], blockIdx.z);
+                if (row < M && col < N) epi(row, col, acc[a][b][r], split);
             }
         }
 }
@@ -269,14 +295,14 @@ struct EpiF32 {  // out[z][row][col] = v (+ bias[col])
         out[z * zstride + (long long)r * ld + c] = v + (bias ? bias[c] : 0.f);
     }
     // 4 consecutive columns per thread, one float4 store (cols and ld are multiples of 4)
-    __device__ __forceinline__ void tile(int m0, int n0, int rows, int cols, float* C, int ldc, int) const
+    __device__ __forceinline__ void tile(int m0, int n0, int rows, int cols, float* C, int ldc, int, int z) const
     {
         const int nq = cols / 4;
-        float* o = out + blockIdx.z * zstride;
+        float* o = out + z * zstride;
         for (int idx = threadIdx.x; idx < rows * nq; idx += 256) {
             const int rr = idx / nq, q = idx % nq;
             const int c = n0 + q * 4;
-            float4 v = *reinterpret_cast<const float4*>(C + rr * ldc + q * 4);
+            float4 v = *reinterpret_cast<const float4*>(C + rr * ldc + tile_col(rr, q * 4, ldc));
             if (bias) {
                 v.x += bias[c];
                 v.y += bias[c + 1];
@@ -324,11 +350,11 @@ __device__ __forceinline__ void tile_colsum(float* colpart, long long ldp, int m
         for (; r + 8 <= r1; r += 8) {
             float v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = C[(r + u) * ldc + c];
+            for (int u = 0; u < 8; ++u) v[u] = C[(r + u) * ldc + tile_col(r + u, c, ldc)];
 #pragma unroll
             for (int u = 0; u < 8; ++u) s += v[u];
         }
-        for (; r < r1; ++r) s += C[r * ldc + c];
+        for (; r < r1; ++r) s += C[r * ldc + tile_col(r, c, ldc)];
         red[threadIdx.x] = s;
     }
     __syncthreads();
@@ -340,16 +366,19 @@ __device__ __forceinline__ void tile_colsum(float* colpart, long long ldp, int m
 }
 
 // bf16 copy of a float32 C tile (rows x cols in LDS), transposed: T[(n0 + c) tld + m0 + r].
-// Thread item (column c, group of 8 rows): one 16-byte store; the 8 threads of a column
-// write 128 contiguous bytes (rows is a multiple of 8, tld of 8).
+// Thread item (column c, group g of 8 rows): one 16-byte store. Eight row groups (four in a
+// tile of 32 or 96 rows) by eight columns per wave: whole 128-byte lines of T, and LDS reads
+// without bank conflicts (rows is a multiple of 32, cols and tld of 8).
 __device__ __forceinline__ void tile_store_t(uint16_t* T, long long tld, int m0, int n0, int rows, int cols,
                                              const float* C, int ldc)
 {
     __syncthreads();
     const int rg = rows / 8;
+    const int gb = rg % 8 == 0 ? 3 : 2, nc = cols / 8;
     for (int i = threadIdx.x; i < cols * rg; i += 256) {
-        const int c = i / rg, g = i % rg;
-        const float* q = C + (g * 8) * ldc + c;
+        const int t = i >> (gb + 3);
+        const int c = (t % nc) * 8 + ((i >> gb) & 7), g = ((t / nc) << gb) + (i & ((1 << gb) - 1));
+        const float* q = C + (g * 8) * ldc + tile_col(g * 8, c, ldc);
         *reinterpret_cast<uint4*>(T + (long long)(n0 + c) * tld + m0 + g * 8) =
             make_uint4(f2bf2(q[0], q[ldc]), f2bf2(q[2 * ldc], q[3 * ldc]), f2bf2(q[4 * ldc], q[5 * ldc]),
                        f2bf2(q[6 * ldc], q[7 * ldc]));
@@ -373,14 +402,15 @@ struct EpiGelu {  // a = v + bias -> (pre-activation), bf16(gelu(a)) [and its tr
     // 8 consecutive columns per thread (cols is a multiple of 8): one 16-byte store of
     // bf16 activations, two float4 stores of the pre-activation; 16 threads write one
     // 128-column row segment in 256 contiguous bytes
-    __device__ __forceinline__ void tile(int m0, int n0, int rows, int cols, float* C, int ldc, int) const
+    __device__ __forceinline__ void tile(int m0, int n0, int rows, int cols, float* C, int ldc, int, int) const
     {
         const int nq = cols / 8;
         for (int idx = threadIdx.x; idx < rows * nq; idx += 256) {
             const int rr = idx / nq, q = idx % nq;
             const int c = n0 + q * 8;
-            const float4 v0 = *reinterpret_cast<const float4*>(C + rr * ldc + q * 8);
-            const float4 v1 = *reinterpret_cast<const float4*>(C + rr * ldc + q * 8 + 4);
+            float* cq = C + rr * ldc + tile_col(rr, q * 8, ldc);
+            const float4 v0 = *reinterpret_cast<const float4*>(cq);
+            const float4 v1 = *reinterpret_cast<const float4*>(cq + 4);
             const float4 b0 = *reinterpret_cast<const float4*>(bias + c);
             const float4 b1 = *reinterpret_cast<const float4*>(bias + c + 4);
             const float4 a0 = make_float4(v0.x + b0.x, v0.y + b0.y, v0.z + b0.z, v0.w + b0.w);
@@ -395,8 +425,8 @@ struct EpiGelu {  // a = v + bias -> (pre-activation), bf16(gelu(a)) [and its tr
             *reinterpret_cast<uint4*>(out + o) =
                 make_uint4(f2bf2(g0.x, g0.y), f2bf2(g0.z, g0.w), f2bf2(g1.x, g1.y), f2bf2(g1.z, g1.w));
             if (tout) {
-                *reinterpret_cast<float4*>(C + rr * ldc + q * 8) = g0;
-                *reinterpret_cast<float4*>(C + rr * ldc + q * 8 + 4) = g1;
+                *reinterpret_cast<float4*>(cq) = g0;
+                *reinterpret_cast<float4*>(cq + 4) = g1;
             }
         }
         if (tout) tile_store_t(tout, tld, m0, n0, rows, cols, C, ldc);
@@ -417,22 +447,23 @@ struct EpiGeluBack {  // d = v * gelu'(pre) -> bf16 [and its transpose], the til
     }
     // 8 consecutive columns per thread: vector loads of pre, one 16-byte bf16 store
     // (cols and ld are multiples of 8); d goes back into the tile for the sums
-    __device__ __forceinline__ void tile(int m0, int n0, int rows, int cols, float* C, int ldc, int bm) const
+    __device__ __forceinline__ void tile(int m0, int n0, int rows, int cols, float* C, int ldc, int bm, int) const
     {
         const int nq = cols / 8;
         for (int idx = threadIdx.x; idx < rows * nq; idx += 256) {
             const int rr = idx / nq, q = idx % nq;
             const long long o = (long long)(m0 + rr) * ld + n0 + q * 8;
-            const float4 v0 = *reinterpret_cast<const float4*>(C + rr * ldc + q * 8);
-            const float4 v1 = *reinterpret_cast<const float4*>(C + rr * ldc + q * 8 + 4);
+            float* cq = C + rr * ldc + tile_col(rr, q * 8, ldc);
+            const float4 v0 = *reinterpret_cast<const float4*>(cq);
+            const float4 v1 = *reinterpret_cast<const float4*>(cq + 4);
             const float4 p0 = *reinterpret_cast<const float4*>(pre + o);
             const float4 p1 = *reinterpret_cast<const float4*>(pre + o + 4);
             const float4 d0 = make_float4(v0.x * gelu_prime(p0.x), v0.y * gelu_prime(p0.y), v0.z * gelu_prime(p0.z),
                                           v0.w * gelu_prime(p0.w));
             const float4 d1 = make_float4(v1.x * gelu_prime(p1.x), v1.y * gelu_prime(p1.y), v1.z * gelu_prime(p1.z),
                                           v1.w * gelu_prime(p1.w));
-            *reinterpret_cast<float4*>(C + rr * ldc + q * 8) = d0;
-            *reinterpret_cast<float4*>(C + rr * ldc + q * 8 + 4) = d1;
+            *reinterpret_cast<float4*>(cq) = d0;
+            *reinterpret_cast<float4*>(cq + 4) = d1;
             *reinterpret_cast<uint4*>(out + o) = make_uint4(f2bf2(d0.x, d0.y), f2bf2(d0.z, d0.w), f2bf2(d1.x, d1.y),
                                                             f2bf2(d1.z, d1.w));
         }
@@ -455,17 +486,18 @@ struct EpiBF16T {
     {
         out[(long long)r * ld + c] = f2bf(v + (bias ? bias[c] : 0.f));
     }
-    __device__ __forceinline__ void tile(int m0, int n0, int rows, int cols, float* C, int ldc, int bm) const
+    __device__ __forceinline__ void tile(int m0, int n0, int rows, int cols, float* C, int ldc, int bm, int) const
     {
         const int nq = cols / 8;
         for (int idx = threadIdx.x; idx < rows * nq; idx += 256) {
             const int rr = idx / nq, q = idx % nq;
             const int c = n0 + q * 8;
+            float* cq = C + rr * ldc + tile_col(rr, q * 8, ldc);
             float x[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                x[u] = C[rr * ldc + q * 8 + u] + (bias ? bias[c + u] : 0.f);
-                C[rr * ldc + q * 8 + u] = x[u];
+                x[u] = cq[u] + (bias ? bias[c + u] : 0.f);
+                cq[u] = x[u];
             }
             *reinterpret_cast<uint4*>(out + (long long)(m0 + rr) * ld + c) =
                 make_uint4(f2bf2(x[0], x[1]), f2bf2(x[2], x[3]), f2bf2(x[4], x[5]), f2bf2(x[6], x[7]));
@@ -496,37 +528,53 @@ struct EpiMse {
     long long tld = 0;
     __device__ __forceinline__ void operator()(int, int, float, int) const {}
     // 8 consecutive columns per thread; 16 threads cover a 128-column row segment
-    __device__ __forceinline__ void tile(int m0, int n0, int rows, int cols, float* C, int ldc, int bm) const
+    __device__ __forceinline__ void tile(int m0, int n0, int rows, int cols, float* C, int ldc, int bm, int) const
     {
         const double inv = 1.0 / (512.0 * wsum[0]);
         const double inv2 = 2.0 * inv;  // d(loss)/d(yhat) per unit weight and difference
         const int nq = cols / 8;
         double tl = 0.0;  // this thread's rows (their q = 0 thread) of the tile's loss
-        for (int idx8 = threadIdx.x; idx8 < rows * nq; idx8 += 256) {
-            const int rr = idx8 / nq, q = idx8 % nq;
-            const int b = m0 + rr, c = n0 + q * 8;
-            const long long src = idx ? idx[b] : b;
-            const float wf = w[b * 4 + (c >> 9)];
-            const float f = (float)(wf * inv2);
-            const uint4 yv = *reinterpret_cast<const uint4*>(y + src * ld + c);
-            const uint32_t yw[4] = {yv.x, yv.y, yv.z, yv.w};
-            float d[8];
-            double acc = 0.0;
+        // the loads of U rows ahead of their use (one dependent pair per row was most of the epilogue)
+        constexpr int U = 4;
+        const int n = rows * nq;
+        for (int base = threadIdx.x; base < n; base += 256 * U) {
+            float wf[U];
+            uint4 yv[U];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const float yh = C[rr * ldc + q * 8 + u] + bias[c + u];
-                const float yi = bf2f((uint16_t)(u & 1 ? yw[u >> 1] >> 16 : yw[u >> 1] & 0xFFFFu));
-                const float diff = yh - yi;
-                acc += (double)wf * diff * diff;
-                d[u] = f * diff;
-                C[rr * ldc + q * 8 + u] = d[u];
+            for (int k = 0; k < U; ++k) {
+                const int i8 = min(base + 256 * k, n - 1);
+                const int b = m0 + i8 / nq, c = n0 + i8 % nq * 8;
+                const long long src = idx ? idx[b] : b;
+                wf[k] = w[b * 4 + (c >> 9)];
+                yv[k] = *reinterpret_cast<const uint4*>(y + src * ld + c);
             }
-            *reinterpret_cast<uint4*>(dq + (long long)b * ld + c) =
-                make_uint4(f2bf2(d[0], d[1]), f2bf2(d[2], d[3]), f2bf2(d[4], d[5]), f2bf2(d[6], d[7]));
-            // the row's share over the tile's columns: the nq threads of a row are consecutive
-            // and aligned (nq = cols / 8 is 8 or 16), so a width-nq shuffle sum closes it
-            for (int o = nq / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, nq);
-            if (q == 0) tl += acc;
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int i8 = base + 256 * k;
+                if (i8 >= n) break;
+                const int rr = i8 / nq, q = i8 % nq;
+                const int b = m0 + rr, c = n0 + q * 8;
+                float* cq = C + rr * ldc + tile_col(rr, q * 8, ldc);
+                const float f = (float)(wf[k] * inv2);
+                const uint32_t yw[4] = {yv[k].x, yv[k].y, yv[k].z, yv[k].w};
+                float d[8];
+                double acc = 0.0;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const float yh = cq[u] + bias[c + u];
+                    const float yi = bf2f((uint16_t)(u & 1 ? yw[u >> 1] >> 16 : yw[u >> 1] & 0xFFFFu));
+                    const float diff = yh - yi;
+                    acc += (double)wf[k] * diff * diff;
+                    d[u] = f * diff;
+                    cq[u] = d[u];
+                }
+                *reinterpret_cast<uint4*>(dq + (long long)b * ld + c) =
+                    make_uint4(f2bf2(d[0], d[1]), f2bf2(d[2], d[3]), f2bf2(d[4], d[5]), f2bf2(d[6], d[7]));
+                // the row's share over the tile's columns: the nq threads of a row are consecutive
+                // and aligned (nq = cols / 8 is 8 or 16), so a width-nq shuffle sum closes it
+                for (int o = nq / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, nq);
+                if (q == 0) tl += acc;
+            }
         }
         // the tile's loss: rows summed per wave (fixed shuffle order), then the 4 waves in order
         for (int o = 32; o > 0; o >>= 1) tl += __shfl_xor(tl, o, 64);
@@ -591,7 +639,7 @@ struct EpiTimeDenorm {  // decoder output of a time vector -> lo + r (v + b) int
     // 4 x-cells of one (t, lz, ly) row of the block, so each thread moves float4s
     // (one LDS read, one store), and a wave's store covers 64 consecutive blocks
     // (a contiguous run of x). The row's block and (lo, r) are resolved once.
-    __device__ __forceinline__ void tile(int m0, int n0, int rows, int cols, float* C, int ldc, int) const
+    __device__ __forceinline__ void tile(int m0, int n0, int rows, int cols, float* C, int ldc, int, int) const
     {
         const int rr = threadIdx.x & 127;
         if (rr >= rows) return;
@@ -607,7 +655,7 @@ struct EpiTimeDenorm {  // decoder output of a time vector -> lo + r (v + b) int
             const int t = c >> 6;
             if (t >= nvalid) break;  // columns ascend, so do the levels
             const int cell = c & 63, lz = cell >> 4, ly = (cell >> 2) & 3;
-            const float4 v = *reinterpret_cast<const float4*>(crow + cq * 4);
+            const float4 v = *reinterpret_cast<const float4*>(crow + tile_col(rr, cq * 4, ldc));
             const float4 bb = *reinterpret_cast<const float4*>(bias + c);
             *reinterpret_cast<float4*>(base + (long long)t * S * N + ((long long)lz * ny + ly) * nx) =
                 make_float4(lo + rg * (v.x + bb.x), lo + rg * (v.y + bb.y), lo + rg * (v.z + bb.z),
@@ -862,16 +910,28 @@ __global__ void batch_weights_kernel(const float* __restrict__ meta, const int* 
 {
     __shared__ double sh[256];
     double acc = 0.0;
-    for (int q = threadIdx.x; q < 4 * B; q += 256) {
-        const int b = q >> 2, f = q & 3;
-        float v = 1.0f;
-        if (weighting) {
-            const long long src = idx ? idx[b] : b;
-            const float t = meta[src * 8 + 2 * f + 1] / beta[f];
-            v = t * t;
+    // eight samples' loads ahead of their sums (each thread's in ascending order)
+    constexpr int U = 8;
+    for (int base = threadIdx.x; base < 4 * B; base += 256 * U) {
+        float v[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int q = min(base + 256 * k, 4 * B - 1), b = q >> 2, f = q & 3;
+            v[k] = 1.0f;
+            if (weighting) {
+                const long long src = idx ? idx[b] : b;
+                const float t = meta[src * 8 + 2 * f + 1] / beta[f];
+                v[k] = t * t;
+            }
         }
-        w[q] = v;
-        acc += v;
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int q = base + 256 * k;
+            if (q < 4 * B) {
+                w[q] = v[k];
+                acc += v[k];
+            }
+        }
     }
     sh[threadIdx.x] = acc;
     __syncthreads();
@@ -882,72 +942,138 @@ __global__ void batch_weights_kernel(const float* __restrict__ meta, const int* 
     if (threadIdx.x == 0) wsum[0] = sh[0];
 }
 
-__global__ void sum_partials_kernel(const double* __restrict__ partial, int n, double scale, double* __restrict__ out,
-                                    int accumulate)
-{
-    __shared__ double sh[256];
-    double a = 0.0;
-    for (int q = threadIdx.x; q < n; q += 256) a += partial[q];
-    sh[threadIdx.x] = a;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[0] = (accumulate ? out[0] : 0.0) + scale * sh[0];
-}
-
-// Several split sums in one launch: segment g sums part[g] ([splits[g]][4 n4[g]]) into
-// out[g], four consecutive elements per thread, eight partials loaded ahead of their
-// sums, each element summed in the order z = 0, 1, ...
-struct SumSegs {
-    const float* part[8];
-    float* out[8];
-    long long n4[8];
-    int splits[8];
-    long long first[9];  // first float4 of each segment in the launch
-    int nseg;
+// One launch after a batch's products, from their partials to the next batch's weights: every
+// gradient summed (the batch splits of a weight, the row tiles of a bias: from 0 in the order
+// z = 0, 1, ...), the Adam update, the bf16 copies W [fi][fo] and W^T [fo][fi], and the batch's
+// loss. Bound by memory: the partials (68 MB at 8 splits of 512 wide layers), 24 bytes a
+// parameter of moments and masters. A work-group takes a 64 x 32 tile of one layer's
+// weights, transposed through LDS, so that rows of both copies leave in whole segments. The loss
+// and the biases, chains of dependent sums, go first.
+// 4096 samples, 512 hidden: 128 MB in 23.9 us (5.3 TB/s); as four launches (sums, Adam, copies,
+// loss) 37 us, the summed gradients written and read again.
+struct UpdateArgs {
+    const float* wpart[4];
+    const float* bpart[4];
+    long long oW[4], ob[4];
+    uint16_t* wb[4];
+    uint16_t* wt[4];
+    int fi[4], fo[4];
+    int first[5];   // first work-group of each layer's tiles, after the loss and the biases
+    int tx[4];      // column tiles of each layer
+    int bfirst[5];  // first float4 of each bias
+    int brows[4];   // row tiles of each bias
+    int splits;
+    float *w, *m, *v;
+    float* grad;  // nullable: the summed gradients as well
+    float lr, b1, b2, eps, c1, c2;
+    const double* lossp;
+    int nloss;
+    double* dloss;
+    int accumulate;
 };
-__global__ void __launch_bounds__(256) sums_kernel(const SumSegs g)
+// four elements summed over n partials `stride` float4s apart, eight loads ahead of their sums
+__device__ __forceinline__ float4 sum_parts(const float4* __restrict__ p, int n, long long stride)
 {
-    const long long q = blockIdx.x * 256LL + threadIdx.x;
-    if (q >= g.first[g.nseg]) return;
-    int sg = 0;
-    while (sg + 1 < g.nseg && q >= g.first[sg + 1]) ++sg;
-    const long long j = q - g.first[sg];
-    const long long n4 = g.n4[sg];
-    const int splits = g.splits[sg];
-    const float4* p = reinterpret_cast<const float4*>(g.part[sg]) + j;
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
     int z = 0;
-    for (; z + 8 <= splits; z += 8) {
+    for (; z + 8 <= n; z += 8) {
         float4 v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = p[(long long)(z + u) * n4];
+        for (int u = 0; u < 8; ++u) v[u] = p[(long long)(z + u) * stride];
 #pragma unroll
         for (int u = 0; u < 8; ++u) s = make_float4(s.x + v[u].x, s.y + v[u].y, s.z + v[u].z, s.w + v[u].w);
     }
-    for (; z < splits; ++z) {
-        const float4 v = p[(long long)z * n4];
+    for (; z < n; ++z) {
+        const float4 v = p[(long long)z * stride];
         s = make_float4(s.x + v.x, s.y + v.y, s.z + v.z, s.w + v.w);
     }
-    reinterpret_cast<float4*>(g.out[sg])[j] = s;
+    return s;
 }
-
-
-__global__ void adam_kernel(float* __restrict__ w, float* __restrict__ m, float* __restrict__ v,
-                            const float* __restrict__ g, long long n, float lr, float b1, float b2, float eps,
-                            float c1, float c2)
+__device__ __forceinline__ void adam(const UpdateArgs& a, float gi, float& w, float& m, float& v)
 {
-    const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    const float mh = mi / c1, vh = vi / c2;
-    w[i] = w[i] - lr * mh / (sqrtf(vh) + eps);
+#pragma clang fp contract(off)
+    // the roundings are written out: which product an addition takes in is part of the result
+    const float mi = __builtin_fmaf(1.0f - a.b1, gi, a.b1 * m);
+    const float vi = __builtin_fmaf(gi, (1.0f - a.b2) * gi, a.b2 * v);
+    m = mi;
+    v = vi;
+    const float mh = mi / a.c1, vh = vi / a.c2;
+    w = w - a.lr * mh / (sqrtf(vh) + a.eps);
+}
+// the parameters o .. o + 3: moments and masters updated in place; the new weights
+__device__ __forceinline__ float4 adam4(const UpdateArgs& a, long long o, float4 g)
+{
+    float4 w = *reinterpret_cast<float4*>(a.w + o), m = *reinterpret_cast<float4*>(a.m + o),
+           v = *reinterpret_cast<float4*>(a.v + o);
+    adam(a, g.x, w.x, m.x, v.x);
+    adam(a, g.y, w.y, m.y, v.y);
+    adam(a, g.z, w.z, m.z, v.z);
+    adam(a, g.w, w.w, m.w, v.w);
+    *reinterpret_cast<float4*>(a.w + o) = w;
+    *reinterpret_cast<float4*>(a.m + o) = m;
+    *reinterpret_cast<float4*>(a.v + o) = v;
+    if (a.grad) *reinterpret_cast<float4*>(a.grad + o) = g;
+    return w;
+}
+constexpr int UPD_R = 64, UPD_C = 32;
+__global__ void __launch_bounds__(256) update_kernel(const UpdateArgs a)
+{
+    const int tid = threadIdx.x;
+    int t = blockIdx.x;
+    if (t == 0) {
+        __shared__ double sh[256];
+        double s = 0.0;
+        for (int q = tid; q < a.nloss; q += 256) s += a.lossp[q];
+        sh[tid] = s;
+        __syncthreads();
+        for (int o = 128; o > 0; o >>= 1) {
+            if (tid < o) sh[tid] += sh[tid + o];
+            __syncthreads();
+        }
+        if (tid == 0) a.dloss[0] = (a.accumulate ? a.dloss[0] : 0.0) + sh[0];
+        return;
+    }
+    if (t < a.first[0]) {
+        const int q = (t - 1) * 256 + tid;
+        if (q >= a.bfirst[4]) return;
+        int l = 0;
+        while (l < 3 && q >= a.bfirst[l + 1]) ++l;
+        const int j = q - a.bfirst[l];
+        const float4 g = sum_parts(reinterpret_cast<const float4*>(a.bpart[l]) + j, a.brows[l], a.fo[l] / 4);
+        adam4(a, a.ob[l] + 4 * j, g);
+        return;
+    }
+    __shared__ uint16_t s[UPD_R][UPD_C + 2];
+    int l = 0;
+    while (l < 3 && t >= a.first[l + 1]) ++l;
+    t -= a.first[l];
+    const int fi = a.fi[l], fo = a.fo[l];
+    const int r0 = (t / a.tx[l]) * UPD_R, c0 = (t % a.tx[l]) * UPD_C;
+    const long long n4 = (long long)fi * fo / 4;
+#pragma unroll
+    for (int k = 0; k < UPD_R * UPD_C / 1024; ++k) {
+        const int i = tid + 256 * k;
+        const int r = i / (UPD_C / 4), c = i % (UPD_C / 4) * 4;
+        if (r0 + r >= fi || c0 + c >= fo) continue;
+        const long long o = (long long)(r0 + r) * fo + c0 + c;
+        const float4 g = sum_parts(reinterpret_cast<const float4*>(a.wpart[l] + o), a.splits, n4);
+        const float4 w = adam4(a, a.oW[l] + o, g);
+        const uint16_t b0 = f2bf(w.x), b1 = f2bf(w.y), b2 = f2bf(w.z), b3 = f2bf(w.w);
+        *reinterpret_cast<uint2*>(a.wb[l] + o) = make_uint2(b0 | (uint32_t)b1 << 16, b2 | (uint32_t)b3 << 16);
+        s[r][c] = b0;
+        s[r][c + 1] = b1;
+        s[r][c + 2] = b2;
+        s[r][c + 3] = b3;
+    }
+    __syncthreads();
+    static_assert(UPD_R * UPD_C == 256 * 8, "one 16-byte piece of the transpose per thread");
+    const int c = tid / (UPD_R / 8), r = tid % (UPD_R / 8) * 8;
+    if (c0 + c < fo && r0 + r < fi) {
+        uint32_t q[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) q[u] = s[r + 2 * u][c] | (uint32_t)s[r + 2 * u + 1][c] << 16;
+        *reinterpret_cast<uint4*>(a.wt[l] + (long long)(c0 + c) * fi + r0 + r) = make_uint4(q[0], q[1], q[2], q[3]);
+    }
 }
 
 // fp32 W_l [fi][fo] -> bf16 W_l [fi][fo] and bf16 W_l^T [fo][fi] for the 4 layers in one
@@ -1070,10 +1196,10 @@ void pack_fused(ae_net* a, hipStream_t st)
     }
 }
 
-// bf16 copies of the weights after a change of the fp32 masters; with pack, also the
-// fragment-ordered copies of the fused encode and decode (training skips them until
-// its last step: only the inference kernels read them)
-void refresh_bf16(ae_net* a, hipStream_t st, bool pack = true)
+// bf16 copies of the weights after a change of the fp32 masters, and the fragment-ordered
+// copies of the fused encode and decode (a training step updates the former by itself and leaves
+// the latter to the end: only the inference kernels read them)
+void refresh_bf16(ae_net* a, hipStream_t st)
 {
     ConvLayers c{};
     int n = 0;
@@ -1090,7 +1216,7 @@ void refresh_bf16(ae_net* a, hipStream_t st, bool pack = true)
     c.first[4] = n;
     hipLaunchKernelGGL(convert_kernel, dim3(n), dim3(256), 0, st, c);
     WV_HIP(hipGetLastError());
-    if (pack) pack_fused(a, st);
+    pack_fused(a, st);
 }
 
 void upload_beta(ae_net* a)
@@ -1487,7 +1613,7 @@ void transpose_rows(const uint16_t* src, long long ld, const int* rows, int R, i
 
 // dW_l = X^T D over the batch, from both operands stored transposed ([width][batch], so
 // the GEMM streams whole k-contiguous rows): the batch is split `splits` ways and the
-// partials are summed at the end of the batch (sum_grads)
+// partials are summed at the end of the batch (update_kernel)
 void weight_grad(ae_net* a, int l, int B, const uint16_t* Xt, const uint16_t* Dt, TrainBufs& t, int splits,
                  hipStream_t st)
 {
@@ -1496,34 +1622,11 @@ void weight_grad(ae_net* a, int l, int B, const uint16_t* Xt, const uint16_t* Dt
               EpiF32{t.wpart[l], fo, (long long)fi * fo, nullptr}, st, splits);
 }
 
-// every gradient of the batch from its partials, in one launch: the 4 weight gradients
-// (split sums) and the 4 bias gradients (row-tile column sums of width fo_l, from
-// work-group tiles of bm[l] rows), each summed in a fixed order
-void sum_grads(ae_net* a, int B, int splits, const int* bm, TrainBufs& t, hipStream_t st)
+// one batch: the products, then the update. with_grads: the summed gradients also go to a->grad
+void train_batch(ae_net* a, const uint16_t* y, const float* meta, const ae_train_cfg& cfg, double lr, const int* idx,
+                 int B, TrainBufs& t, int splits, double* dloss, int accumulate, bool with_grads, hipStream_t st)
 {
-    SumSegs g{};
-    long long q = 0;
-    int sg = 0;
-    for (int l = 0; l < 4; ++l)
-        for (int b = 0; b < 2; ++b) {
-            const long long n = b ? a->fo[l] : (long long)a->fi[l] * a->fo[l];
-            WV_REQUIRE(n % 4 == 0, WV_EINVAL, "gradient sums need layer widths that are multiples of 4");
-            g.part[sg] = b ? t.bpart[l] : t.wpart[l];
-            g.out[sg] = a->grad + (b ? a->ob[l] : a->oW[l]);
-            g.n4[sg] = n / 4;
-            g.splits[sg] = b ? (B + bm[l] - 1) / bm[l] : splits;
-            g.first[sg] = q;
-            q += n / 4;
-            ++sg;
-        }
-    g.first[sg] = q;
-    g.nseg = sg;
-    hipLaunchKernelGGL(sums_kernel, dim3(blocks(q, 256)), dim3(256), 0, st, g);
-}
-
-void train_batch(ae_net* a, const uint16_t* y, const float* meta, int weighting, const int* idx, int B,
-                 TrainBufs& t, int splits, double* dloss, int accumulate, hipStream_t st)
-{
+    const int weighting = cfg.weighting;
     const int in = a->in, hid = a->hid, lat = a->lat;
     // forward; the epilogues also write the transposed activations the weight gradients read
     gemm_auto(B, hid, in, LoadK{y, in, idx, B, in}, LoadK{a->wt[0], in, nullptr, hid, in},
@@ -1545,8 +1648,6 @@ void train_batch(ae_net* a, const uint16_t* y, const float* meta, int weighting,
     const int bn4 = gemm_auto_bn(B, in);
     gemm_auto(B, in, hid, LoadK{t.h3, hid, nullptr, B, hid}, LoadK{a->wt[3], hid, nullptr, in, hid},
               EpiMse{a->bias(3), y, idx, in, t.w, t.wsum, t.d4, t.bpart[3], t.lossp, in / bn4, t.d4t, B}, st);
-    hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, st, t.lossp,
-                       ((B + bm[3] - 1) / bm[3]) * (in / bn4), 1.0, dloss, accumulate);
     // backward: layer 4
     weight_grad(a, 3, B, t.h3t, t.d4t, t, splits, st);
     gemm_auto(B, hid, in, LoadK{t.d4, in, nullptr, B, in}, LoadK{a->wb[3], in, nullptr, hid, in},
@@ -1562,7 +1663,46 @@ void train_batch(ae_net* a, const uint16_t* y, const float* meta, int weighting,
     // layer 1: the batch's input rows, gathered and transposed
     transpose_rows(y, in, idx, B, in, t.yt, st);
     weight_grad(a, 0, B, t.yt, t.d1t, t, splits, st);
-    sum_grads(a, B, splits, bm, t, st);
+    a->step += 1;
+    UpdateArgs u{};
+    int n = 0, nb = 0;
+    for (int l = 0; l < 4; ++l) {
+        u.bfirst[l] = nb;
+        nb += a->fo[l] / 4;
+    }
+    u.bfirst[4] = nb;
+    n = 1 + blocks(nb, 256);
+    for (int l = 0; l < 4; ++l) {
+        u.wpart[l] = t.wpart[l];
+        u.bpart[l] = t.bpart[l];
+        u.oW[l] = a->oW[l];
+        u.ob[l] = a->ob[l];
+        u.wb[l] = a->wb[l];
+        u.wt[l] = a->wt[l];
+        u.fi[l] = a->fi[l];
+        u.fo[l] = a->fo[l];
+        u.brows[l] = (B + bm[l] - 1) / bm[l];
+        u.tx[l] = (a->fo[l] + UPD_C - 1) / UPD_C;
+        u.first[l] = n;
+        n += u.tx[l] * ((a->fi[l] + UPD_R - 1) / UPD_R);
+    }
+    u.first[4] = n;
+    u.splits = splits;
+    u.w = a->master;
+    u.m = a->m1;
+    u.v = a->m2;
+    u.grad = with_grads ? a->grad : nullptr;
+    u.lr = (float)lr;
+    u.b1 = (float)cfg.beta1;
+    u.b2 = (float)cfg.beta2;
+    u.eps = (float)cfg.eps;
+    u.c1 = (float)(1.0 - std::pow(cfg.beta1, (double)a->step));
+    u.c2 = (float)(1.0 - std::pow(cfg.beta2, (double)a->step));
+    u.lossp = t.lossp;
+    u.nloss = ((B + bm[3] - 1) / bm[3]) * (in / bn4);
+    u.dloss = dloss;
+    u.accumulate = accumulate;
+    hipLaunchKernelGGL(update_kernel, dim3(n), dim3(256), 0, st, u);
     WV_HIP(hipGetLastError());
 }
 
@@ -1572,17 +1712,6 @@ void train_batch(ae_net* a, const uint16_t* y, const float* meta, int weighting,
 #define WV_TRAIN_SPLITS_MAX 8
 #endif
 int train_splits(int B) { return std::max(1, std::min(WV_TRAIN_SPLITS_MAX, B / 512)); }
-
-void adam_update(ae_net* a, double lr, const ae_train_cfg& cfg, hipStream_t st, bool pack = true)
-{
-    a->step += 1;
-    const double c1 = 1.0 - std::pow(cfg.beta1, (double)a->step);
-    const double c2 = 1.0 - std::pow(cfg.beta2, (double)a->step);
-    hipLaunchKernelGGL(adam_kernel, dim3(blocks(a->nparam, 256)), dim3(256), 0, st, a->master, a->m1, a->m2, a->grad,
-                       a->nparam, (float)lr, (float)cfg.beta1, (float)cfg.beta2, (float)cfg.eps, (float)c1, (float)c2);
-    WV_HIP(hipGetLastError());
-    refresh_bf16(a, st, pack);
-}
 
 ae_net* new_net(int in, int hid, int lat)
 {
@@ -1939,9 +2068,9 @@ int ae_train_step(ae_net* a, const uint16_t* y, const float* meta, const int32_t
         const int splits = train_splits(B);
         TrainBufs t = train_buffers(a, B, splits, st);
         double* dloss = a->loss_d;
-        train_batch(a, y, meta, cfg->weighting, idx, B, t, splits, dloss, 0, st);
+        train_batch(a, y, meta, *cfg, lr, idx, B, t, splits, dloss, 0, h_grads != nullptr, st);
         if (h_grads) WV_HIP(hipMemcpyAsync(h_grads, a->grad, a->nparam * 4, hipMemcpyDeviceToHost, st));
-        adam_update(a, lr, *cfg, st);
+        pack_fused(a, st);
         double L = 0;
         WV_HIP(hipMemcpyAsync(&L, dloss, sizeof(double), hipMemcpyDeviceToHost, st));
         WV_HIP(hipStreamSynchronize(st));
@@ -1976,8 +2105,7 @@ int ae_train(ae_net* a, const uint16_t* y, const float* meta, int64_t nsamples, 
             const double lr = cfg->lr * std::pow(cfg->decay_factor, (double)(e / std::max(cfg->decay_every, 1)));
             const int* order = perm ? perm + (long long)e * nsamples : dseq;
             for (long long b = 0; b < nb; ++b) {
-                train_batch(a, y, meta, cfg->weighting, order + b * B, B, t, splits, dloss, b > 0, st);
-                adam_update(a, lr, *cfg, st, false);
+                train_batch(a, y, meta, *cfg, lr, order + b * B, B, t, splits, dloss, b > 0, false, st);
             }
             double L = 0;
             WV_HIP(hipMemcpyAsync(&L, dloss, sizeof(double), hipMemcpyDeviceToHost, st));
