@@ -39,12 +39,13 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // that know the source layout; epilogues consume (row, col, value).
 // ------------------------------------------------------------------------------------
 constexpr int BK = 64;  // k per LDS stage: two 32-deep MFMA steps; depths below a multiple are zero-filled
-// k-tiles in flight in the generic GEMM (128 x 128 work-group tiles, smaller ones)
+// k-tiles in flight in the generic GEMM (128 x 128 work-group tiles, smaller ones): 64 Adam steps
+// at 4096 samples take 12.60 ms with 4 for the smaller tiles, 12.30 with 3 (6, 8: no better)
 #ifndef WV_GEMM_PF_BIG
 #define WV_GEMM_PF_BIG 3
 #endif
 #ifndef WV_GEMM_PF_SMALL
-#define WV_GEMM_PF_SMALL 4
+#define WV_GEMM_PF_SMALL 3
 #endif
 constexpr int GEMM_PF_BIG = WV_GEMM_PF_BIG, GEMM_PF_SMALL = WV_GEMM_PF_SMALL;
 static_assert(GEMM_PF_BIG >= 2 && GEMM_PF_SMALL >= 2, "at least the next k-tile in flight");
@@ -151,36 +152,46 @@ struct LoadK {
 };
 
 
-template <int BM, int BN, int WM, int WN, class LA, class LB, class EPI>
-__global__ void __launch_bounds__(256) gemm_kernel(int M, int N, int K, int k_per_split, LA la, LB lb, EPI epi)
+// one product as a launch's work: `tiles` x `splits` work-groups, number lin = 0, 1, ...
+template <int BM_, int BN_, int WM_, int WN_, class LA, class LB, class EPI>
+struct GemmWork {
+    static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
+    // two LDS stages of both operands
+    static constexpr int LDS = 2 * (BM + BN) * (BK + LDS_PAD);
+    int M, N, K, k_per_split, tiles, splits;
+    LA la;
+    LB lb;
+    EPI epi;
+    int groups() const { return tiles * splits; }
+    __device__ __forceinline__ void run(uint16_t* smem, int lin) const;
+};
+template <int BM_, int BN_, int WM_, int WN_, class LA, class LB, class EPI>
+__device__ __forceinline__ void GemmWork<BM_, BN_, WM_, WN_, LA, LB, EPI>::run(uint16_t* smem, int lin) const
 {
     static_assert((BM / WM) * (BN / WN) == 4, "4 waves");
     constexpr int TM = WM / 16, TN = WN / 16;
     // two LDS stages: the next k-tile is loaded into registers while the MFMAs of the
     // current one run, and stored to the other stage after them. An epilogue that
     // writes whole tiles gets the C tile staged in the same memory afterwards.
-    __shared__ __attribute__((aligned(16))) uint16_t smem[2 * (BM + BN) * (BK + LDS_PAD)];
     auto sA = reinterpret_cast<uint16_t(*)[BM][BK + LDS_PAD]>(smem);
     auto sB = reinterpret_cast<uint16_t(*)[BN][BK + LDS_PAD]>(smem + 2 * BM * (BK + LDS_PAD));
 
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
     const int wm0 = (wave / (BN / WN)) * WM, wn0 = (wave % (BN / WN)) * WN;
-    // tiles in a 1D grid, column tiles fastest so the row tile of A is reused from L2 by
-    // the work-groups that follow; with a multiple of 8 tiles each XCD (work-group id
-    // mod 8) takes a contiguous run of tiles, so that reuse stays within one L2
+    // column tiles fastest so the row tile of A is reused from L2 by the work-groups that
+    // follow; with a multiple of 8 tiles each XCD (work-group number mod 8) takes a
+    // contiguous run of tiles, so that reuse stays within one L2
     const int ntn = (N + BN - 1) / BN;
-    const int ntiles = ntn * ((M + BM - 1) / BM);
     // A product split 8 ways over its depth gives each XCD one split instead: all its tiles read
     // the same depth range, 1/8 of both operands (512 x 2048 x 4096: 2.5 MB per L2, else 9 MB;
     // 21.5 -> 19.9 us).
-    int bid = blockIdx.x, split = blockIdx.z;
-    if (gridDim.z == 8) {
-        const int lin = bid + (int)gridDim.x * split;
+    int bid = lin % tiles, split = lin / tiles;
+    if (splits == 8) {
         split = lin & 7;
         bid = lin >> 3;
-    } else if (ntiles % 8 == 0) {
-        bid = (bid % 8) * (ntiles / 8) + bid / 8;
+    } else if (tiles % 8 == 0) {
+        bid = (bid % 8) * (tiles / 8) + bid / 8;
     }
     const int m0 = (bid / ntn) * BM, n0 = (bid % ntn) * BN;
     const int kb = split * k_per_split;
@@ -256,7 +267,7 @@ __global__ void __launch_bounds__(256) gemm_kernel(int M, int N, int K, int k_pe
     const int cc = lane & 15, cr = (lane >> 4) * 4;
     if constexpr (EpiHasTile<EPI>::value) {
         constexpr int LDC = BN + 4;
-        static_assert(BM * LDC * 4 <= (int)sizeof(smem), "the C tile fits in the operand stages");
+        static_assert(BM * LDC * 4 <= LDS * 2, "the C tile fits in the operand stages");
         float* C = reinterpret_cast<float*>(smem);  // the loop ended with a barrier: the stages are free
 #pragma unroll
         for (int a = 0; a < TM; ++a)
@@ -282,6 +293,25 @@ __global__ void __launch_bounds__(256) gemm_kernel(int M, int N, int K, int k_pe
                 if (row < M && col < N) epi(row, col, acc[a][b][r], split);
             }
         }
+}
+template <class W>
+__global__ void __launch_bounds__(256) gemm_kernel(const W w)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t smem[W::LDS];
+    w.run(smem, blockIdx.x);
+}
+// Two works that do not need each other's results in one launch: a training step is a chain of
+// launches of some 10 us, each of which fills and drains the GPU once. The second begins where the
+// first leaves CUs idle (4096 samples: a delta with a weight gradient 42 us, apart 25 + 20; the
+// first product with the rows' transpose 30, apart 25 + 7; a step 210 -> 195 us).
+template <class W1, class W2>
+__global__ void __launch_bounds__(256) two_works_kernel(const W1 w1, const W2 w2, int n1)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t smem[W1::LDS > W2::LDS ? W1::LDS : W2::LDS];
+    if ((int)blockIdx.x < n1)
+        w1.run(smem, blockIdx.x);
+    else
+        w2.run(smem, blockIdx.x - n1);
 }
 
 // ---- epilogues ----------------------------------------------------------------------
@@ -603,16 +633,6 @@ struct EpiDenorm {  // decoder output of field f -> lo + r (v + b) scattered int
     }
 };
 
-template <int BM, int BN, int WM, int WN, class LA, class LB, class EPI>
-void gemm(int M, int N, int K, const LA& la, const LB& lb, const EPI& epi, hipStream_t st, int splits = 1)
-{
-    WV_REQUIRE(K % 32 == 0, WV_EINVAL, "GEMM depth must be a multiple of 32");
-    const int kps = (((K + BK - 1) / BK + splits - 1) / splits) * BK;
-    dim3 grid(((M + BM - 1) / BM) * ((N + BN - 1) / BN), 1, splits);
-    hipLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, LA, LB, EPI>), grid, dim3(256), 0, st, M, N, K, kps, la, lb, epi);
-    WV_HIP(hipGetLastError());
-}
-
 // wide N (>= 128) and narrow N (<= 32) tile shapes
 struct EpiTimeDenorm {  // decoder output of a time vector -> lo + r (v + b) into levels t < nvalid
     static constexpr bool kTile = true;
@@ -681,16 +701,46 @@ inline int gemm_auto_bn(int M, int N, int splits = 1)
     return N <= 32 ? 32 : (wg128 < WV_GEMM_BIG_MIN_WG ? 64 : 128);
 }
 
-template <class LA, class LB, class EPI>
-void gemm_auto(int M, int N, int K, const LA& la, const LB& lb, const EPI& epi, hipStream_t st, int splits = 1)
+template <int BM, int BN, int WM, int WN, class LA, class LB, class EPI>
+GemmWork<BM, BN, WM, WN, LA, LB, EPI> gemm_work(int M, int N, int K, const LA& la, const LB& lb, const EPI& epi,
+                                                int splits)
+{
+    WV_REQUIRE(K % 32 == 0, WV_EINVAL, "GEMM depth must be a multiple of 32");
+    const int kps = (((K + BK - 1) / BK + splits - 1) / splits) * BK;
+    return {M, N, K, kps, ((M + BM - 1) / BM) * ((N + BN - 1) / BN), splits, la, lb, epi};
+}
+
+// go(work) with the product's work in the tiles chosen for it
+template <class LA, class LB, class EPI, class GO>
+void gemm_visit(int M, int N, int K, const LA& la, const LB& lb, const EPI& epi, int splits, GO&& go)
 {
     const int bm = gemm_auto_bm(M, N, splits), bn = gemm_auto_bn(M, N, splits);
     if (bn == 32)
-        gemm<128, 32, 32, 32>(M, N, K, la, lb, epi, st, splits);
+        go(gemm_work<128, 32, 32, 32>(M, N, K, la, lb, epi, splits));
     else if (bm == 64)
-        gemm<64, 64, 32, 32>(M, N, K, la, lb, epi, st, splits);
+        go(gemm_work<64, 64, 32, 32>(M, N, K, la, lb, epi, splits));
     else
-        gemm<128, 128, 64, 64>(M, N, K, la, lb, epi, st, splits);
+        go(gemm_work<128, 128, 64, 64>(M, N, K, la, lb, epi, splits));
+}
+
+template <class W>
+void launch_work(const W& w, hipStream_t st)
+{
+    hipLaunchKernelGGL((gemm_kernel<W>), dim3(w.groups()), dim3(256), 0, st, w);
+    WV_HIP(hipGetLastError());
+}
+template <class W1, class W2>
+void launch_works(const W1& w1, const W2& w2, hipStream_t st)
+{
+    hipLaunchKernelGGL((two_works_kernel<W1, W2>), dim3(w1.groups() + w2.groups()), dim3(256), 0, st, w1, w2,
+                       w1.groups());
+    WV_HIP(hipGetLastError());
+}
+
+template <class LA, class LB, class EPI>
+void gemm_auto(int M, int N, int K, const LA& la, const LB& lb, const EPI& epi, hipStream_t st)
+{
+    gemm_visit(M, N, K, la, lb, epi, 1, [&](const auto& w) { launch_work(w, st); });
 }
 
 // ------------------------------------------------------------------------------------
@@ -1567,59 +1617,58 @@ TrainBufs train_buffers(const ae_net* a, int B, int splits, hipStream_t st)
     return t;
 }
 
-// weight gradient dW[fi][fo] = X^T D with split-K over the batch
 // dst [C][R] = src rows transposed: dst[c][r] = src[rows ? rows[r] : r][c] for a bf16
 // matrix of R rows (R % 8 == 0) and C columns (C % 8 == 0) with row stride ld; 64 x 64
 // tiles through LDS, 16-byte loads and stores
-__global__ void __launch_bounds__(256) transpose_kernel(const uint16_t* __restrict__ src, long long ld,
-                                                        const int* __restrict__ rows, int R, int C,
-                                                        uint16_t* __restrict__ dst)
-{
-    __shared__ uint16_t tile[64][64 + 2];
-    const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
+struct TransposeWork {
+    static constexpr int LDT = 64 + 2, LDS = 64 * LDT;
+    const uint16_t* src;
+    long long ld;
+    const int* rows;
+    int R, C;
+    uint16_t* dst;
+    int groups() const { return (C + 63) / 64 * ((R + 63) / 64); }
+    __device__ __forceinline__ void run(uint16_t* tile, int lin) const
+    {
+        const int nc = (C + 63) / 64;
+        const int c0 = lin % nc * 64, r0 = lin / nc * 64;
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int k = threadIdx.x + 256 * q;
-        const int r = k >> 3, c8 = (k & 7) * 8;
-        uint16_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (r0 + r < R && c0 + c8 < C) {
-            const long long sr = rows ? rows[r0 + r] : r0 + r;
-            const uint4 w = *reinterpret_cast<const uint4*>(src + sr * ld + c0 + c8);
-            memcpy(v, &w, 16);
+        for (int q = 0; q < 2; ++q) {
+            const int k = threadIdx.x + 256 * q;
+            const int r = k >> 3, c8 = (k & 7) * 8;
+            uint16_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+            if (r0 + r < R && c0 + c8 < C) {
+                const long long sr = rows ? rows[r0 + r] : r0 + r;
+                const uint4 w = *reinterpret_cast<const uint4*>(src + sr * ld + c0 + c8);
+                memcpy(v, &w, 16);
+            }
+            for (int i = 0; i < 8; ++i) tile[r * LDT + c8 + i] = v[i];
         }
-        for (int i = 0; i < 8; ++i) tile[r][c8 + i] = v[i];
-    }
-    __syncthreads();
+        __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int k = threadIdx.x + 256 * q;
-        const int c = k >> 3, r8 = (k & 7) * 8;
-        if (c0 + c < C && r0 + r8 < R) {
-            uint16_t v[8];
-            for (int i = 0; i < 8; ++i) v[i] = tile[r8 + i][c];
-            uint4 w;
-            memcpy(&w, v, 16);
-            *reinterpret_cast<uint4*>(dst + (long long)(c0 + c) * R + r0 + r8) = w;
+        for (int q = 0; q < 2; ++q) {
+            const int k = threadIdx.x + 256 * q;
+            const int c = k >> 3, r8 = (k & 7) * 8;
+            if (c0 + c < C && r0 + r8 < R) {
+                uint16_t v[8];
+                for (int i = 0; i < 8; ++i) v[i] = tile[(r8 + i) * LDT + c];
+                uint4 w;
+                memcpy(&w, v, 16);
+                *reinterpret_cast<uint4*>(dst + (long long)(c0 + c) * R + r0 + r8) = w;
+            }
         }
     }
-}
-
-void transpose_rows(const uint16_t* src, long long ld, const int* rows, int R, int C, uint16_t* dst, hipStream_t st)
-{
-    hipLaunchKernelGGL(transpose_kernel, dim3((C + 63) / 64, (R + 63) / 64), dim3(256), 0, st, src, ld, rows, R, C,
-                       dst);
-    WV_HIP(hipGetLastError());
-}
+};
 
 // dW_l = X^T D over the batch, from both operands stored transposed ([width][batch], so
 // the GEMM streams whole k-contiguous rows): the batch is split `splits` ways and the
 // partials are summed at the end of the batch (update_kernel)
-void weight_grad(ae_net* a, int l, int B, const uint16_t* Xt, const uint16_t* Dt, TrainBufs& t, int splits,
-                 hipStream_t st)
+template <class GO>
+void weight_grad(ae_net* a, int l, int B, const uint16_t* Xt, const uint16_t* Dt, TrainBufs& t, int splits, GO&& go)
 {
     const int fi = a->fi[l], fo = a->fo[l];
-    gemm_auto(fi, fo, B, LoadK{Xt, B, nullptr, fi, B}, LoadK{Dt, B, nullptr, fo, B},
-              EpiF32{t.wpart[l], fo, (long long)fi * fo, nullptr}, st, splits);
+    gemm_visit(fi, fo, B, LoadK{Xt, B, nullptr, fi, B}, LoadK{Dt, B, nullptr, fo, B},
+               EpiF32{t.wpart[l], fo, (long long)fi * fo, nullptr}, splits, go);
 }
 
 // one batch: the products, then the update. with_grads: the summed gradients also go to a->grad
@@ -1628,9 +1677,11 @@ void train_batch(ae_net* a, const uint16_t* y, const float* meta, const ae_train
 {
     const int weighting = cfg.weighting;
     const int in = a->in, hid = a->hid, lat = a->lat;
-    // forward; the epilogues also write the transposed activations the weight gradients read
-    gemm_auto(B, hid, in, LoadK{y, in, idx, B, in}, LoadK{a->wt[0], in, nullptr, hid, in},
-              EpiGelu{t.h1, hid, a->bias(0), t.a1, t.h1t, B}, st);
+    // forward; the epilogues also write the transposed activations the weight gradients read.
+    // Beside the first product, for the last weight gradient: the batch's input rows transposed
+    gemm_visit(B, hid, in, LoadK{y, in, idx, B, in}, LoadK{a->wt[0], in, nullptr, hid, in},
+               EpiGelu{t.h1, hid, a->bias(0), t.a1, t.h1t, B}, 1,
+               [&](const auto& w) { launch_works(w, TransposeWork{y, in, idx, B, in, t.yt}, st); });
     gemm_auto(B, lat, hid, LoadK{t.h1, hid, nullptr, B, hid}, LoadK{a->wt[1], hid, nullptr, lat, hid},
               EpiBF16T{t.zb, lat, a->bias(1), nullptr, t.zbt, B}, st);
     gemm_auto(B, hid, lat, LoadK{t.zb, lat, nullptr, B, lat}, LoadK{a->wt[2], lat, nullptr, hid, lat},
@@ -1648,21 +1699,17 @@ void train_batch(ae_net* a, const uint16_t* y, const float* meta, const ae_train
     const int bn4 = gemm_auto_bn(B, in);
     gemm_auto(B, in, hid, LoadK{t.h3, hid, nullptr, B, hid}, LoadK{a->wt[3], hid, nullptr, in, hid},
               EpiMse{a->bias(3), y, idx, in, t.w, t.wsum, t.d4, t.bpart[3], t.lossp, in / bn4, t.d4t, B}, st);
-    // backward: layer 4
-    weight_grad(a, 3, B, t.h3t, t.d4t, t, splits, st);
-    gemm_auto(B, hid, in, LoadK{t.d4, in, nullptr, B, in}, LoadK{a->wb[3], in, nullptr, hid, in},
-              EpiGeluBack{t.d3, t.a3, hid, t.bpart[2], t.d3t, B}, st);
-    // layer 3
-    weight_grad(a, 2, B, t.zbt, t.d3t, t, splits, st);
-    gemm_auto(B, lat, hid, LoadK{t.d3, hid, nullptr, B, hid}, LoadK{a->wb[2], hid, nullptr, lat, hid},
-              EpiBF16T{t.dz, lat, nullptr, t.bpart[1], t.dzt, B}, st);
-    // layer 2
-    weight_grad(a, 1, B, t.h1t, t.dzt, t, splits, st);
-    gemm_auto(B, hid, lat, LoadK{t.dz, lat, nullptr, B, lat}, LoadK{a->wb[1], lat, nullptr, hid, lat},
-              EpiGeluBack{t.d1, t.a1, hid, t.bpart[0], t.d1t, B}, st);
-    // layer 1: the batch's input rows, gathered and transposed
-    transpose_rows(y, in, idx, B, in, t.yt, st);
-    weight_grad(a, 0, B, t.yt, t.d1t, t, splits, st);
+    // backward: each layer's weight gradient beside the product that takes the delta on
+    auto backward = [&](int l, const uint16_t* Xt, const uint16_t* Dt, const uint16_t* d, const auto& epi) {
+        gemm_visit(B, a->fi[l], a->fo[l], LoadK{d, a->fo[l], nullptr, B, a->fo[l]},
+                   LoadK{a->wb[l], a->fo[l], nullptr, a->fi[l], a->fo[l]}, epi, 1, [&](const auto& w) {
+                       weight_grad(a, l, B, Xt, Dt, t, splits, [&](const auto& g) { launch_works(w, g, st); });
+                   });
+    };
+    backward(3, t.h3t, t.d4t, t.d4, EpiGeluBack{t.d3, t.a3, hid, t.bpart[2], t.d3t, B});
+    backward(2, t.zbt, t.d3t, t.d3, EpiBF16T{t.dz, lat, nullptr, t.bpart[1], t.dzt, B});
+    backward(1, t.h1t, t.dzt, t.dz, EpiGeluBack{t.d1, t.a1, hid, t.bpart[0], t.d1t, B});
+    weight_grad(a, 0, B, t.yt, t.d1t, t, splits, [&](const auto& g) { launch_work(g, st); });
     a->step += 1;
     UpdateArgs u{};
     int n = 0, nb = 0;
