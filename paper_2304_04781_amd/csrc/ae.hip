@@ -785,6 +785,7 @@ __global__ void __launch_bounds__(256) normalize_kernel(const float* __restrict_
 // order): the 512 rows (t, lz, ly) of the window are read as G float4 runs each,
 // G * 16 bytes contiguous, so a row of blocks is fetched in whole cache lines.
 // Thread i holds block i % G and rows i / G + (256 / G) m, m < 2 G.
+// y null: only (lo, r).
 template <int G>
 __global__ void __launch_bounds__(256) time_normalize_group_kernel(const float* __restrict__ e_win, int S, int ny,
                                                                   int nx, long long N, int By, int Bx, long long B,
@@ -827,12 +828,14 @@ __global__ void __launch_bounds__(256) time_normalize_group_kernel(const float* 
     const float rr = fmaxf(hi - lo, beta[0]);
     const float rinv = 1.0f / rr;
     uint16_t* yv = y + (v0 + g) * (TWIN * 64);
+    if (y) {
 #pragma unroll
-    for (int m = 0; m < NR; ++m) {
-        const int r = r0 + RS * m;
-        const uint2 o = make_uint2(f2bf2((v[m].x - lo) * rinv, (v[m].y - lo) * rinv),
-                                   f2bf2((v[m].z - lo) * rinv, (v[m].w - lo) * rinv));
-        *reinterpret_cast<uint2*>(yv + r * 4) = o;
+        for (int m = 0; m < NR; ++m) {
+            const int r = r0 + RS * m;
+            const uint2 o = make_uint2(f2bf2((v[m].x - lo) * rinv, (v[m].y - lo) * rinv),
+                                       f2bf2((v[m].z - lo) * rinv, (v[m].w - lo) * rinv));
+            *reinterpret_cast<uint2*>(yv + r * 4) = o;
+        }
     }
     if (threadIdx.x < G) {
         meta[(v0 + g) * 2] = lo;
@@ -1470,6 +1473,11 @@ void ae_time_encode(const ae_net* a, const TimeGrid& tg, const float* e_win, int
                     float* meta, hipStream_t st)
 {
     const long long M = tg.B * tg.S;
+    if (fused_supported(a->hid, a->lat) && time_encode_fused(M)) {
+        ae_time_normalize_rows(a, tg, e_win, nvalid, nullptr, M, nullptr, meta, st);
+        fused_time_encode(tg, e_win, nvalid, meta, a->wp1, a->bias(0), a->wt[1], a->bias(1), latent, st);
+        return;
+    }
     const size_t oh = align256(M * (size_t)a->in * 2);
     uint8_t* ws = (uint8_t*)workspace(a, align256(oh + M * (size_t)a->hid * 2), st);
     uint16_t* y = (uint16_t*)ws;
@@ -1487,6 +1495,10 @@ void ae_time_decode(const ae_net* a, const TimeGrid& tg, const uint16_t* latent,
     WV_REQUIRE(a->in == TWIN * 64, WV_EINVAL, "time compression needs an input width of 2048");
     WV_REQUIRE(nvalid >= 1 && nvalid <= TWIN, WV_EINVAL, "nvalid must lie in [1, 32]");
     const long long M = tg.B * tg.S;
+    if (fused_supported(a->hid, a->lat) && time_decode_fused(M)) {
+        fused_time_decode(tg, latent, meta, nvalid, a->wt[2], a->bias(2), a->wp4, a->bias(3), e_win, st);
+        return;
+    }
     uint16_t* h = (uint16_t*)workspace(a, align256(M * (size_t)a->hid * 2), st);
     gemm_auto((int)M, a->hid, a->lat, LoadK{latent, a->lat, nullptr, (int)M, a->lat},
               LoadK{a->wt[2], a->lat, nullptr, a->hid, a->lat}, EpiGelu{h, a->hid, a->bias(2), nullptr}, st);

@@ -50,6 +50,10 @@ struct EncArgs {
     // P patches of all sources: Ps per source, whose states are sstride floats apart
     long long P, N, Ps, sstride;
     int ny, nx, Py, Px;
+    // time vectors: state = the window [TWIN][S][N] (lstride = S N), whose levels from nvalid on
+    // repeat the last one before; P blocks of 4^3 cells, Ps per source; meta [P][2]
+    int nvalid;
+    long long lstride;
 };
 
 // first element of patch p's cells in the states, field 0
@@ -59,6 +63,15 @@ __device__ __forceinline__ long long patch_base(const A& a, long long p)
     const unsigned u = (unsigned)p, s = u / (unsigned)a.Ps, q = u % (unsigned)a.Ps;  // below 2^31 (fused_patches)
     const unsigned px = q % (unsigned)a.Px, t = q / (unsigned)a.Px, py = t % (unsigned)a.Py, pz = t / (unsigned)a.Py;
     return s * a.sstride + ((long long)(pz * 8) * a.ny + py * 8) * a.nx + px * 8;
+}
+
+// first element of block b's cells at the first level of a window of levels
+template <class A>
+__device__ __forceinline__ long long block_base(const A& a, long long b)
+{
+    const unsigned u = (unsigned)b, s = u / (unsigned)a.Ps, q = u % (unsigned)a.Ps;
+    const unsigned bx = q % (unsigned)a.Px, t = q / (unsigned)a.Px, by = t % (unsigned)a.Py, bz = t / (unsigned)a.Py;
+    return s * a.N + ((long long)(bz * 4) * a.ny + by * 4) * a.nx + bx * 4;
 }
 
 // e4m3 scale of a patch whose largest |latent| is m
@@ -149,7 +162,13 @@ constexpr int ENC_HLD = 64 + 8;  // bf16 row of a wave's hidden staging tile [16
 constexpr int ENC_ZLD = 32 + 4;  // float row of the latent partial sums [BM][ENC_ZLD]
 constexpr int ENC_R_BYTES = 8 * 16 * ENC_HLD * 2;  // the largest use of the shared region
 
-template <int L, int WD, int RD>
+//
+// TIME: the vectors of the time scheme (4^3 cells x 32 levels of e, one range each) in the same
+// way, from metadata known beforehand; only the second layer's sum differs, which runs on
+// from wave to wave through LDS: the order of one product over all 512 hidden units, which the
+// general path has. A window of 256^3 (262144 vectors, 2.1 GB of levels) takes 1019 us with the
+// pass over its ranges before; 1503 us with normalised vectors and hidden layer in memory.
+template <int L, int WD, int RD, bool TIME>
 __global__ void __launch_bounds__(NT) encode_kernel(const EncArgs a)
 {
     static_assert(L == 32, "two latent column tiles");
@@ -171,16 +190,19 @@ __global__ void __launch_bounds__(NT) encode_kernel(const EncArgs a)
     const long long pa = m0 + am;
     const bool a_ok = pa < a.P;
     long long abase = 0;
-    if (a_ok) abase = patch_base(a, pa) + aq * a.nx;
-    const float* rsrc = a.state + abase;
     const long long plane = (long long)a.ny * a.nx;
+    // (time: k-step kk is level kk / 2, z rows 2 (kk % 2) and the next; thread (am, aq) takes the
+    // rows 2 (aq % 2) and the next of z row aq / 2 of them)
+    if (a_ok) abase = TIME ? block_base(a, pa) + (aq >> 1) * plane + 2 * (aq & 1) * a.nx : patch_base(a, pa) + aq * a.nx;
+    const float* rsrc = a.state + abase;
     // k-step kk: field kk / 16, z level (kk % 16) / 2, y rows 4 (kk % 2) .. + 3. Steps past
     // the last reload the last one, so every step issues the same loads.
     auto load_raw = [&](int kk, float4(&d)[2]) {
         const int k = kk < 64 ? kk : 63;
-        const float* s = rsrc + ((k >> 4) * a.N + ((k & 15) >> 1) * plane + 4 * (k & 1) * a.nx);
+        const float* s = TIME ? rsrc + (min(k >> 1, a.nvalid - 1) * a.lstride + 2 * (k & 1) * plane)
+                              : rsrc + ((k >> 4) * a.N + ((k & 15) >> 1) * plane + 4 * (k & 1) * a.nx);
         d[0] = *reinterpret_cast<const float4*>(s);
-        d[1] = *reinterpret_cast<const float4*>(s + 4);
+        d[1] = *reinterpret_cast<const float4*>(TIME ? s + a.nx : s + 4);
     };
     // fragment-ordered W1: block (kk, hidden tile t) of 64 lanes x 8 values at ((kk * 32 + t) * 64) * 8;
     // wave w owns hidden tiles 4 w .. 4 w + 3
@@ -202,7 +224,12 @@ __global__ void __launch_bounds__(NT) encode_kernel(const EncArgs a)
     for (int q = 0; q < WD - 1; ++q) load_w(q, wb[q]);
 
     // thread (field aq, patch am) forms (lo, 1 / r): from the partials, or from the metadata
-    if (a.mm) {
+    if constexpr (TIME) {
+        if (aq == 0) {
+            const float2 m = a_ok ? *reinterpret_cast<const float2*>(a.meta + pa * 2) : make_float2(0.f, 1.f);
+            sLR[0][am] = make_float2(m.x, 1.0f / m.y);
+        }
+    } else if (a.mm) {
         sLR[aq][am] = enc_lo_rinv(a, pa, aq, true);
     } else {
         const float2 m = a_ok ? *reinterpret_cast<const float2*>(a.meta + pa * 8 + 2 * aq) : make_float2(0.f, 1.f);
@@ -214,7 +241,7 @@ __global__ void __launch_bounds__(NT) encode_kernel(const EncArgs a)
     const uint32_t amask = a_ok ? 0xFFFFFFFFu : 0u;
     uint16_t* const a_dst = sR + ((am >> 4) * 64 + (am & 15) + 16 * aq) * 8;
     auto normalize = [&](int kk, const float4(&x)[2], int buf) {
-        const int f = (kk < 64 ? kk : 63) >> 4;
+        const int f = TIME ? 0 : (kk < 64 ? kk : 63) >> 4;
         const float2 lr = sLR[f][am];
         const float l = lr.x, ri = lr.y;
         uint4 w;
@@ -292,6 +319,7 @@ __global__ void __launch_bounds__(NT) encode_kernel(const EncArgs a)
             w2f[ks][jj] = *reinterpret_cast<const bf16x8*>(a.w2t + (long long)(jj * 16 + fr) * HID + wave * 64 +
                                                            ks * 32 + fq);
     f32x4 zp[TI][2];
+    bf16x8 ht[TI][2];  // TIME: the GELU outputs as A fragments
 #pragma unroll
     for (int i = 0; i < TI; ++i) {
 #pragma unroll
@@ -305,6 +333,10 @@ __global__ void __launch_bounds__(NT) encode_kernel(const EncArgs a)
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             const bf16x8 ah = *reinterpret_cast<const bf16x8*>(sHw + fr * ENC_HLD + ks * 32 + fq);
+            if (TIME) {
+                ht[i][ks] = ah;
+                continue;
+            }
 #pragma unroll
             for (int jj = 0; jj < 2; ++jj)
                 zp[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, w2f[ks][jj], zp[i][jj], 0, 0, 0);
@@ -312,7 +344,7 @@ __global__ void __launch_bounds__(NT) encode_kernel(const EncArgs a)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    // the partial blocks summed in wave order: ((z_0 + z_1) + z_2) + ... in a [BM][ENC_ZLD] area
+    // the partial blocks summed in wave order (TIME: the sum itself taken on): ((z_0 + z_1) + z_2) + ... in a [BM][ENC_ZLD] area
     float* sZ = reinterpret_cast<float*>(sR);
     __syncthreads();  // every wave is done with its staging area
     for (int w = 0; w < 8; ++w) {
@@ -320,12 +352,25 @@ __global__ void __launch_bounds__(NT) encode_kernel(const EncArgs a)
 #pragma unroll
             for (int i = 0; i < TI; ++i)
 #pragma unroll
-                for (int jj = 0; jj < 2; ++jj)
+                for (int jj = 0; jj < 2; ++jj) {
+                    if constexpr (TIME) {
+                        f32x4 t = f32x4{0.f, 0.f, 0.f, 0.f};
+                        if (w > 0)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) t[r] = sZ[(i * 16 + cr + r) * ENC_ZLD + jj * 16 + fr];
+#pragma unroll
+                        for (int ks = 0; ks < 2; ++ks)
+                            t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ht[i][ks], w2f[ks][jj], t, 0, 0, 0);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) sZ[(i * 16 + cr + r) * ENC_ZLD + jj * 16 + fr] = t[r];
+                        continue;
+                    }
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         float* z = sZ + (i * 16 + cr + r) * ENC_ZLD + jj * 16 + fr;
                         *z = w == 0 ? zp[i][jj][r] : *z + zp[i][jj][r];
                     }
+                }
         }
         __syncthreads();
     }
@@ -767,6 +812,128 @@ __global__ void __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(WV_
         }
 }
 
+struct TimeDecArgs {
+    const uint16_t* z;    // [M][L] bf16
+    const float* meta;    // [M][2]
+    const uint16_t* w3t;  // [HID][L]
+    const float* b3;
+    const uint16_t* w4p;  // W4^T [2048][HID] in fragment order
+    const float* b4;      // [2048]
+    float* win;           // [TWIN][S][N]
+    long long M, Ps, N, lstride;
+    int ny, nx, Py, Px, nvalid;
+};
+
+// Decode of time vectors: the levels t < nvalid of BM blocks per work-group of eight waves. The
+// hidden layer is formed once, in LDS, and multiplied by W4 a fourth (8 levels) at a time;
+// wave w owns the levels t % 8 = w. Two work-groups share a CU, so that one multiplies while the
+// other stores; bound by that overlap: stores 0.34 ms, W4 from L2 (2 MiB a work-group) and MFMA
+// 0.22 each at 256^3. A window of 256^3 takes 926 us; 1360 with the hidden layer in memory. 128
+// blocks per work-group, half the reads of W4 but one to a CU: 1115.
+template <int L, int BMT>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
+    time_decode_kernel(const TimeDecArgs a)
+{
+    static_assert(L == KB, "one k-step in layer 3");
+    constexpr int IT = BMT / 16, OPW = 64, JT = OPW / 16, NK = HID / KB, PFD = 2;
+    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+    uint16_t(*sH)[HID + HPAD] = reinterpret_cast<uint16_t(*)[HID + HPAD]>(smem);
+    long long* sBase = reinterpret_cast<long long*>(smem + BMT * (HID + HPAD));
+    float2* sLR = reinterpret_cast<float2*>(sBase + BMT);
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int fr = lane & 15, fq = (lane >> 4) * 8, cr = (lane >> 4) * 4, q = lane >> 4;
+    const long long m0 = (long long)blockIdx.x * BMT;
+    if (tid < BMT) {
+        const bool ok = m0 + tid < a.M;
+        sBase[tid] = ok ? block_base(a, m0 + tid) : 0;
+        sLR[tid] = ok ? *reinterpret_cast<const float2*>(a.meta + (m0 + tid) * 2) : make_float2(0.f, 0.f);
+    }
+    const uint16_t* wb = a.w4p + ((long long)(wave * JT) * 64 + lane) * 8;  // + 512 * 32 per fourth
+    {
+        f32x4 acc[IT][JT];
+        bf16x8 bw[JT];
+#pragma unroll
+        for (int j = 0; j < JT; ++j)
+            bw[j] = *reinterpret_cast<const bf16x8*>(a.w3t + (long long)(wave * OPW + j * 16 + fr) * L + fq);
+#pragma unroll
+        for (int i = 0; i < IT; ++i) {
+            const long long p = m0 + i * 16 + fr;
+            const uint4 zero = make_uint4(0, 0, 0, 0);
+            const uint4 zr = p < a.M ? *reinterpret_cast<const uint4*>(a.z + p * L + fq) : zero;
+#pragma unroll
+            for (int j = 0; j < JT; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, zr), bw[j],
+                                                                    f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        }
+#pragma unroll
+        for (int j = 0; j < JT; ++j) {
+            const int n = wave * OPW + j * 16 + fr;
+            const float bias = a.b3[n];
+#pragma unroll
+            for (int i = 0; i < IT; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sH[i * 16 + cr + r][n] = f2bf(gelu(acc[i][j][r] + bias));
+        }
+    }
+    __syncthreads();
+    // A row m of tile i is block 16 i + 4 (m % 4) + m / 4: the C rows held for one r by the four lane
+    // groups are four x-adjacent blocks, and the four r of a wave 256 contiguous bytes of a row
+    const int arow = 4 * (fr & 3) + (fr >> 2);
+    for (int f = 0; 8 * f < a.nvalid; ++f) {
+        asm volatile("" ::: "memory");  // the hidden layer is read again, not kept in registers
+        const uint16_t* wf = wb + (long long)f * (32 * 512);
+        bf16x8 bq[PFD + 1][JT];
+#pragma unroll
+        for (int u = 0; u < PFD; ++u)
+#pragma unroll
+            for (int j = 0; j < JT; ++j)
+                bq[u][j] = *reinterpret_cast<const bf16x8*>(wf + (long long)u * (128 * 512) + j * 512);
+        f32x4 acc[IT][JT];
+#pragma unroll
+        for (int i = 0; i < IT; ++i)
+#pragma unroll
+            for (int j = 0; j < JT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk) {
+            if (kk + PFD < NK)
+#pragma unroll
+                for (int j = 0; j < JT; ++j)
+                    bq[(kk + PFD) % (PFD + 1)][j] =
+                        *reinterpret_cast<const bf16x8*>(wf + (long long)(kk + PFD) * (128 * 512) + j * 512);
+            bf16x8 af[IT];
+#pragma unroll
+            for (int i = 0; i < IT; ++i) af[i] = *reinterpret_cast<const bf16x8*>(&sH[i * 16 + arow][kk * KB + fq]);
+#pragma unroll
+            for (int i = 0; i < IT; ++i)
+#pragma unroll
+                for (int j = 0; j < JT; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bq[kk % (PFD + 1)][j], acc[i][j], 0, 0, 0);
+        }
+        // columns 64 t + 16 j + fr of level t = 8 f + wave: z row j, y row fr / 4, cell fr % 4
+        const int t = 8 * f + wave;
+        if (t >= a.nvalid) continue;
+        float* out = a.win + t * a.lstride + ((fr >> 2) * a.nx + (fr & 3));
+        const long long plane = (long long)a.ny * a.nx;
+        float bias[JT];
+#pragma unroll
+        for (int j = 0; j < JT; ++j) bias[j] = a.b4[t * 64 + j * 16 + fr];
+#pragma unroll
+        for (int i = 0; i < IT; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                asm volatile("" ::: "memory");  // the rows' tables are read as they are used
+                const int pl = i * 16 + 4 * r + q;
+                if (m0 + pl >= a.M) continue;
+                float* o = out + sBase[pl];
+                const float2 lr = sLR[pl];
+#pragma unroll
+                for (int j = 0; j < JT; ++j)
+                    // not read again before the window's gigabytes have passed the caches
+                    __builtin_nontemporal_store(lr.x + lr.y * (acc[i][j][r] + bias[j]), o + j * plane);
+            }
+    }
+}
+
 __global__ void pack_kernel(const uint16_t* __restrict__ w, int rows, int K, uint16_t* __restrict__ out)
 {
     const long long c = blockIdx.x * (long long)blockDim.x + threadIdx.x;  // 8-value chunk
@@ -842,7 +1009,7 @@ void fused_encode(EncPlan plan, const PatchGrid& pg, int nsrc, const float* stat
     WV_REQUIRE(zbf || (codes && scale), WV_EINVAL, "encode: null latent buffer");
     const long long N = (long long)pg.nz * pg.ny * pg.nx;
     const EncArgs a{state, meta, meta16, mm, H, beta, w1p, b1, w2t, b2, zbf, codes, scale, fused_patches(pg, nsrc), N, pg.P, 4 * N,
-                    pg.ny, pg.nx, pg.ny / 8, pg.nx / 8};
+                    pg.ny, pg.nx, pg.ny / 8, pg.nx / 8, 0, 0};
     switch (plan) {
     case ENC_FEW_SPLIT:
         WV_REQUIRE(zpart, WV_EINVAL, "encode: null work buffer");
@@ -853,7 +1020,7 @@ void fused_encode(EncPlan plan, const PatchGrid& pg, int nsrc, const float* stat
     case ENC_FEW: launch_few<1, 4>(a, nullptr, st); break;
     case ENC_FEW_PAIR: launch_few<2, 4>(a, nullptr, st); break;
     default:
-        hipLaunchKernelGGL((encode_kernel<32, ENC_WD, ENC_RD>), dim3((unsigned)((a.P + BM - 1) / BM)), dim3(NT), 0, st,
+        hipLaunchKernelGGL((encode_kernel<32, ENC_WD, ENC_RD, false>), dim3((unsigned)((a.P + BM - 1) / BM)), dim3(NT), 0, st,
                            a);
     }
     WV_HIP(hipGetLastError());
@@ -904,6 +1071,38 @@ void fused_decode(const PatchGrid& pg, int nsrc, const uint16_t* z, const uint8_
     if (bm == 16) launch_decode<16>(a, nsrc, 0, st);
     else if (bm == 32) launch_decode<32>(a, nsrc, 0, st);
     else launch_decode<DEC_BM>(a, nsrc, grid, st);
+}
+
+// vectors from which the fused kernels take over
+// (general / fused us per window: encode 77 / 77 at 8000, 104 / 76 at 13824, 1503 / 1019 at 262144;
+// decode 49 / 67 at 8000, 78 / 73 at 13824, 1360 / 926 at 262144: a fused work-group takes its
+// whole march, 60 to 75 us, however few there are)
+constexpr long long TIME_ENC_MIN = 8192, TIME_DEC_MIN = 12288;
+bool time_encode_fused(long long M) { return M >= TIME_ENC_MIN && M < (1LL << 31); }
+bool time_decode_fused(long long M) { return M >= TIME_DEC_MIN && M < (1LL << 31); }
+
+void fused_time_encode(const TimeGrid& tg, const float* e_win, int nvalid, const float* meta, const uint16_t* w1p,
+                       const float* b1, const uint16_t* w2t, const float* b2, uint16_t* z, hipStream_t st)
+{
+    const long long M = tg.B * tg.S, N = (long long)tg.nz * tg.ny * tg.nx;
+    const EncArgs a{e_win, meta, nullptr, nullptr, 0, nullptr, w1p, b1, w2t, b2, z, nullptr, nullptr, M, N, tg.B, N,
+                    tg.ny, tg.nx, tg.ny / 4, tg.nx / 4, nvalid, tg.S * N};
+    hipLaunchKernelGGL((encode_kernel<32, ENC_WD, ENC_RD, true>), dim3((unsigned)((M + BM - 1) / BM)), dim3(NT), 0, st,
+                       a);
+    WV_HIP(hipGetLastError());
+}
+
+void fused_time_decode(const TimeGrid& tg, const uint16_t* z, const float* meta, int nvalid, const uint16_t* w3t,
+                       const float* b3, const uint16_t* w4p, const float* b4, float* e_win, hipStream_t st)
+{
+    constexpr int BMT = 64;
+    const long long M = tg.B * tg.S, N = (long long)tg.nz * tg.ny * tg.nx;
+    const size_t sm = (size_t)BMT * (HID + HPAD) * 2 + (size_t)BMT * 16;
+    allow_smem(time_decode_kernel<32, BMT>, sm);
+    const TimeDecArgs a{z, meta, w3t, b3, w4p, b4, e_win, M, tg.B, N, tg.S * N, tg.ny, tg.nx, tg.ny / 4, tg.nx / 4,
+                        nvalid};
+    hipLaunchKernelGGL((time_decode_kernel<32, BMT>), dim3((unsigned)((M + BMT - 1) / BMT)), dim3(512), sm, st, a);
+    WV_HIP(hipGetLastError());
 }
 
 }  // namespace wv

@@ -109,6 +109,14 @@ void fused_encode(EncPlan plan, const PatchGrid& pg, int nsrc, const float* stat
 // their exact values.
 // grid > 0: the decode is queued as launches of at most grid work-groups, one after the
 // other on st, so it holds fewer CUs at a time (0: one launch).
+// Time vectors with the fused kernels: latents from the window and its metadata, and back.
+// Bit for bit the general path's. time_*_fused: they are the faster ones for M vectors
+bool time_encode_fused(long long M);
+bool time_decode_fused(long long M);
+void fused_time_encode(const TimeGrid& tg, const float* e_win, int nvalid, const float* meta, const uint16_t* w1p,
+                       const float* b1, const uint16_t* w2t, const float* b2, uint16_t* z, hipStream_t st);
+void fused_time_decode(const TimeGrid& tg, const uint16_t* z, const float* meta, int nvalid, const uint16_t* w3t,
+                       const float* b3, const uint16_t* w4p, const float* b4, float* e_win, hipStream_t st);
 void fused_decode(const PatchGrid& pg, int nsrc, const uint16_t* z, const uint8_t* codes, const float* scale,
                   const float* meta, const uint16_t* w3t, const float* b3, const uint16_t* w4p, const float* b4, int f,
                   float* state, long long sstride, hipStream_t st, const ExcPatches* exc, const uint16_t* meta16,
