@@ -2352,15 +2352,15 @@ int prior_solve(wv_ctx* c, const float* b, float* x, double rtol, int maxit, dou
             c->prior_theta[2] / h2);
     WV_REQUIRE(!p.wide || ((uintptr_t)x | (uintptr_t)c->pvec) % 16 == 0, WV_EINVAL, "misaligned work vectors");
     if (!c->cg_part) {
-        c->cg_part = dev_alloc<double>(2 * (size_t)p.nb_r + p.nb_d);
+        c->cg_part = dev_alloc<double>(3 * (size_t)p.nb);
         c->cg_state = dev_alloc<CgState>(1);
     }
-    float* const dir[2] = {c->pvec + 2 * N, c->pvec + 4 * N};
-    double* const part[2] = {c->cg_part, c->cg_part + p.nb_r};
+    float* const dir[2] = {c->pvec + 2 * N, c->pvec + 3 * N};
+    double* const part[2] = {c->cg_part, c->cg_part + p.nb};
     p.x = x;
     p.r = c->pvec + N;
-    p.Ad = c->pvec + 3 * N;
-    p.part_d = c->cg_part + 2 * p.nb_r;
+    p.Ad = N < CG_AGAIN_MIN ? c->pvec + 4 * N : nullptr;
+    p.part_d = c->cg_part + 2 * p.nb;
     p.st = c->cg_state;
     p.rtol = rtol;
     p.part_r = part[0];

@@ -108,10 +108,13 @@ __global__ void dot_finalize(const double* __restrict__ partial, int n, double* 
 
 // ---- conjugate gradients on A x = b with the scalars on the device ---------------------
 // One iteration is two launches, each streaming its vectors once:
-//   direction: d' = r + beta d (into the other direction buffer), A d' and its dot with d';
+//   direction: d' = r + beta d (into the other direction buffer) and the dot of A d' with d';
 //   update:    x += alpha d', r -= alpha A d', and r.r.
-// 40 B per cell and iteration (a launch per vector operation moved 60 and cost two host
-// round trips; 256^3: 260 us per iteration, 125 now). Every work-group sums the partial dots of
+// A d' is stored by the first for the second on small grids (40 B per cell and iteration, mostly
+// from the caches), formed again on large ones (32 B). 256^3: 260 us per iteration with a launch per
+// vector operation (60 B and two host round trips), 125 with A d' stored, 86 now, 6.2 TB/s of
+// its 537 MB, part of it from the Infinity Cache: on large grids the update visits the grid
+// backwards, so that each launch meets what the one before left. Every work-group sums the partial dots of
 // the launch before, in a fixed order, so no launch of its own reduces them; work-group 0
 // keeps the scalars. Once converged, the launches already queued return at once.
 
@@ -173,16 +176,16 @@ __global__ void __launch_bounds__(DB) cg_check_kernel(const CgParams c)
 {
     if (c.st->done) return;
     float beta;
-    (void)cg_scalars(c, block_total(c.part_r, c.nb_r), &beta);
+    (void)cg_scalars(c, block_total(c.part_r, c.nb), &beta);
 }
 
 // A work-group holds CG_TY rows of CG_TX lanes (VX cells each) and marches over kc levels; d'
-// of the level sits in LDS with a one-cell ring (whose d' the ring's threads form anew), the
-// levels below and above in registers. The next level's r and d are loaded while one is
+// of the level sits in LDS with a one-cell ring (whose d' the ring's threads load, or form anew), the
+// levels below and above in registers. The next level's vectors are loaded while one is
 // computed. Boundary faces carry no flux.
 constexpr int CG_TX = 32, CG_TY = 8;
-template <int VX>
-__global__ void __launch_bounds__(DB) cg_direction_kernel(const CgParams c)
+template <int VX, bool UPDATE>
+__global__ void __launch_bounds__(DB) cg_step_kernel(const CgParams c)
 {
     // the products fused with an addition are written out, as in prior_kernel and axpby_kernel
 #pragma clang fp contract(off)
@@ -190,12 +193,26 @@ __global__ void __launch_bounds__(DB) cg_direction_kernel(const CgParams c)
     constexpr int W = CG_TX * VX;
     __shared__ __attribute__((aligned(16))) float sD[2][CG_TY + 2][W + 8];  // cell x at column x + 4
     if (c.st->done) return;
-    float beta;
-    if (!cg_scalars(c, block_total(c.part_r, c.nb_r), &beta)) return;
+    float beta = 0.f, alpha = 0.f, nalpha = 0.f;
+    if constexpr (UPDATE) {
+        const double a = c.st->rr[c.it & 1] / block_total(c.part_d, c.nb);
+        alpha = (float)a;
+        nalpha = (float)-a;
+    } else {
+        if (!cg_scalars(c, block_total(c.part_r, c.nb), &beta)) return;
+    }
 
+    // each XCD takes a contiguous range of the tiles, whose rings overlap
+    int b = blockIdx.x;
+    {
+        const int x = b & 7, q = c.nb >> 3, r = c.nb & 7, n = q + (x < r);
+        b >>= 3;
+        if (UPDATE) b = n - 1 - b;
+        b += x * q + min(x, r);
+    }
     const int tx = threadIdx.x % CG_TX, ty = threadIdx.x / CG_TX;
-    const int txx = blockIdx.x % c.tiles_x, tyy = (blockIdx.x / c.tiles_x) % c.tiles_y;
-    const int cz = blockIdx.x / (c.tiles_x * c.tiles_y);
+    const int txx = b % c.tiles_x, tyy = (b / c.tiles_x) % c.tiles_y;
+    const int cz = b / (c.tiles_x * c.tiles_y);
     const int i = txx * W + tx * VX, j = tyy * CG_TY + ty;
     const bool inside = i < c.nx && j < c.ny;  // VX divides nx
     const int k0 = cz * c.kc, k1 = min(c.nz, k0 + c.kc);
@@ -210,105 +227,131 @@ __global__ void __launch_bounds__(DB) cg_direction_kernel(const CgParams c)
     const bool has_col = inside && (col_lo ? i > 0 : col_hi && i + VX < c.nx);
     const long long ecell = has_col ? (long long)j * c.nx + (col_lo ? i - 1 : i + VX) : cell;
     const bool first = c.it == 0;
-    auto dir = [&](float r, float d) { return first ? r : r + beta * d; };
-    struct Lev {
-        float r[VX], d[VX];
+    struct Vec {
+        float v[VX];
     };
-    auto load = [&](long long at, Lev& v) {
+    auto ld = [&](const float* p, long long at) {
+        Vec t;
         if constexpr (VX == 4) {
-            const float4 a = *reinterpret_cast<const float4*>(c.r + at), b = *reinterpret_cast<const float4*>(c.d_in + at);
-            v.r[0] = a.x; v.r[1] = a.y; v.r[2] = a.z; v.r[3] = a.w;
-            v.d[0] = b.x; v.d[1] = b.y; v.d[2] = b.z; v.d[3] = b.w;
+            const float4 a = *reinterpret_cast<const float4*>(p + at);
+            t.v[0] = a.x; t.v[1] = a.y; t.v[2] = a.z; t.v[3] = a.w;
         } else {
-            v.r[0] = c.r[at];
-            v.d[0] = c.d_in[at];
+            t.v[0] = p[at];
         }
+        return t;
     };
-    float lo[VX], cur[VX];
-    Lev nxt, row;
-    float er, ed;
-    {
-        Lev a, b;
-        load(cell + (long long)max(k0 - 1, 0) * plane, a);
-        load(cell + (long long)k0 * plane, b);
-        load(cell + (long long)min(k0 + 1, c.nz - 1) * plane, nxt);
-        load(rcell + (long long)k0 * plane, row);
-        er = c.r[ecell + (long long)k0 * plane];
-        ed = c.d_in[ecell + (long long)k0 * plane];
+    auto stv = [&](float* p, long long at, const Vec& t) {
+        if constexpr (VX == 4)
+            *reinterpret_cast<float4*>(p + at) = make_float4(t.v[0], t.v[1], t.v[2], t.v[3]);
+        else
+            p[at] = t.v[0];
+    };
+    // what d' is formed from: r and d, or (UPDATE) itself
+    const float* const dsrc = UPDATE ? c.d_out : c.d_in;
+    struct Lev {
+        Vec r, d;
+    };
+    auto load = [&](long long at) {
+        Lev l{};
+        if (!UPDATE) l.r = ld(c.r, at);
+        l.d = ld(dsrc, at);
+        return l;
+    };
+    auto dir1 = [&](float r, float d) { return UPDATE ? d : first ? r : r + beta * d; };
+    auto dir = [&](const Lev& l) {
+        Vec t;
 #pragma unroll
-        for (int u = 0; u < VX; ++u) {
-            lo[u] = dir(a.r[u], a.d[u]);
-            cur[u] = dir(b.r[u], b.d[u]);
-        }
+        for (int u = 0; u < VX; ++u) t.v[u] = dir1(l.r.v[u], l.d.v[u]);
+        return t;
+    };
+    const long long at0 = (long long)k0 * plane;
+    Vec lo = dir(load(cell + (long long)max(k0 - 1, 0) * plane)), cur = dir(load(cell + at0));
+    Lev nxt = load(cell + (long long)min(k0 + 1, c.nz - 1) * plane), row = load(rcell + at0);
+    float er = UPDATE ? 0.f : c.r[ecell + at0], ed = dsrc[ecell + at0];
+    Vec xv{}, rv{};
+    if (UPDATE) {
+        xv = ld(c.x, cell + at0);
+        rv = ld(c.r, cell + at0);
     }
     double acc = 0.0;
     for (int k = k0; k < k1; ++k) {
         float(*s)[W + 8] = sD[k & 1];
-        float hi[VX];
+        const Vec hi = dir(nxt);
 #pragma unroll
-        for (int u = 0; u < VX; ++u) {
-            hi[u] = dir(nxt.r[u], nxt.d[u]);
-            s[ty + 1][tx * VX + u + 4] = cur[u];
-        }
+        for (int u = 0; u < VX; ++u) s[ty + 1][tx * VX + u + 4] = cur.v[u];
         if (row_lo || row_hi) {
             const int y = row_lo ? 0 : CG_TY + 1;
+            const Vec t = dir(row);
 #pragma unroll
-            for (int u = 0; u < VX; ++u) s[y][tx * VX + u + 4] = dir(row.r[u], row.d[u]);
+            for (int u = 0; u < VX; ++u) s[y][tx * VX + u + 4] = t.v[u];
         }
-        if (col_lo || col_hi) s[ty + 1][col_lo ? 3 : W + 4] = dir(er, ed);
+        if (col_lo || col_hi) s[ty + 1][col_lo ? 3 : W + 4] = dir1(er, ed);
         __syncthreads();  // the other buffer serves the next level: one barrier per level
         const long long at = (long long)k * plane;
+        Vec x = xv, r = rv, out;
         if (k + 1 < k1) {
-            load(cell + (long long)min(k + 2, c.nz - 1) * plane, nxt);
-            load(rcell + at + plane, row);
-            er = c.r[ecell + at + plane];
-            ed = c.d_in[ecell + at + plane];
-        }
-        float out[VX];
-#pragma unroll
-        for (int u = 0; u < VX; ++u) {
-            const int x = tx * VX + u + 4;
-            const float w = cur[u];
-            float flux = 0.f;
-            if (k > 0) flux = __builtin_fmaf(c.cz, lo[u] - w, flux);
-            if (k < c.nz - 1) flux = __builtin_fmaf(c.cz, hi[u] - w, flux);
-            if (j > 0) flux = __builtin_fmaf(c.cy, s[ty][x] - w, flux);
-            if (j < c.ny - 1) flux = __builtin_fmaf(c.cy, s[ty + 2][x] - w, flux);
-            if (i + u > 0) flux = __builtin_fmaf(c.cx, s[ty + 1][x - 1] - w, flux);
-            if (i + u < c.nx - 1) flux = __builtin_fmaf(c.cx, s[ty + 1][x + 1] - w, flux);
-            out[u] = c.alpha * (w - flux);
-            if (inside) acc = fma((double)w, (double)out[u], acc);
-        }
-        if (inside) {
-            if constexpr (VX == 4) {
-                *reinterpret_cast<float4*>(c.d_out + cell + at) = make_float4(cur[0], cur[1], cur[2], cur[3]);
-                *reinterpret_cast<float4*>(c.Ad + cell + at) = make_float4(out[0], out[1], out[2], out[3]);
-            } else {
-                c.d_out[cell + at] = cur[0];
-                c.Ad[cell + at] = out[0];
+            nxt = load(cell + (long long)min(k + 2, c.nz - 1) * plane);
+            row = load(rcell + at + plane);
+            if (!UPDATE) er = c.r[ecell + at + plane];
+            ed = dsrc[ecell + at + plane];
+            if (UPDATE) {
+                xv = ld(c.x, cell + at + plane);
+                rv = ld(c.r, cell + at + plane);
             }
         }
 #pragma unroll
         for (int u = 0; u < VX; ++u) {
-            lo[u] = cur[u];
-            cur[u] = hi[u];
+            const int q = tx * VX + u + 4;
+            const float w = cur.v[u];
+            float flux = 0.f;
+            if (k > 0) flux = __builtin_fmaf(c.cz, lo.v[u] - w, flux);
+            if (k < c.nz - 1) flux = __builtin_fmaf(c.cz, hi.v[u] - w, flux);
+            if (j > 0) flux = __builtin_fmaf(c.cy, s[ty][q] - w, flux);
+            if (j < c.ny - 1) flux = __builtin_fmaf(c.cy, s[ty + 2][q] - w, flux);
+            if (i + u > 0) flux = __builtin_fmaf(c.cx, s[ty + 1][q - 1] - w, flux);
+            if (i + u < c.nx - 1) flux = __builtin_fmaf(c.cx, s[ty + 1][q + 1] - w, flux);
+            const float Ad = c.alpha * (w - flux);
+            out.v[u] = Ad;
+            if constexpr (UPDATE) {
+                x.v[u] = __builtin_fmaf(alpha, w, x.v[u]);
+                r.v[u] = __builtin_fmaf(nalpha, Ad, r.v[u]);
+                if (inside) acc = fma((double)r.v[u], (double)r.v[u], acc);
+            } else {
+                if (inside) acc = fma((double)w, (double)Ad, acc);
+            }
         }
+        if (inside) {
+            if constexpr (UPDATE) {
+                stv(c.x, cell + at, x);
+                stv(c.r, cell + at, r);
+            } else {
+                stv(c.d_out, cell + at, cur);
+                if (c.Ad) stv(c.Ad, cell + at, out);
+            }
+        }
+        lo = cur;
+        cur = hi;
     }
     const double t = dblock_sum(acc);
-    if (threadIdx.x == 0) c.part_d[blockIdx.x] = t;
+    if (threadIdx.x == 0) (UPDATE ? c.part_next : c.part_d)[b] = t;
 }
 
+// the update with A d' stored by the direction launch
 template <int VX>
 __global__ void __launch_bounds__(DB) cg_update_kernel(const CgParams c)
 {
 #pragma clang fp contract(off)
     if (c.st->done) return;
-    const double dAd = block_total(c.part_d, c.nb_d);
+    const double dAd = block_total(c.part_d, c.nb);
     const double a = c.st->rr[c.it & 1] / dAd;
     const float alpha = (float)a, nalpha = (float)-a;
     double acc = 0.0;
+    // each XCD streams the part of the grid whose tiles it takes in the direction launch, as
+    // nearly as a contiguous eighth is that: small grids stay in its L2
     const long long n = c.n / VX;
-    for (long long q = blockIdx.x * (long long)DB + threadIdx.x; q < n; q += (long long)gridDim.x * DB) {
+    const int xcd = min(8, c.nb), x8 = blockIdx.x % xcd, on = c.nb / xcd + (x8 < c.nb % xcd);
+    const long long q1 = n * (x8 + 1) / xcd;
+    for (long long q = n * x8 / xcd + (blockIdx.x / xcd) * (long long)DB + threadIdx.x; q < q1; q += (long long)on * DB) {
         float x[VX], r[VX], d[VX], Ad[VX];
         if constexpr (VX == 4) {
             const float4 vx = reinterpret_cast<const float4*>(c.x)[q], vr = reinterpret_cast<const float4*>(c.r)[q];
@@ -390,24 +433,24 @@ void cg_plan(CgParams& c, int nz, int ny, int nx, double alpha, double cz, doubl
     const long long tiles = (long long)c.tiles_x * c.tiles_y;
     const int chunks = (int)std::max<long long>(1, std::min<long long>(nz, CG_BLOCKS / tiles));
     c.kc = (nz + chunks - 1) / chunks;
-    c.nb_d = (int)(tiles * ((nz + c.kc - 1) / c.kc));
-    c.nb_r = (int)std::max<long long>(1, std::min<long long>(CG_BLOCKS, (c.n + 4 * DB - 1) / (4 * DB)));
+    c.nb = (int)(tiles * ((nz + c.kc - 1) / c.kc));
 }
 
 void launch_cg_init(const CgParams& c, const float* b, hipStream_t st)
 {
-    hipLaunchKernelGGL(cg_init_kernel, dim3(c.nb_r), dim3(DB), 0, st, b, c.x, c.r, c.n, c.part_r, c.st);
+    hipLaunchKernelGGL(cg_init_kernel, dim3(c.nb), dim3(DB), 0, st, b, c.x, c.r, c.n, c.part_r, c.st);
     WV_HIP(hipGetLastError());
 }
 
 void launch_cg_iteration(const CgParams& c, hipStream_t st)
 {
+    const auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(c.nb), dim3(DB), 0, st, c); };
     if (c.wide) {
-        hipLaunchKernelGGL(cg_direction_kernel<4>, dim3(c.nb_d), dim3(DB), 0, st, c);
-        hipLaunchKernelGGL(cg_update_kernel<4>, dim3(c.nb_r), dim3(DB), 0, st, c);
+        go(cg_step_kernel<4, false>);
+        c.Ad ? go(cg_update_kernel<4>) : go(cg_step_kernel<4, true>);
     } else {
-        hipLaunchKernelGGL(cg_direction_kernel<1>, dim3(c.nb_d), dim3(DB), 0, st, c);
-        hipLaunchKernelGGL(cg_update_kernel<1>, dim3(c.nb_r), dim3(DB), 0, st, c);
+        go(cg_step_kernel<1, false>);
+        c.Ad ? go(cg_update_kernel<1>) : go(cg_step_kernel<1, true>);
     }
     WV_HIP(hipGetLastError());
 }

@@ -226,6 +226,10 @@ struct CgState {
     double rel;    // |r| / |b| at the start of iteration it
     int it, done;
 };
+// cells from which the update forms A d' again instead of reading it: below, the vectors stay in
+// the caches and the sums cost more than the reads (ms per draw stored / again: 131 x 118 x 101 1.73 /
+// 2.05, 160^3 2.99 / 3.08, 200^3 4.67 / 4.50, 256^3 14.5 / 10.3)
+constexpr long long CG_AGAIN_MIN = 3LL << 21;
 constexpr int CG_BLOCKS = 1024;  // work-groups aimed at per launch
 struct CgParams {
     int nz, ny, nx;
@@ -233,8 +237,9 @@ struct CgParams {
     float alpha, cz, cy, cx;
     int tiles_x, tiles_y, kc;
     bool wide;               // four cells per lane (nx divisible by 4)
-    int nb_d, nb_r;          // work-groups of the direction and the update launch
-    float *x, *r, *Ad;
+    int nb;                  // work-groups of either launch
+    float *x, *r;
+    float* Ad;               // A d' of the iteration, or null: the update forms it again
     const float* d_in;       // the direction before this iteration, and this one's
     float* d_out;
     double *part_d, *part_r, *part_next;  // partials of d.Ad, of r.r, and of the next r.r

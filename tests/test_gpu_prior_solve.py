@@ -1,6 +1,6 @@
 """The elliptic solve behind prior draws and the prior preconditioner, over the shapes where
 its launches differ (four cells or one per lane, ragged tiles, one or many levels per chunk,
-2D): the residual of the returned draw in float64, the iteration limit, and repeatability.
+2D, products stored or formed twice): the residual of the returned draw in float64, the iteration limit, and repeatability.
 The float32 recurrence's residual (1e-6) is off the true one by the rounding of the residual
 updates, about sqrt(iterations) x 61 x 6e-8 (61: the operator's largest row sum at theta /
 dx^2 = 5): 2e-5 bounds it."""
@@ -28,7 +28,7 @@ def operator(u, alpha, t):
 
 
 @pytest.mark.parametrize("shape", [(2, 3, 4), (5, 9, 7), (33, 17, 128), (24, 40, 132), (9, 130, 260), (70, 8, 31),
-                                   (61, 1, 96), (40, 1, 33), (96, 96, 96)])
+                                   (61, 1, 96), (40, 1, 33), (96, 96, 96), (190, 180, 184), (185, 184, 187)])
 def test_prior_draw_residual(shape):
     print("case", shape, flush=True)
     nz, ny, nx = shape
