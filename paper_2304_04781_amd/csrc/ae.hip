@@ -1369,7 +1369,8 @@ namespace {
 // noalloc, nor on a stream under graph capture (a captured pointer would outlive the
 // buffer's growth).
 void encode_fused(const ae_net* a, const PatchGrid& pg, int nsrc, const float* state, const float* mm, int H, int fmt,
-                  void* latent, float* meta, float* qscale, hipStream_t st, uint16_t* meta16, bool noalloc)
+                  void* latent, float* meta, float* qscale, hipStream_t st, uint16_t* meta16, bool noalloc,
+                  LatentSums* defer = nullptr)
 {
     const long long P = pg.P * nsrc;
     EncPlan plan = fused_encode_plan(P, !noalloc);
@@ -1390,7 +1391,8 @@ void encode_fused(const ae_net* a, const PatchGrid& pg, int nsrc, const float* s
     }
     const bool fp8 = fmt == AE_LATENT_FP8;
     fused_encode(plan, pg, nsrc, state, meta, mm, H, a->beta_d, a->wp1, a->bias(0), a->wt[1], a->bias(1),
-                 fp8 ? nullptr : (uint16_t*)latent, fp8 ? (uint8_t*)latent : nullptr, qscale, zpart, st, meta16);
+                 fp8 ? nullptr : (uint16_t*)latent, fp8 ? (uint8_t*)latent : nullptr, qscale, zpart, st, meta16,
+                 defer);
 }
 
 }  // namespace
@@ -1426,7 +1428,8 @@ void ae_encode_state(const ae_net* a, const PatchGrid& pg, const float* state, i
 }
 
 void ae_encode_states_mm(const ae_net* a, const PatchGrid& pg, int nsrc, const float* state, const float* mm, int H,
-                         int fmt, void* latent, float* meta, float* qscale, hipStream_t st, uint16_t* meta16)
+                         int fmt, void* latent, float* meta, float* qscale, hipStream_t st, uint16_t* meta16,
+                         LatentSums* defer)
 {
     if (!fused_supported(a->hid, a->lat)) {
         WV_REQUIRE(!meta16, WV_EINVAL, "16-bit metadata needs the fused network shape (hidden 512, latent 32)");
@@ -1439,7 +1442,7 @@ void ae_encode_states_mm(const ae_net* a, const PatchGrid& pg, int nsrc, const f
     }
     WV_REQUIRE(a && state && mm && latent && (meta || meta16) && (fmt == AE_LATENT_BF16 || qscale), WV_EINVAL,
                "encode: null buffer");
-    encode_fused(a, pg, nsrc, state, mm, H, fmt, latent, meta, qscale, st, meta16, false);
+    encode_fused(a, pg, nsrc, state, mm, H, fmt, latent, meta, qscale, st, meta16, false, defer);
 }
 
 void ae_time_normalize_rows(const ae_net* a, const TimeGrid& tg, const float* e_win, int nvalid,

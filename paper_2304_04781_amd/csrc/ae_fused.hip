@@ -74,16 +74,6 @@ __device__ __forceinline__ long long block_base(const A& a, long long b)
     return s * a.N + ((long long)(bz * 4) * a.ny + by * 4) * a.nx + bx * 4;
 }
 
-// e4m3 scale of a patch whose largest |latent| is m
-__device__ __forceinline__ float fp8_scale(float m) { return m > 0.f ? m / 448.0f : 1.0f; }
-// the largest of the 32 values of a half wave
-__device__ __forceinline__ float half_wave_max(float m)
-{
-#pragma unroll
-    for (int o = 16; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-    return m;
-}
-
 struct DecArgs {
     const uint16_t* z;    // [P][L] bf16, or (null)
     const uint8_t* codes;  // [P][L] e4m3 codes with
@@ -409,7 +399,7 @@ __global__ void __launch_bounds__(NT) encode_kernel(const EncArgs a)
 // It is bound by those reads (64 B per clock and CU from L2: 3.4 us per 128 hidden units), hence
 // the split of the hidden units over work-groups while CUs are free. JW = 4 holds all 512
 // hidden units and sums the 8 partial latent blocks itself; with fewer, the blocks go to
-// zpart [8][P][L] and encode_finish_kernel sums them. Either way the additions are those of
+// zpart [8][P][L] and finish_latents sums them. Either way the additions are those of
 // the tiled kernel, in its order.
 template <int L, int TI, int JW>
 __global__ void __launch_bounds__(NT) encode_few_kernel(const EncArgs a, float* zpart)
@@ -598,30 +588,9 @@ __global__ void __launch_bounds__(NT) encode_few_kernel(const EncArgs a, float* 
     }
 }
 
-// latents from the partial blocks of encode_few_kernel: the 8 blocks in order, then the bias;
-// bfloat16, or e4m3 codes with the patch's scale. A half wave per patch.
-__global__ void __launch_bounds__(256) encode_finish_kernel(const float* __restrict__ zpart, const float* __restrict__ b2,
-                                                            long long P, uint16_t* __restrict__ zbf,
-                                                            uint8_t* __restrict__ codes, float* __restrict__ scale)
+__global__ void __launch_bounds__(256) encode_finish_kernel(const LatentSums f)
 {
-    const long long e = blockIdx.x * 256LL + threadIdx.x;
-    const long long p = e >> 5;
-    const int c = (int)(e & 31);
-    if (p >= P) return;
-    float g[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) g[q] = zpart[(q * P + p) * 32 + c];
-    float v = g[0];
-#pragma unroll
-    for (int q = 1; q < 8; ++q) v += g[q];
-    v += b2[c];
-    if (zbf) {
-        zbf[e] = f2bf(v);
-        return;
-    }
-    const float s = fp8_scale(half_wave_max(fabsf(v)));
-    codes[e] = f2e4m3(v / s);
-    if (c == 0) scale[p] = s;
+    finish_latents(f, blockIdx.x * 256LL + threadIdx.x);
 }
 
 // Decode: DEC_NW waves per work-group of DEC_BM patches; wave w owns hidden units
@@ -644,14 +613,16 @@ __global__ void __launch_bounds__(256) encode_finish_kernel(const float* __restr
 constexpr int DEC_NW = WV_DEC_WAVES;
 constexpr int DEC_NT = DEC_NW * 64;
 
-// BM: patches per work-group (16, 32 or DEC_BM)
-template <int L, int BM>
+// BM: patches per work-group (16, 32 or DEC_BM). SP: work-groups (blockIdx.y) that share a tile's 512
+// outputs, each with the whole hidden layer
+template <int L, int BM, int SP>
 __global__ void __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(WV_DEC_WPE > 0 ? WV_DEC_WPE : 1)))
     decode_kernel(const DecArgs a)
 {
     constexpr int IT = BM / 16;        // 16-row tiles
     constexpr int OPW = HID / DEC_NW;  // hidden units / outputs per wave
-    constexpr int JT = OPW / 16;       // 16-wide column tiles per wave
+    constexpr int JT = OPW / 16;       // 16-wide column tiles of hidden units per wave
+    constexpr int JO = JT / SP;        // and of outputs
     constexpr int NK = HID / KB;       // k-steps of layer 4
     constexpr int PFD = WV_DEC_PF;
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
@@ -668,6 +639,7 @@ __global__ void __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(WV_
     const long long m0 = tile * BM;  // first patch within the source
     const long long g0 = src * a.Ps;  // the source's first row of latents and metadata
     const bool has_exc = a.eidx != nullptr;
+    const int ot = (SP == 1 ? wave : (int)blockIdx.y * DEC_NW + wave) * JO;  // the wave's first output tile
 
     if (tid < BM) {
         sExc[tid] = -1;
@@ -690,13 +662,13 @@ __global__ void __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(WV_
     }
 
     // fragment-ordered W4: block (ks, r) at ((ks * 128 + r) * 64) * 8, rows of field f at r = 32 f
-    const uint16_t* wb = a.w4p + ((long long)(a.f * 32 + wave * JT) * 64 + lane) * 8;
-    bf16x8 bq[PFD + 1][JT];
+    const uint16_t* wb = a.w4p + ((long long)(a.f * 32 + ot) * 64 + lane) * 8;
+    bf16x8 bq[PFD + 1][JO];
     // the first W4 stages are in flight during layer 3
     #pragma unroll
     for (int u = 0; u < PFD; ++u)
         #pragma unroll
-        for (int j = 0; j < JT; ++j)
+        for (int j = 0; j < JO; ++j)
             bq[u][j] = *reinterpret_cast<const bf16x8*>(wb + (long long)u * (128 * 512) + j * 512);
 
     // layer 3: H[BM][HID] = GELU(Z W3^T + b3) for this wave's hidden units
@@ -759,17 +731,17 @@ __global__ void __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(WV_
     // layer 4, rows of field f. A row m of tile i is patch 16 i + 4 (m % 4) + m / 4, so that the C rows
     // held for one r by the four lane groups are four x-adjacent patches: each store then covers whole
     // 128-byte rows.
-    f32x4 acc[IT][JT];
+    f32x4 acc[IT][JO];
     #pragma unroll
     for (int i = 0; i < IT; ++i)
         #pragma unroll
-        for (int j = 0; j < JT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < JO; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int arow = 4 * (fr & 3) + (fr >> 2);
     #pragma unroll
     for (int kk = 0; kk < NK; ++kk) {
         if (kk + PFD < NK)
             #pragma unroll
-            for (int j = 0; j < JT; ++j)
+            for (int j = 0; j < JO; ++j)
                 bq[(kk + PFD) % (PFD + 1)][j] =
                     *reinterpret_cast<const bf16x8*>(wb + (long long)(kk + PFD) * (128 * 512) + j * 512);
         bf16x8 af[IT];
@@ -778,15 +750,15 @@ __global__ void __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(WV_
         #pragma unroll
         for (int i = 0; i < IT; ++i)
             #pragma unroll
-            for (int j = 0; j < JT; ++j)
+            for (int j = 0; j < JO; ++j)
                 acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bq[kk % (PFD + 1)][j], acc[i][j], 0, 0, 0);
     }
-    // de-normalise and write: output o = OPW wave + 16 j + fr of the patch -> (lz, ly, lx) = (o / 64, o / 8 % 8, o % 8)
-    float bias[JT];
-    long long off[JT];
+    // de-normalise and write: output o = 16 (ot + j) + fr of the patch -> (lz, ly, lx) = (o / 64, o / 8 % 8, o % 8)
+    float bias[JO];
+    long long off[JO];
     #pragma unroll
-    for (int j = 0; j < JT; ++j) {
-        const int o = wave * OPW + j * 16 + fr;
+    for (int j = 0; j < JO; ++j) {
+        const int o = (ot + j) * 16 + fr;
         bias[j] = a.b4[a.f * 512 + o];
         off[j] = ((long long)(o >> 6) * a.ny + ((o >> 3) & 7)) * a.nx + (o & 7);
     }
@@ -803,11 +775,11 @@ __global__ void __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(WV_
             const int slot = has_exc ? sExc[pl] : -1;
             if (slot < 0) {
                 #pragma unroll
-                for (int j = 0; j < JT; ++j) out[base + off[j]] = lo + rg * (acc[i][j][r] + bias[j]);
+                for (int j = 0; j < JO; ++j) out[base + off[j]] = lo + rg * (acc[i][j][r] + bias[j]);
             } else {
                 #pragma unroll
-                for (int j = 0; j < JT; ++j)
-                    out[base + off[j]] = a.exc[(long long)slot * 512 + wave * OPW + j * 16 + fr];
+                for (int j = 0; j < JO; ++j)
+                    out[base + off[j]] = a.exc[(long long)slot * 512 + (ot + j) * 16 + fr];
             }
         }
 }
@@ -1003,7 +975,8 @@ EncPlan fused_encode_plan(long long P, bool can_split)
 
 void fused_encode(EncPlan plan, const PatchGrid& pg, int nsrc, const float* state, float* meta, const float* mm, int H,
                   const float* beta, const uint16_t* w1p, const float* b1, const uint16_t* w2t, const float* b2,
-                  uint16_t* zbf, uint8_t* codes, float* scale, float* zpart, hipStream_t st, uint16_t* meta16)
+                  uint16_t* zbf, uint8_t* codes, float* scale, float* zpart, hipStream_t st, uint16_t* meta16,
+                  LatentSums* defer)
 {
     WV_REQUIRE(!meta16 || mm, WV_EINVAL, "16-bit metadata is written from the step's (min, max) partials");
     WV_REQUIRE(zbf || (codes && scale), WV_EINVAL, "encode: null latent buffer");
@@ -1014,8 +987,10 @@ void fused_encode(EncPlan plan, const PatchGrid& pg, int nsrc, const float* stat
     case ENC_FEW_SPLIT:
         WV_REQUIRE(zpart, WV_EINVAL, "encode: null work buffer");
         launch_few<1, 1>(a, zpart, st);
-        hipLaunchKernelGGL(encode_finish_kernel, dim3((unsigned)((a.P * 32 + 255) / 256)), dim3(256), 0, st, zpart, b2,
-                           a.P, zbf, codes, scale);
+        if (const LatentSums f{zpart, b2, a.P, zbf, codes, scale}; defer)
+            *defer = f;
+        else
+            hipLaunchKernelGGL(encode_finish_kernel, dim3((unsigned)((a.P * 32 + 255) / 256)), dim3(256), 0, st, f);
         break;
     case ENC_FEW: launch_few<1, 4>(a, nullptr, st); break;
     case ENC_FEW_PAIR: launch_few<2, 4>(a, nullptr, st); break;
@@ -1028,17 +1003,17 @@ void fused_encode(EncPlan plan, const PatchGrid& pg, int nsrc, const float* stat
 
 namespace {
 
-template <int BMT>
+template <int BMT, int SP = 1>
 void launch_decode(DecArgs a, int nsrc, long long grid, hipStream_t st)
 {
     const size_t sm = (size_t)BMT * (HID + HPAD) * 2 + (size_t)BMT * 20;
-    allow_smem(decode_kernel<32, BMT>, sm);
+    allow_smem(decode_kernel<32, BMT, SP>, sm);
     a.tps = (a.Ps + BMT - 1) / BMT;
     const long long tiles = a.tps * nsrc;
     const long long per = grid > 0 ? grid : tiles;
     for (a.t0 = 0; a.t0 < tiles; a.t0 += per) {
-        hipLaunchKernelGGL((decode_kernel<32, BMT>), dim3((unsigned)std::min(per, tiles - a.t0)), dim3(DEC_NT), sm, st,
-                           a);
+        hipLaunchKernelGGL((decode_kernel<32, BMT, SP>), dim3((unsigned)std::min(per, tiles - a.t0), SP), dim3(DEC_NT),
+                           sm, st, a);
         WV_HIP(hipGetLastError());
     }
 }
@@ -1066,9 +1041,12 @@ void fused_decode(const PatchGrid& pg, int nsrc, const uint16_t* z, const uint8_
     // Work-groups of fewer patches while that fills more CUs (each reads 512 KiB of W4 from L2):
     // us per decode of e for 16 / 32 / 64 patches: 8.3 / 10.5 / 16.2 at 216 patches, 10.8 / 12.2 /
     // 17.8 at 4096, 15.9 / 13.4 / 18.5 at 6144, 25.3 / 21.1 / 20.7 at 12288.
+    // While four times as many work-groups of 16 still fit one round of CUs, four share a tile's
+    // outputs (128 KiB of W4 each): a step of the reverse sweep at 216 patches 16.4 -> 14.1 us.
     const long long P = fused_patches(pg, nsrc);
     const int bm = P <= 4096 ? 16 : P <= 8192 ? 32 : DEC_BM;
-    if (bm == 16) launch_decode<16>(a, nsrc, 0, st);
+    if (P <= 1024) launch_decode<16, 4>(a, nsrc, 0, st);
+    else if (bm == 16) launch_decode<16>(a, nsrc, 0, st);
     else if (bm == 32) launch_decode<32>(a, nsrc, 0, st);
     else launch_decode<DEC_BM>(a, nsrc, grid, st);
 }

@@ -5,6 +5,8 @@
 
 namespace wv {
 
+struct LatentSums;  // ae_math.h
+
 struct PatchGrid {
     int nz, ny, nx;
     long long P;  // patches = (nz/8)(ny/8)(nx/8)
@@ -62,9 +64,11 @@ void ae_encode_state(const ae_net* net, const PatchGrid& pg, const float* state,
 // normalisation) into contiguous latents, metadata and scales.
 // meta16 (optional): bfloat16 (lo, r) written instead of meta, lo rounded down and
 // r up to bfloat16 before the normalisation uses them.
+// defer (optional): where the latents' last sums would be a launch of their own they are left in
+// *defer, for a launch that the caller queues next on st (exceptions_select).
 void ae_encode_states_mm(const ae_net* net, const PatchGrid& pg, int nsrc, const float* state, const float* mm, int H,
                          int fmt, void* latent, float* meta, float* qscale, hipStream_t st,
-                         uint16_t* meta16 = nullptr);
+                         uint16_t* meta16 = nullptr, LatentSums* defer = nullptr);
 // Exception patches of a stored state, per source: K patch indices in increasing order,
 // their exact e values [K][512] ((lz, ly, lx) order), and rng [ceil(P/DEC_BM) + 1]:
 // the exceptions of patches [DEC_BM b, DEC_BM b + DEC_BM) are idx[rng[b] .. rng[b+1]).
@@ -104,7 +108,8 @@ EncPlan fused_encode_plan(long long P, bool can_split);
 // w1p: W1^T packed by fused_pack; w4p: W4^T packed by fused_pack.
 void fused_encode(EncPlan plan, const PatchGrid& pg, int nsrc, const float* state, float* meta, const float* mm, int H,
                   const float* beta, const uint16_t* w1p, const float* b1, const uint16_t* w2t, const float* b2,
-                  uint16_t* zbf, uint8_t* codes, float* scale, float* zpart, hipStream_t st, uint16_t* meta16);
+                  uint16_t* zbf, uint8_t* codes, float* scale, float* zpart, hipStream_t st, uint16_t* meta16,
+                  LatentSums* defer);
 // latents z, or codes and scale (z null); exc (field 0 only): exception patches written with
 // their exact values.
 // grid > 0: the decode is queued as launches of at most grid work-groups, one after the
@@ -131,10 +136,12 @@ constexpr int EXC_NBIN = 1 << (32 - EXC_BIN_SHIFT);
 // selection from meta [P][4][2] into idx [K] (increasing patch order) and the ranges
 // rng [ceil(P/bm) + 1] (rng[b] = number of idx entries below patch bm b); a single
 // work-group kernel, cheap to overlap with other work. Few patches (exceptions_fused) are
-// also copied by it: exc [K][512] from state
+// also copied by it: exc [K][512] from state. fin (few patches, exceptions_few): the encode's latents
+// are finished by the same launch, beside the selection
+inline bool exceptions_few(long long P) { return P <= 1024; }
 inline bool exceptions_fused(int K) { return K <= 64; }
 void exceptions_select(const PatchGrid& pg, const float* state, const float* meta, int K, int* idx, int bm, int* rng,
-                       float* exc, hipStream_t st, const uint16_t* meta16);
+                       float* exc, hipStream_t st, const uint16_t* meta16, const LatentSums* fin = nullptr);
 // copy the e values of the selected patches to exc [K][512] (not exceptions_fused)
 void exceptions_gather(const PatchGrid& pg, const float* state, int K, const int* idx, float* exc, hipStream_t st);
 // Write the stored e values back into an e field [N].

@@ -99,4 +99,46 @@ __device__ __forceinline__ float gelu_prime(float x)
            x * __builtin_amdgcn_exp2f(-0.5f * x * x * 1.4426950408889634f) * 0.39894228040143268f;
 }
 
+// e4m3 scale of a patch whose largest |latent| is m
+__device__ __forceinline__ float fp8_scale(float m) { return m > 0.f ? m / 448.0f : 1.0f; }
+// the largest of the 32 values of a half wave
+__device__ __forceinline__ float half_wave_max(float m)
+{
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    return m;
+}
+
+// Latents of an encode that was split over the hidden units: 8 partial blocks [8][P][32] to be
+// summed in order, then the bias; bfloat16, or e4m3 codes with the patch's scale.
+struct LatentSums {
+    const float* zpart;  // null: nothing to do
+    const float* b2;
+    long long P;
+    uint16_t* zbf;
+    uint8_t* codes;
+    float* scale;
+};
+// latent e % 32 of patch e / 32: a half wave per patch
+__device__ __forceinline__ void finish_latents(const LatentSums& f, long long e)
+{
+    const long long p = e >> 5;
+    const int c = (int)(e & 31);
+    if (p >= f.P) return;
+    float g[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) g[q] = f.zpart[(q * f.P + p) * 32 + c];
+    float v = g[0];
+#pragma unroll
+    for (int q = 1; q < 8; ++q) v += g[q];
+    v += f.b2[c];
+    if (f.zbf) {
+        f.zbf[e] = f2bf(v);
+        return;
+    }
+    const float s = fp8_scale(half_wave_max(fabsf(v)));
+    f.codes[e] = f2e4m3(v / s);
+    if (c == 0) f.scale[p] = s;
+}
+
 }  // namespace wv

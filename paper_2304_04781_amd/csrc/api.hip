@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "ae_internal.h"
+#include "ae_math.h"
 #include "wv_internal.h"
 
 namespace wv {
@@ -837,13 +838,15 @@ hipStream_t side_stream(wv_ctx* c, int which);
 // encode x_n of every source into the autoencoder store L on stream st, with the
 // per-patch (min, max) partials mm of the step that wrote it when given (else the
 // encode computes them)
-void encode_state_into(wv_ctx* c, LatStore& L, int n, const float* state, hipStream_t st, const float* mm)
+// (defer: as in ae_encode_states_mm)
+void encode_state_into(wv_ctx* c, LatStore& L, int n, const float* state, hipStream_t st, const float* mm,
+                       LatentSums* defer = nullptr)
 {
     const PatchGrid pg = patch_grid(c->g.nz, c->g.ny, c->g.nx);
     const int te = c->tm.begin(TM_ENCODE, st);
     if (mm) {
         ae_encode_states_mm(c->ae, pg, c->S, state, mm, c->H, ae_fmt(c->mode), lat_slot(c, L, n - 1, 0),
-                            meta_slot(c, L, n - 1, 0), qs_slot(c, L, n - 1, 0), st, meta16_slot(c, L, n - 1, 0));
+                            meta_slot(c, L, n - 1, 0), qs_slot(c, L, n - 1, 0), st, meta16_slot(c, L, n - 1, 0), defer);
     } else {
         WV_REQUIRE(!c->m16, WV_EINVAL, "16-bit metadata needs the step's (min, max) partials");
         for (int s = 0; s < c->S; ++s)
@@ -969,7 +972,11 @@ void store_state_async(wv_ctx* c, int j, const float* state, const float* mm)
     const int b = j % 3;
     hipStream_t s1 = side_stream(c, 0), s2 = side_stream(c, 1);
     order_after(s1, c->st, c->ev_step[b]);
-    encode_state_into(c, c->fs, j, state, s1, mm);
+    // in order on one stream, the selection's launch finishes the latents (their partial sums
+    // stay in the stream's work buffer until then)
+    LatentSums fin{};
+    const bool join = c->K > 0 && s1 == s2 && exceptions_few(c->P);
+    encode_state_into(c, c->fs, j, state, s1, mm, join ? &fin : nullptr);
     if (c->K <= 0) {
         if (s1 != c->st) WV_HIP(hipEventRecord(c->ev_stored[b], s1));
         return;
@@ -980,7 +987,7 @@ void store_state_async(wv_ctx* c, int j, const float* state, const float* mm)
         const long long q = (long long)(j - 1) * c->S + s;
         exceptions_select(pg, state + s * 4 * c->N, meta_slot(c, c->fs, j - 1, s), c->K, c->fs.exc_idx + q * c->K,
                           DEC_BM, rng_slot(c, c->fs, q), c->fs.exc + q * c->K * 512, s2,
-                          meta16_slot(c, c->fs, j - 1, s));
+                          meta16_slot(c, c->fs, j - 1, s), s == 0 ? &fin : nullptr);
     }
     c->tm.end(tx, s2);
     const int tg = c->tm.begin(TM_EXC_GATHER, s2);

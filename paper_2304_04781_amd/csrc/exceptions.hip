@@ -6,6 +6,7 @@
 // per window and source with its e-only vectors (4^3 cells x 32 levels).
 
 #include "ae_internal.h"
+#include "ae_math.h"
 
 namespace wv {
 namespace {
@@ -95,9 +96,19 @@ __device__ __forceinline__ void select_tail(int P, int K, const int* out, const 
         st.rng[b2] = lo;
     }
     if (!st.exc) return;
-    for (int e = tid; e < K * 512; e += SEL_THREADS) {
-        const int p = out[e >> 9];
-        if (p >= 0 && p < P) st.exc[e] = st.state[patch_cell(p, e & 511, st.ny, st.nx, st.Py, st.Px)];
+    constexpr int U = 4;  // loads ahead of the stores
+    for (int e0 = tid; e0 < K * 512; e0 += U * SEL_THREADS) {
+        float v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = min(e0 + u * SEL_THREADS, K * 512 - 1), p = out[e >> 9];
+            v[u] = p >= 0 && p < P ? st.state[patch_cell(p, e & 511, st.ny, st.nx, st.Py, st.Px)] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = e0 + u * SEL_THREADS;
+            if (e < K * 512) st.exc[e] = v[u];
+        }
     }
 }
 
@@ -216,13 +227,21 @@ __global__ void __launch_bounds__(SEL_THREADS) select_kernel(const float* __rest
 // (patch 64 q + lane in slot q), finds the bin of the K-th largest by bisection over the bin
 // numbers, counting with ballots, and lists in patch order with the ballots' prefix counts:
 // no barrier, no histogram. The histogram kernel clears and scans 16384 bins whatever P
-// (12 to 17 us for 216 to 1000 patches).
+// (12 to 17 us for 216 to 1000 patches). What follows reads the list from LDS.
+// The other work-groups of the launch finish the encode's latents, when asked (216 patches: 5.4 us
+// together, 9.3 and 3.4 apart with the list read back from memory).
 constexpr int SEL_FEW = 1024;
+template <int NQ>
 __global__ void __launch_bounds__(SEL_THREADS) select_few_kernel(const float* __restrict__ meta,
                                                                  const uint16_t* __restrict__ meta16, int ms, int P,
-                                                                 int K, int* out, const SelectTail st)
+                                                                 int K, int* out, const SelectTail st,
+                                                                 const LatentSums fin)
 {
-    constexpr int NQ = SEL_FEW / 64;
+    if (blockIdx.x > 0) {
+        finish_latents(fin, (blockIdx.x - 1) * (long long)SEL_THREADS + threadIdx.x);
+        return;
+    }
+    __shared__ int list[64 * NQ];
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
         int key[NQ];  // bins are below 2^14; slots past P hold -1
@@ -251,12 +270,12 @@ __global__ void __launch_bounds__(SEL_THREADS) select_few_kernel(const float* __
             const unsigned long long eq = __ballot(key[q] == lo);
             const bool pick = key[q] > lo || (key[q] == lo && eqs + __popcll(eq & below) < rem);
             const unsigned long long picked = __ballot(pick);
-            if (pick) out[pos + __popcll(picked & below)] = q * 64 + lane;
+            if (pick) list[pos + __popcll(picked & below)] = out[pos + __popcll(picked & below)] = q * 64 + lane;
             pos += __popcll(picked);
             eqs += __popcll(eq);
         }
     }
-    select_tail(P, K, out, st);
+    select_tail(P, K, list, st);
 }
 
 // exc[k][l] = e of patch idx[k] at local cell l (one block per patch)
@@ -318,7 +337,7 @@ __global__ void time_scatter_kernel(float* __restrict__ e_win, int S, int s, int
 }  // namespace
 
 void exceptions_select(const PatchGrid& pg, const float* state, const float* meta, int K, int* idx, int bm, int* rng,
-                       float* exc, hipStream_t st, const uint16_t* meta16)
+                       float* exc, hipStream_t st, const uint16_t* meta16, const LatentSums* fin)
 {
     if (K <= 0) return;
     WV_REQUIRE(K <= pg.P, WV_EINVAL, "more exception patches than patches");
@@ -328,8 +347,16 @@ void exceptions_select(const PatchGrid& pg, const float* state, const float* met
     // for 4 patches took 4 (and the range table 5)
     const SelectTail tail{rng, bm, (int)((pg.P + bm - 1) / bm), state, exceptions_fused(K) ? exc : nullptr,
                           pg.ny, pg.nx, pg.ny / 8, pg.nx / 8};
-    if (pg.P <= SEL_FEW)
-        hipLaunchKernelGGL(select_few_kernel, dim3(1), dim3(SEL_THREADS), 0, st, meta, meta16, 8, (int)pg.P, K, idx, tail);
+    const LatentSums f = fin ? *fin : LatentSums{};
+    WV_REQUIRE(!f.zpart || exceptions_few(pg.P), WV_EINVAL, "latents left to a selection of many patches");
+    static_assert(SEL_FEW == 1024, "exceptions_few");
+    const unsigned nb = 1 + (f.zpart ? (unsigned)((f.P * 32 + SEL_THREADS - 1) / SEL_THREADS) : 0);
+    if (pg.P <= 256)
+        hipLaunchKernelGGL(select_few_kernel<4>, dim3(nb), dim3(SEL_THREADS), 0, st, meta, meta16, 8, (int)pg.P, K, idx,
+                           tail, f);
+    else if (exceptions_few(pg.P))
+        hipLaunchKernelGGL(select_few_kernel<16>, dim3(nb), dim3(SEL_THREADS), 0, st, meta, meta16, 8, (int)pg.P, K, idx,
+                           tail, f);
     else
         hipLaunchKernelGGL(select_kernel, dim3(1), dim3(SEL_THREADS), 0, st, meta, meta16, 8, (int)pg.P, K, idx, tail);
     WV_HIP(hipGetLastError());
