@@ -56,6 +56,19 @@ T* dev_alloc(size_t count)
     return static_cast<T*>(p);
 }
 
+
+
+// a buffer that only makes a path faster: null where there is no memory for it
+template <class T>
+T* dev_try_alloc(size_t count)
+{
+    try {
+        return dev_alloc<T>(count);
+    } catch (const Error& e) {
+        if (e.code != WV_ENOMEM) throw;
+        return nullptr;
+    }
+}
 template <class T>
 void dev_free(T*& p)
 {
@@ -243,7 +256,7 @@ struct wv_ctx {
     float* m = nullptr;
     float* c_last = nullptr;
     float* wavelet = nullptr;
-    float* work[3] = {nullptr, nullptr, nullptr};  // [2]: only for autoencoder stores
+    float* work[4] = {nullptr, nullptr, nullptr, nullptr};  // [2], [3]: see forward_sweep, reverse_sweep
     float* adj[2] = {nullptr, nullptr};
     float* incb[3] = {nullptr, nullptr, nullptr};  // the third only while an incremental store runs beside
     float* acc = nullptr;
@@ -287,7 +300,7 @@ struct wv_ctx {
     int K = 0;                   // active exception patches per state
     int nbd = 0;                 // decode work-groups per state
     long long pipe_grid = 0;     // work-groups per decode launch of the running decode pipeline (0: one launch)
-    float* mmpart = nullptr;     // [3][S][P][H][4][2] (min, max) partials of the forward step
+    float* mmpart = nullptr;     // [4][S][P][max(H, 8)][4][2] (min, max) partials of the forward steps
     int H = 1;                   // partials per patch: y sub-tiles times z sub-chunks
     // Autoencoder stores and decodes run beside the stencil steps: `side` encodes
     // x_j (and decodes e^k for the reverse sweeps), `side2` selects and copies the
@@ -299,9 +312,9 @@ struct wv_ctx {
     hipStream_t side = nullptr;
     hipStream_t side2 = nullptr;
     hipStream_t side3 = nullptr;
-    hipEvent_t ev_step[3] = {};    // main: x_j written (j mod 3)
-    hipEvent_t ev_enc[3] = {};     // side: x_j encoded
-    hipEvent_t ev_stored[3] = {};  // x_j fully stored: its buffer and mmpart slot are free
+    hipEvent_t ev_step[4] = {};    // main: x_j written (j mod the number of state buffers)
+    hipEvent_t ev_enc[4] = {};     // side: x_j encoded
+    hipEvent_t ev_stored[4] = {};  // x_j fully stored: its buffer and mmpart slot are free
     hipEvent_t ev_ready[NEB] = {};  // side: e^k decoded into ebuf slot
     hipEvent_t ev_free[NEB] = {};   // main: ebuf slot consumed
     hipEvent_t ev_join = nullptr;
@@ -573,6 +586,22 @@ void pair_fwd(wv_ctx* c, const float* in, float* out, int n, float* traces, floa
     c->tm.end(t, c->st);
 }
 
+// forward steps n and n + 1 with both states written, and their (min, max) partials, 8 per patch
+void pair_fwd_mid(wv_ctx* c, const float* in, float* mid, float* out, int n, float* traces, float* mm1, float* mm2)
+{
+    PairArgs a = pair_args(c, in, out, n, n + 1);
+    a.kc = c->pair.kc_mid;
+    a.chunks_z = c->pair.chunks_mid;
+    a.traces = traces;
+    if (!traces) a.nrec = 0;
+    a.mid = mid;
+    a.mm1 = mm1;
+    a.mm2 = mm2;
+    const int t = c->tm.begin(TM_FWD, c->st, 2);
+    launch_pair(MODE_FWD, c->pair, a, c->S, c->st);
+    c->tm.end(t, c->st);
+}
+
 // incremental steps n and n + 1 with the forward e of both levels; x1, x2: the new e also there
 void pair_inc(wv_ctx* c, const float* in, float* out, int n, const float* e1, const float* e2, long long estride,
               float* dtraces, float* x1, float* x2)
@@ -697,6 +726,7 @@ void free_store(wv_ctx* c)
     c->delta_bytes = 0;
     dev_free(c->mmpart);
     dev_free(c->work[2]);
+    dev_free(c->work[3]);
     dev_free(c->gbuf);
     dev_free(c->gpart);
     dev_free(c->gres);
@@ -838,14 +868,14 @@ hipStream_t side_stream(wv_ctx* c, int which);
 // encode x_n of every source into the autoencoder store L on stream st, with the
 // per-patch (min, max) partials mm of the step that wrote it when given (else the
 // encode computes them)
-// (defer: as in ae_encode_states_mm)
+// (defer: as in ae_encode_states_mm; H partials per patch, 0: the single steps' c->H)
 void encode_state_into(wv_ctx* c, LatStore& L, int n, const float* state, hipStream_t st, const float* mm,
-                       LatentSums* defer = nullptr)
+                       LatentSums* defer = nullptr, int H = 0)
 {
     const PatchGrid pg = patch_grid(c->g.nz, c->g.ny, c->g.nx);
     const int te = c->tm.begin(TM_ENCODE, st);
     if (mm) {
-        ae_encode_states_mm(c->ae, pg, c->S, state, mm, c->H, ae_fmt(c->mode), lat_slot(c, L, n - 1, 0),
+        ae_encode_states_mm(c->ae, pg, c->S, state, mm, H ? H : c->H, ae_fmt(c->mode), lat_slot(c, L, n - 1, 0),
                             meta_slot(c, L, n - 1, 0), qs_slot(c, L, n - 1, 0), st, meta16_slot(c, L, n - 1, 0), defer);
     } else {
         WV_REQUIRE(!c->m16, WV_EINVAL, "16-bit metadata needs the step's (min, max) partials");
@@ -965,18 +995,17 @@ bool store_side(wv_ctx* c) { return side_stream(c, c->K > 0 ? 1 : 0) != c->st; }
 
 // Autoencoder store of x_j (1 <= j <= T-1) written by the forward step just
 // launched on the main stream, with its min/max partials in mm: encode on `side`,
-// exception selection and copy on `side2`; ev_stored[j % 3] marks the end.
-void store_state_async(wv_ctx* c, int j, const float* state, const float* mm)
+// exception selection and copy on `side2`; ev_stored[b] marks the end (b: x_j's state buffer).
+void store_state_async(wv_ctx* c, int j, const float* state, const float* mm, int b, int H = 0)
 {
     const PatchGrid pg = patch_grid(c->g.nz, c->g.ny, c->g.nx);
-    const int b = j % 3;
     hipStream_t s1 = side_stream(c, 0), s2 = side_stream(c, 1);
     order_after(s1, c->st, c->ev_step[b]);
     // in order on one stream, the selection's launch finishes the latents (their partial sums
     // stay in the stream's work buffer until then)
     LatentSums fin{};
     const bool join = c->K > 0 && s1 == s2 && exceptions_few(c->P);
-    encode_state_into(c, c->fs, j, state, s1, mm, join ? &fin : nullptr);
+    encode_state_into(c, c->fs, j, state, s1, mm, join ? &fin : nullptr, H);
     if (c->K <= 0) {
         if (s1 != c->st) WV_HIP(hipEventRecord(c->ev_stored[b], s1));
         return;
@@ -1243,21 +1272,53 @@ float* forward_sweep(wv_ctx* c, float* traces, const std::vector<int>* snap, flo
         c->tdelta_ok = false;
     }
     if (c->plane) return plane_forward_sweep(c, traces, snap, capture, every, last, ecap_idx, ecap);
-    // autoencoder stores run beside the steps (x_j in work[j % 3])
+    // autoencoder stores run beside the steps (x_j in work[j % nbuf]): a third buffer, and where
+    // two steps are taken per launch a fourth, so that the two states before may still be read
     const bool ae = is_ae(c->mode) && c->mmpart && c->has_y;
     if (ae && !c->work[2]) c->work[2] = dev_alloc<float>(c->state_floats());
+    if (ae && c->pair.use && !c->work[3]) c->work[3] = dev_try_alloc<float>(c->state_floats());
+    const int nbuf = c->work[3] ? 4 : 3;
+    // before a step overwrites the buffer and min/max slot of x_j: the store of their x_{j - nbuf}
+    auto reuse = [&](int j) {
+        if (j - nbuf >= 1 && j - nbuf <= c->T - 1 && store_side(c)) wait_event(c->st, c->ev_stored[j % nbuf]);
+    };
     launch_fill(c->work[0], c->state_floats(), 0.f, c->st);
     float* cur = c->work[0];
     float* prev = cur;
     const int ncap = (capture && every > 0) ? (c->T - 1) / every : 0;
-    const long long mm_stride = (long long)c->S * c->P * c->H * 8;
+    const long long mm_stride = (long long)c->S * c->P * std::max(c->H, 8) * 8;
     // two steps per launch where x_{n+1} is not needed whole: no snapshot (x_{T-1} among them) or
     // capture of it, no encode
     auto needed = [&](int j) {
         return (snap && ((*snap)[j] > 0 || j == c->T - 1)) || (ncap > 0 && j % every == 0 && j / every <= ncap) ||
                (ecap_idx && (*ecap_idx)[j] >= 0);
     };
+    auto captured = [&](int j, const float* x) {
+        if (ncap > 0 && j % every == 0 && j / every <= ncap)
+            WV_HIP(hipMemcpyAsync(capture + (long long)(j / every - 1) * c->state_floats(), x,
+                                  sizeof(float) * c->state_floats(), hipMemcpyDeviceToDevice, c->st));
+        if (ecap_idx && (*ecap_idx)[j] >= 0)
+            for (int s = 0; s < c->S; ++s)
+                launch_copy(ecap + ((long long)(*ecap_idx)[j] * c->S + s) * c->N, x + s * 4 * c->N, c->N, c->st);
+    };
     for (int n = 0; n < c->T; ++n) {
+        if (ae && nbuf == 4 && n + 2 <= c->T - 1) {
+            reuse(n + 1);
+            reuse(n + 2);
+            float *const mid = c->work[(n + 1) % 4], *const out = c->work[(n + 2) % 4];
+            pair_fwd_mid(c, cur, mid, out, n, traces, c->mmpart + (n + 1) % 4 * mm_stride,
+                         c->mmpart + (n + 2) % 4 * mm_stride);
+            for (int j = n + 1; j <= n + 2; ++j) {
+                float* const x = c->work[j % 4];
+                store_state_async(c, j, x, c->mmpart + j % 4 * mm_stride, j % 4, 8);
+                guard_check(c, j, x, j % 4);
+                captured(j, x);
+            }
+            prev = mid;
+            cur = out;
+            ++n;
+            continue;
+        }
         if (c->pair.use && !ae && !is_ae(c->mode) && n + 2 <= c->T && !needed(n + 1)) {
             auto slot = [&](int j) -> float* {
                 return j > c->T - 1 ? nullptr : is_time(c->mode) ? time_slot(c, c->ts, j)
@@ -1270,29 +1331,19 @@ float* forward_sweep(wv_ctx* c, float* traces, const std::vector<int>* snap, flo
             cur = out;
             for (int j = n + 1; j <= n + 2; ++j) store_state(c, c->fs, j, out);
             ++n;
-            if (needed(n + 1)) {
-                const int j = n + 1;
-                if (ncap > 0 && j % every == 0 && j / every <= ncap)
-                    WV_HIP(hipMemcpyAsync(capture + (long long)(j / every - 1) * c->state_floats(), out,
-                                          sizeof(float) * c->state_floats(), hipMemcpyDeviceToDevice, c->st));
-                if (ecap_idx && (*ecap_idx)[j] >= 0)
-                    for (int s = 0; s < c->S; ++s)
-                        launch_copy(ecap + ((long long)(*ecap_idx)[j] * c->S + s) * c->N, out + s * 4 * c->N, c->N,
-                                    c->st);
-            }
+            captured(n + 1, out);
             continue;
         }
         const int j = n + 1;  // this step writes x_j
         const bool store = j <= c->T - 1;
         float* out;
         if (ae) {
-            out = c->work[j % 3];
-            // the buffer and min/max slot held x_{j-3}: its store must be done
-            if (j - 3 >= 1 && j - 3 <= c->T - 1 && store_side(c)) wait_event(c->st, c->ev_stored[j % 3]);
+            out = c->work[j % nbuf];
+            reuse(j);
         } else {
             out = (snap && (*snap)[j] > 0) ? c->slot_ptr((*snap)[j]) : other_work(c, cur);
         }
-        float* mm = (ae && store) ? c->mmpart + (j % 3) * mm_stride : nullptr;
+        float* mm = (ae && store) ? c->mmpart + (j % nbuf) * mm_stride : nullptr;
         // time compression: the step writes e^j straight into its window slot; the
         // buffer held window w - 2, whose compression must have read it. Full storage: into
         // the history (a copy after each step cost the 128 x 128 solve 1.6 us of its 5)
@@ -1301,17 +1352,12 @@ float* forward_sweep(wv_ctx* c, float* traces, const std::vector<int>* snap, flo
         fwd_step(c, cur, out, n, traces, mm, ew);
         if (store) {
             if (ae)
-                store_state_async(c, j, out, mm);
+                store_state_async(c, j, out, mm, j % nbuf);
             else
                 store_state(c, c->fs, j, out);
-            guard_check(c, j, out, ae ? j % 3 : -1);
+            guard_check(c, j, out, ae ? j % nbuf : -1);
         }
-        if (ncap > 0 && j % every == 0 && j / every <= ncap)
-            WV_HIP(hipMemcpyAsync(capture + (long long)(j / every - 1) * c->state_floats(), out,
-                                  sizeof(float) * c->state_floats(), hipMemcpyDeviceToDevice, c->st));
-        if (ecap_idx && (*ecap_idx)[j] >= 0)
-            for (int s = 0; s < c->S; ++s)
-                launch_copy(ecap + ((long long)(*ecap_idx)[j] * c->S + s) * c->N, out + s * 4 * c->N, c->N, c->st);
+        captured(j, out);
         prev = cur;
         cur = out;
     }
@@ -1410,7 +1456,7 @@ void reverse_sweep(wv_ctx* c, const float* resid, const std::vector<RevAction>* 
     long long extra = 0;
     const float* held = nullptr;
     int held_k = 0;
-    if (c->pair.use && !c->work[2]) c->work[2] = dev_alloc<float>(c->state_floats());
+    if (c->pair.use && !c->work[2]) c->work[2] = dev_try_alloc<float>(c->state_floats());
     auto next_work = [&](const float* from) {
         for (float* w : {c->work[0], c->work[1], c->work[2]})
             if (w != from && w != held) return w;
@@ -1425,7 +1471,7 @@ void reverse_sweep(wv_ctx* c, const float* resid, const std::vector<RevAction>* 
                 std::swap(ain, aout);
                 done += 2;
                 held = nullptr;
-            } else if (c->pair.use && A.a >= 2 && done % 2 == 0) {
+            } else if (c->pair.use && c->work[2] && A.a >= 2 && done % 2 == 0) {
                 held = cur;
                 held_k = A.a;
             } else {
@@ -1595,7 +1641,7 @@ int wv_create(const wv_grid* grid, const int32_t* h_src, const int32_t* h_rec, v
         c->dtr = dev_alloc<float>(ntr);
         c->dresid = dev_alloc<float>(ntr);
         shared_side(c.get());
-        for (int b = 0; b < 3; ++b) {
+        for (int b = 0; b < 4; ++b) {
             WV_HIP(hipEventCreateWithFlags(&c->ev_step[b], SYNC_EVENT_FLAGS));
             WV_HIP(hipEventCreateWithFlags(&c->ev_enc[b], SYNC_EVENT_FLAGS));
             WV_HIP(hipEventCreateWithFlags(&c->ev_stored[b], SYNC_EVENT_FLAGS));
@@ -1631,8 +1677,9 @@ int wv_destroy(wv_ctx* c)
     c->tm.destroy();
     free_store(c);
     free_tiling(c->tl);
-    for (hipEvent_t e : {c->ev_step[0], c->ev_step[1], c->ev_step[2], c->ev_enc[0], c->ev_enc[1], c->ev_enc[2],
-                         c->ev_stored[0], c->ev_stored[1], c->ev_stored[2], c->ev_join, c->ev_dstep[0],
+    for (hipEvent_t e : {c->ev_step[0], c->ev_step[1], c->ev_step[2], c->ev_step[3], c->ev_enc[0], c->ev_enc[1],
+                         c->ev_enc[2], c->ev_enc[3], c->ev_stored[0], c->ev_stored[1], c->ev_stored[2],
+                         c->ev_stored[3], c->ev_join, c->ev_dstep[0],
                          c->ev_dstep[1], c->ev_dstep[2], c->ev_denc[0], c->ev_denc[1], c->ev_denc[2],
                          c->ev_dstored[0], c->ev_dstored[1], c->ev_dstored[2]})
         if (e) (void)hipEventDestroy(e);
@@ -1723,7 +1770,7 @@ void set_storage_mode(wv_ctx* c, int mode, int32_t n_checkpoints, ae_net* ae, in
         alloc_latstore(c, c->fs, mode, K);
         c->K = K;
         c->H = 8 / c->tl.by * (c->tl.kc_mm < 8 ? 8 / c->tl.kc_mm : 1);
-        c->mmpart = dev_alloc<float>((size_t)3 * c->S * c->P * c->H * 8);
+        c->mmpart = dev_alloc<float>((size_t)4 * c->S * c->P * std::max(c->H, 8) * 8);
         if (guard_tol > 0.0) {
             c->gbuf = dev_alloc<float>((size_t)c->S * c->N);
             c->gpart = dev_alloc<double>(3 * (size_t)c->nblk_red);

@@ -79,7 +79,12 @@ __device__ __forceinline__ float lane_from_right(float v)
 }
 
 // LXW lanes per row (64 / LXW rows per wave)
-template <int LXW, int MODE, bool TAIL, bool EX>
+// MID (forward): the state between the steps is written as well (a.mid), and of both new states the
+// (min, max) of each field over the levels of every row of an 8^3 patch, gathered level by level in
+// LDS: 8 partials per patch, one a row. For the autoencoder stores, which encode every state.
+// 256^3 with bf16 latents 54.7 -> 53.9 ms (the encodes beside, 2 x 79 us alone, are the longer
+// half of it), 4 sources of 128 x 192 x 256 with FP8, encoded in order, 51.8 -> 48.8.
+template <int LXW, int MODE, bool TAIL, bool EX, bool MID>
 __global__ void __launch_bounds__(NT) pair_step_kernel(const PairArgs a)
 {
     // every product that is fused with an addition is written as an fma
@@ -88,6 +93,9 @@ __global__ void __launch_bounds__(NT) pair_step_kernel(const PairArgs a)
     constexpr int ROWS = NW * 64 / LXW;
     constexpr int CORE = ROWS - 4;
     __shared__ f32x4 sX[2][4][ROWS][LXW];  // P and v_y of the first step's level, then of the second's
+
+    static_assert(!MID || (MODE == MODE_FWD && !TAIL), "whole patches");
+    __shared__ f32x4 sM[MID ? 2 : 1][2][MID ? ROWS : 1][LXW];  // per step: running (min, max) of this thread's cells
 
     const int nblk = a.tiles_x * a.tiles_y * a.chunks_z;
     int b = blockIdx.x;
@@ -254,6 +262,46 @@ __global__ void __launch_bounds__(NT) pair_step_kernel(const PairArgs a)
         return d;
     };
 
+    // MID: level lvl of a new state joins the thread's (min, max); the last of a patch's levels writes
+    // the row's partial
+    auto minmax = [&](int step, int lvl, const f32x4& e, const f32x4& vz, const f32x4& vy, const f32x4& vx, float* mm) {
+        f32x4 mn, mx;
+        const f32x4* v[4] = {&e, &vz, &vy, &vx};
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+            const f32x4 q = *v[f];
+            mn[f] = fminf(fminf(q[0], q[1]), fminf(q[2], q[3]));
+            mx[f] = fmaxf(fmaxf(q[0], q[1]), fmaxf(q[2], q[3]));
+        }
+        f32x4 &lo = sM[step][0][row][lane], &hi = sM[step][1][row][lane];
+        if (lvl & 7) {
+            const f32x4 l = lo, h = hi;
+#pragma unroll
+            for (int f = 0; f < 4; ++f) {
+                mn[f] = fminf(mn[f], l[f]);
+                mx[f] = fmaxf(mx[f], h[f]);
+            }
+        }
+        if ((lvl & 7) != 7) {
+            lo = mn;
+            hi = mx;
+            return;
+        }
+        // the patch's other four columns are the next lane's
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+            const float l = lane_from_right(mn[f]), h = lane_from_right(mx[f]);
+            mn[f] = fminf(mn[f], l);
+            mx[f] = fmaxf(mx[f], h);
+        }
+        if (core && (i & 4) == 0) {
+            const long long p = ((long long)(lvl >> 3) * (ny >> 3) + (j >> 3)) * (nx >> 3) + (i >> 3);
+            f32x4* o = reinterpret_cast<f32x4*>(mm + ((s * (N >> 9) + p) * 8 + (j & 7)) * 8);
+            o[0] = f32x4{mn[0], mx[0], mn[1], mx[1]};
+            o[1] = f32x4{mn[2], mx[2], mn[3], mx[3]};
+        }
+    };
+
     const int Kb = max(k0 - 1, 0);
     f32x4 P, A, m, dm, v1;             // first step at level K: v1 its new v_z face
     f32x4 P2, A2, m2, dm2, Vy2, Vx2;   // second step's operands at level K - 1
@@ -341,6 +389,14 @@ __global__ void __launch_bounds__(NT) pair_step_kernel(const PairArgs a)
             if (core1) {
                 record(K, a.tidx, v1);
                 if (EX && a.x1) st4<TAIL, AUX_NT>(nA, a.x1 + s * N + lK, pb4, o_k, nvalid);
+                if constexpr (MID) {
+                    float* mid = a.mid + s * a.sstride + lK;
+                    st4<TAIL, AUX_NT>(nA, mid, pb4, o_k, nvalid);
+                    st4<TAIL, AUX_NT>(v1, mid + N, pb4, o_k, nvalid);
+                    st4<TAIL, AUX_NT>(nVy, mid + 2 * N, pb4, o_k, nvalid);
+                    st4<TAIL, AUX_NT>(nVx, mid + 3 * N, pb4, o_k, nvalid);
+                    minmax(0, K, nA, v1, nVy, nVx, a.mm1);
+                }
             }
         }
         // ---- second step: its v_z face at K, then the cells of k = K - 1
@@ -388,6 +444,7 @@ __global__ void __launch_bounds__(NT) pair_step_kernel(const PairArgs a)
             st4<TAIL, AUX_NT>(Vy, outA + 2 * N + lk, pb4, o_k, nvalid);
             st4<TAIL, AUX_NT>(Vx, outA + 3 * N + lk, pb4, o_k, nvalid);
             if (EX && a.x2) st4<TAIL, AUX_NT>(Ao, a.x2 + s * N + lk, pb4, o_k, nvalid);
+            if constexpr (MID) minmax(MID ? 1 : 0, k, Ao, v2, Vy, Vx, a.mm2);
             if (ADJ) {
                 if (a.closes) {
                     st4<TAIL, 0>(sum, acc + lk, pb4, o_k, nvalid);
@@ -439,6 +496,8 @@ PairPlan pair_plan(int nz, int ny, int nx, int nsrc)
     chunks = std::min(chunks, std::max(1, nz / PR_MIN_KC));
     p.kc = (nz + chunks - 1) / chunks;
     p.chunks = (nz + p.kc - 1) / p.kc;
+    p.kc_mid = (p.kc + 7) / 8 * 8;  // whole patches
+    p.chunks_mid = (nz + p.kc_mid - 1) / p.kc_mid;
     p.use = (long long)nz * ny * nx * nsrc >= PR_MIN_CELLS;
     return p;
 }
@@ -447,15 +506,22 @@ template <int LXW, int MODE, bool EX>
 static void launch_one(const PairArgs& a, const dim3& grid, hipStream_t st)
 {
     if (a.nx % VX != 0)
-        hipLaunchKernelGGL((pair_step_kernel<LXW, MODE, true, EX>), grid, dim3(NT), 0, st, a);
+        hipLaunchKernelGGL((pair_step_kernel<LXW, MODE, true, EX, false>), grid, dim3(NT), 0, st, a);
     else
-        hipLaunchKernelGGL((pair_step_kernel<LXW, MODE, false, EX>), grid, dim3(NT), 0, st, a);
+        hipLaunchKernelGGL((pair_step_kernel<LXW, MODE, false, EX, false>), grid, dim3(NT), 0, st, a);
 }
 
 void launch_pair(int mode, const PairPlan& p, const PairArgs& a, int nsrc, hipStream_t st)
 {
-    const dim3 grid(p.tiles_x * p.tiles_y * p.chunks, nsrc);
     const bool wide = p.lxw == 64;
+    if (a.mid) {
+        const dim3 gm(p.tiles_x * p.tiles_y * p.chunks_mid, nsrc);
+        if (wide) hipLaunchKernelGGL((pair_step_kernel<64, MODE_FWD, false, false, true>), gm, dim3(NT), 0, st, a);
+        else hipLaunchKernelGGL((pair_step_kernel<32, MODE_FWD, false, false, true>), gm, dim3(NT), 0, st, a);
+        WV_HIP(hipGetLastError());
+        return;
+    }
+    const dim3 grid(p.tiles_x * p.tiles_y * p.chunks, nsrc);
     if (mode == MODE_ADJ) wide ? launch_one<64, MODE_ADJ, false>(a, grid, st) : launch_one<32, MODE_ADJ, false>(a, grid, st);
     else if (mode == MODE_INC) wide ? launch_one<64, MODE_INC, true>(a, grid, st) : launch_one<32, MODE_INC, true>(a, grid, st);
     else wide ? launch_one<64, MODE_FWD, true>(a, grid, st) : launch_one<32, MODE_FWD, true>(a, grid, st);

@@ -151,6 +151,7 @@ constexpr int PR_MIN_KC = 4, PR_MAX_KC = 32;
 struct PairPlan {
     bool use;
     int lxw, core_y, tiles_x, tiles_y, kc, chunks;
+    int kc_mid, chunks_mid;  // where the state between is written: chunks of whole patches
 };
 PairPlan pair_plan(int nz, int ny, int nx, int nsrc);
 struct PairArgs {
@@ -180,6 +181,8 @@ struct PairArgs {
     float *acc, *blk;
     int first, closes;       // adjoint: the pair starts / ends an accumulation block
     const float* dm;
+    float* mid;              // forward: x_{n+1} [S][4][N], with the partials of both states (null: no)
+    float *mm1, *mm2;        // [S][P][8][4][2] each
     float *x1, *x2;          // forward, incremental: the new e of each step also here [S][N] (null: no)
 };
 void launch_pair(int mode, const PairPlan& p, const PairArgs& a, int nsrc, hipStream_t st);
