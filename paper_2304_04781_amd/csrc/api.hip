@@ -973,10 +973,15 @@ void order_after(hipStream_t to, hipStream_t from, hipEvent_t ev)
 // work-groups and the side-stream kernels starve beside it (an 8-source 512^2 x 256
 // decode ran 10x slower than alone), so such contexts use mode 2.
 // States of few patches are stored and read in order on the main stream too: their kernels
-// are shorter than the event records and cross-stream waits (gradient of 48^3 x 240 steps, 216
-// patches: 11.2 ms in order, 17.5 beside; 80^3 x 100, 1000 patches: 9.3 and 7.7).
+// are shorter than the event records and cross-stream waits. Gradients of 100 steps in order / with
+// the selection beside (2) / with all beside (1), in ms: 64^3 (512 patches) 4.0 / 4.7 / 4.0, 72^3
+// 5.2 / 5.0 / 6.2, 80^3 5.7 / 5.2 / 7.5, 88^3 (1331) 7.2 / 6.1 / 6.8; 96^3 (1728, two steps per launch)
+// 8.0 / 7.0 / 5.7.
 #ifndef WV_OVERLAP
 #define WV_OVERLAP 1
+#endif
+#ifndef WV_OVERLAP_ALL_P
+#define WV_OVERLAP_ALL_P 1536
 #endif
 #ifndef WV_OVERLAP_MIN_P
 #define WV_OVERLAP_MIN_P 512
@@ -984,7 +989,7 @@ void order_after(hipStream_t to, hipStream_t from, hipEvent_t ev)
 hipStream_t side_stream(wv_ctx* c, int which)
 {
     if (is_ae(c->mode) && c->P * c->S <= WV_OVERLAP_MIN_P) return c->st;
-    const int mode = (WV_OVERLAP == 1 && c->S > 1) ? 2 : WV_OVERLAP;
+    const int mode = (WV_OVERLAP == 1 && (c->S > 1 || (is_ae(c->mode) && c->P * c->S < WV_OVERLAP_ALL_P))) ? 2 : WV_OVERLAP;
     if (which == 2) return mode == 1 ? c->side3 : c->st;
     if (which) return mode >= 1 ? c->side2 : c->st;
     return mode == 1 ? c->side : c->st;
