@@ -1370,7 +1370,7 @@ namespace {
 // buffer's growth).
 void encode_fused(const ae_net* a, const PatchGrid& pg, int nsrc, const float* state, const float* mm, int H, int fmt,
                   void* latent, float* meta, float* qscale, hipStream_t st, uint16_t* meta16, bool noalloc,
-                  LatentSums* defer = nullptr)
+                  LatentSums* defer = nullptr, const float* state2 = nullptr)
 {
     const long long P = pg.P * nsrc;
     EncPlan plan = fused_encode_plan(P, !noalloc);
@@ -1392,7 +1392,7 @@ void encode_fused(const ae_net* a, const PatchGrid& pg, int nsrc, const float* s
     const bool fp8 = fmt == AE_LATENT_FP8;
     fused_encode(plan, pg, nsrc, state, meta, mm, H, a->beta_d, a->wp1, a->bias(0), a->wt[1], a->bias(1),
                  fp8 ? nullptr : (uint16_t*)latent, fp8 ? (uint8_t*)latent : nullptr, qscale, zpart, st, meta16,
-                 defer);
+                 defer, state2);
 }
 
 }  // namespace
@@ -1429,9 +1429,17 @@ void ae_encode_state(const ae_net* a, const PatchGrid& pg, const float* state, i
 
 void ae_encode_states_mm(const ae_net* a, const PatchGrid& pg, int nsrc, const float* state, const float* mm, int H,
                          int fmt, void* latent, float* meta, float* qscale, hipStream_t st, uint16_t* meta16,
-                         LatentSums* defer)
+                         LatentSums* defer, const float* state2)
 {
     if (!fused_supported(a->hid, a->lat)) {
+        if (state2) {
+            const size_t np = (size_t)nsrc * pg.P;
+            ae_encode_states_mm(a, pg, nsrc, state, mm, H, fmt, latent, meta, qscale, st, meta16);
+            ae_encode_states_mm(a, pg, nsrc, state2, mm + np * H * 8, H, fmt,
+                                (uint8_t*)latent + np * ae_latent_bytes_per_patch(a, fmt), meta + np * 8,
+                                qscale ? qscale + np : nullptr, st, meta16);
+            return;
+        }
         WV_REQUIRE(!meta16, WV_EINVAL, "16-bit metadata needs the fused network shape (hidden 512, latent 32)");
         const long long N = (long long)pg.nz * pg.ny * pg.nx;
         for (int s = 0; s < nsrc; ++s)
@@ -1442,7 +1450,7 @@ void ae_encode_states_mm(const ae_net* a, const PatchGrid& pg, int nsrc, const f
     }
     WV_REQUIRE(a && state && mm && latent && (meta || meta16) && (fmt == AE_LATENT_BF16 || qscale), WV_EINVAL,
                "encode: null buffer");
-    encode_fused(a, pg, nsrc, state, mm, H, fmt, latent, meta, qscale, st, meta16, false, defer);
+    encode_fused(a, pg, state2 ? 2 * nsrc : nsrc, state, mm, H, fmt, latent, meta, qscale, st, meta16, false, defer, state2);
 }
 
 void ae_time_normalize_rows(const ae_net* a, const TimeGrid& tg, const float* e_win, int nvalid,

@@ -54,6 +54,9 @@ struct EncArgs {
     // repeat the last one before; P blocks of 4^3 cells, Ps per source; meta [P][2]
     int nvalid;
     long long lstride;
+    // two states in one launch: the patches from `half` on are of the states that lie `delta` floats
+    // further than the first ones' stride tells
+    long long half = 1LL << 62, delta = 0;
 };
 
 // first element of patch p's cells in the states, field 0
@@ -63,6 +66,11 @@ __device__ __forceinline__ long long patch_base(const A& a, long long p)
     const unsigned u = (unsigned)p, s = u / (unsigned)a.Ps, q = u % (unsigned)a.Ps;  // below 2^31 (fused_patches)
     const unsigned px = q % (unsigned)a.Px, t = q / (unsigned)a.Px, py = t % (unsigned)a.Py, pz = t / (unsigned)a.Py;
     return s * a.sstride + ((long long)(pz * 8) * a.ny + py * 8) * a.nx + px * 8;
+}
+
+__device__ __forceinline__ long long enc_base(const EncArgs& a, long long p)
+{
+    return patch_base(a, p) + (p >= a.half ? a.delta : 0);
 }
 
 // first element of block b's cells at the first level of a window of levels
@@ -183,7 +191,7 @@ __global__ void __launch_bounds__(NT) encode_kernel(const EncArgs a)
     const long long plane = (long long)a.ny * a.nx;
     // (time: k-step kk is level kk / 2, z rows 2 (kk % 2) and the next; thread (am, aq) takes the
     // rows 2 (aq % 2) and the next of z row aq / 2 of them)
-    if (a_ok) abase = TIME ? block_base(a, pa) + (aq >> 1) * plane + 2 * (aq & 1) * a.nx : patch_base(a, pa) + aq * a.nx;
+    if (a_ok) abase = TIME ? block_base(a, pa) + (aq >> 1) * plane + 2 * (aq & 1) * a.nx : enc_base(a, pa) + aq * a.nx;
     const float* rsrc = a.state + abase;
     // k-step kk: field kk / 16, z level (kk % 16) / 2, y rows 4 (kk % 2) .. + 3. Steps past
     // the last reload the last one, so every step issues the same loads.
@@ -437,7 +445,7 @@ __global__ void __launch_bounds__(NT) encode_few_kernel(const EncArgs a, float* 
     for (int t = 0; t < TI; ++t) {
         const long long pa = m0 + t * 16 + fr;
         ok[t] = pa < a.P;
-        const float* src = a.state + (ok[t] ? patch_base(a, pa) : 0);
+        const float* src = a.state + (ok[t] ? enc_base(a, pa) : 0);
 #pragma unroll
         for (int q = 0; q < NP; ++q) {
             const int r = 32 * (q & 1) + 4 * wave + (lane >> 4);  // row within the field
@@ -973,16 +981,36 @@ EncPlan fused_encode_plan(long long P, bool can_split)
     return ENC_TILED;
 }
 
+// One launch for two sets of P patches where that takes fewer rounds of work-groups over the 256 CUs, and
+// for the tiled kernel, whose rounds are whole at most by chance. Gradients of 100 steps, in two
+// launches / in one, ms: 2 x 96^3 FP8 8.4 / 7.2, 128^3 9.0 / 7.6, 160^3 (one round of 250, or two) 11.9 / 12.5;
+// 256^3 x 160 54.0 / 52.8, 4 x 128 x 192 x 256 x 96 FP8 (two rounds each, or three) 48.6 / 45.4.
+bool fused_encode_two(long long P)
+{
+    auto rounds = [](long long n, EncPlan plan) {
+        const long long wgs = plan == ENC_TILED      ? (n + BM - 1) / BM
+                              : plan == ENC_FEW_PAIR ? (n + 31) / 32
+                                                     : (n + 15) / 16 * (plan == ENC_FEW_SPLIT ? 4 : 1);
+        return (wgs + 255) / 256;
+    };
+    const EncPlan one = fused_encode_plan(P, true), two = fused_encode_plan(2 * P, true);
+    return one == ENC_TILED || rounds(2 * P, two) < 2 * rounds(P, one);
+}
+
 void fused_encode(EncPlan plan, const PatchGrid& pg, int nsrc, const float* state, float* meta, const float* mm, int H,
                   const float* beta, const uint16_t* w1p, const float* b1, const uint16_t* w2t, const float* b2,
                   uint16_t* zbf, uint8_t* codes, float* scale, float* zpart, hipStream_t st, uint16_t* meta16,
-                  LatentSums* defer)
+                  LatentSums* defer, const float* state2)
 {
     WV_REQUIRE(!meta16 || mm, WV_EINVAL, "16-bit metadata is written from the step's (min, max) partials");
     WV_REQUIRE(zbf || (codes && scale), WV_EINVAL, "encode: null latent buffer");
     const long long N = (long long)pg.nz * pg.ny * pg.nx;
-    const EncArgs a{state, meta, meta16, mm, H, beta, w1p, b1, w2t, b2, zbf, codes, scale, fused_patches(pg, nsrc), N, pg.P, 4 * N,
+    EncArgs a{state, meta, meta16, mm, H, beta, w1p, b1, w2t, b2, zbf, codes, scale, fused_patches(pg, nsrc), N, pg.P, 4 * N,
                     pg.ny, pg.nx, pg.ny / 8, pg.nx / 8, 0, 0};
+    if (state2) {
+        a.half = a.P / 2;
+        a.delta = ((intptr_t)state2 - (intptr_t)state) / (intptr_t)sizeof(float) - nsrc / 2 * a.sstride;
+    }
     switch (plan) {
     case ENC_FEW_SPLIT:
         WV_REQUIRE(zpart, WV_EINVAL, "encode: null work buffer");

@@ -66,9 +66,11 @@ void ae_encode_state(const ae_net* net, const PatchGrid& pg, const float* state,
 // r up to bfloat16 before the normalisation uses them.
 // defer (optional): where the latents' last sums would be a launch of their own they are left in
 // *defer, for a launch that the caller queues next on st (exceptions_select).
+// state2 (optional): a second set of nsrc states, whose partials, latents, metadata and scales follow
+// the first set's.
 void ae_encode_states_mm(const ae_net* net, const PatchGrid& pg, int nsrc, const float* state, const float* mm, int H,
                          int fmt, void* latent, float* meta, float* qscale, hipStream_t st,
-                         uint16_t* meta16 = nullptr, LatentSums* defer = nullptr);
+                         uint16_t* meta16 = nullptr, LatentSums* defer = nullptr, const float* state2 = nullptr);
 // Exception patches of a stored state, per source: K patch indices in increasing order,
 // their exact e values [K][512] ((lz, ly, lx) order), and rng [ceil(P/DEC_BM) + 1]:
 // the exceptions of patches [DEC_BM b, DEC_BM b + DEC_BM) are idx[rng[b] .. rng[b+1]).
@@ -101,6 +103,8 @@ void fused_pack(const uint16_t* w, int rows, int K, uint16_t* out, hipStream_t s
 enum EncPlan { ENC_TILED = 0, ENC_FEW_SPLIT = 1, ENC_FEW = 2, ENC_FEW_PAIR = 3 };
 inline bool encode_splits(EncPlan p) { return p == ENC_FEW_SPLIT; }
 EncPlan fused_encode_plan(long long P, bool can_split);
+// whether two sets of P patches are better encoded by one launch
+bool fused_encode_two(long long P);
 // nsrc states 4 N floats apart, everything else contiguous over the sources. meta: output,
 // from the partial (min, max) table mm [P][H][4][2] of the forward step when given
 // (r = max(max - min, beta_f)), else from the state; ENC_TILED without mm takes meta as its
@@ -109,7 +113,7 @@ EncPlan fused_encode_plan(long long P, bool can_split);
 void fused_encode(EncPlan plan, const PatchGrid& pg, int nsrc, const float* state, float* meta, const float* mm, int H,
                   const float* beta, const uint16_t* w1p, const float* b1, const uint16_t* w2t, const float* b2,
                   uint16_t* zbf, uint8_t* codes, float* scale, float* zpart, hipStream_t st, uint16_t* meta16,
-                  LatentSums* defer);
+                  LatentSums* defer, const float* state2 = nullptr);
 // latents z, or codes and scale (z null); exc (field 0 only): exception patches written with
 // their exact values.
 // grid > 0: the decode is queued as launches of at most grid work-groups, one after the

@@ -868,15 +868,17 @@ hipStream_t side_stream(wv_ctx* c, int which);
 // encode x_n of every source into the autoencoder store L on stream st, with the
 // per-patch (min, max) partials mm of the step that wrote it when given (else the
 // encode computes them)
-// (defer: as in ae_encode_states_mm; H partials per patch, 0: the single steps' c->H)
+// (defer: as in ae_encode_states_mm; H partials per patch, 0: the single steps' c->H;
+// state2: x_{n+1}, stored in the same launch)
 void encode_state_into(wv_ctx* c, LatStore& L, int n, const float* state, hipStream_t st, const float* mm,
-                       LatentSums* defer = nullptr, int H = 0)
+                       LatentSums* defer = nullptr, int H = 0, const float* state2 = nullptr)
 {
     const PatchGrid pg = patch_grid(c->g.nz, c->g.ny, c->g.nx);
-    const int te = c->tm.begin(TM_ENCODE, st);
+    const int te = c->tm.begin(TM_ENCODE, st, state2 ? 2 : 1);
     if (mm) {
         ae_encode_states_mm(c->ae, pg, c->S, state, mm, H ? H : c->H, ae_fmt(c->mode), lat_slot(c, L, n - 1, 0),
-                            meta_slot(c, L, n - 1, 0), qs_slot(c, L, n - 1, 0), st, meta16_slot(c, L, n - 1, 0), defer);
+                            meta_slot(c, L, n - 1, 0), qs_slot(c, L, n - 1, 0), st, meta16_slot(c, L, n - 1, 0), defer,
+                            state2);
     } else {
         WV_REQUIRE(!c->m16, WV_EINVAL, "16-bit metadata needs the step's (min, max) partials");
         for (int s = 0; s < c->S; ++s)
@@ -1000,8 +1002,10 @@ bool store_side(wv_ctx* c) { return side_stream(c, c->K > 0 ? 1 : 0) != c->st; }
 
 // Autoencoder store of x_j (1 <= j <= T-1) written by the forward step just
 // launched on the main stream, with its min/max partials in mm: encode on `side`,
-// exception selection and copy on `side2`; ev_stored[b] marks the end (b: x_j's state buffer).
-void store_state_async(wv_ctx* c, int j, const float* state, const float* mm, int b, int H = 0)
+// exception selection and copy on `side2`; ev_stored[b] marks the end (b: x_j's state buffer). With
+// state2, x_{j+1} (buffer b2, partials after x_j's) is stored by the same launches.
+void store_state_async(wv_ctx* c, int j, const float* state, const float* mm, int b, int H = 0,
+                       const float* state2 = nullptr, int b2 = -1)
 {
     const PatchGrid pg = patch_grid(c->g.nz, c->g.ny, c->g.nx);
     hipStream_t s1 = side_stream(c, 0), s2 = side_stream(c, 1);
@@ -1010,28 +1014,34 @@ void store_state_async(wv_ctx* c, int j, const float* state, const float* mm, in
     // stay in the stream's work buffer until then)
     LatentSums fin{};
     const bool join = c->K > 0 && s1 == s2 && exceptions_few(c->P);
-    encode_state_into(c, c->fs, j, state, s1, mm, join ? &fin : nullptr, H);
+    encode_state_into(c, c->fs, j, state, s1, mm, join ? &fin : nullptr, H, state2);
     if (c->K <= 0) {
-        if (s1 != c->st) WV_HIP(hipEventRecord(c->ev_stored[b], s1));
+        if (s1 != c->st)
+            for (int e : {b, b2})
+                if (e >= 0) WV_HIP(hipEventRecord(c->ev_stored[e], s1));
         return;
     }
     order_after(s2, s1, c->ev_enc[b]);
-    const int tx = c->tm.begin(TM_EXC_SELECT, s2);
-    for (int s = 0; s < c->S; ++s) {
+    const int nst = state2 ? 2 : 1;  // the states' slots follow each other
+    auto of = [&](int s) { return (s < c->S ? state : state2) + (long long)(s % c->S) * 4 * c->N; };
+    const int tx = c->tm.begin(TM_EXC_SELECT, s2, nst);
+    for (int s = 0; s < nst * c->S; ++s) {
         const long long q = (long long)(j - 1) * c->S + s;
-        exceptions_select(pg, state + s * 4 * c->N, meta_slot(c, c->fs, j - 1, s), c->K, c->fs.exc_idx + q * c->K,
+        exceptions_select(pg, of(s), meta_slot(c, c->fs, j - 1, s), c->K, c->fs.exc_idx + q * c->K,
                           DEC_BM, rng_slot(c, c->fs, q), c->fs.exc + q * c->K * 512, s2,
                           meta16_slot(c, c->fs, j - 1, s), s == 0 ? &fin : nullptr);
     }
     c->tm.end(tx, s2);
-    const int tg = c->tm.begin(TM_EXC_GATHER, s2);
-    for (int s = 0; s < c->S; ++s) {
+    const int tg = c->tm.begin(TM_EXC_GATHER, s2, nst);
+    for (int s = 0; s < nst * c->S; ++s) {
         const long long q = (long long)(j - 1) * c->S + s;
-        exceptions_gather(pg, state + s * 4 * c->N, c->K, c->fs.exc_idx + q * c->K, c->fs.exc + q * c->K * 512,
+        exceptions_gather(pg, of(s), c->K, c->fs.exc_idx + q * c->K, c->fs.exc + q * c->K * 512,
                           s2);
     }
     c->tm.end(tg, s2);
-    if (s2 != c->st) WV_HIP(hipEventRecord(c->ev_stored[b], s2));
+    if (s2 != c->st)
+        for (int e : {b, b2})
+            if (e >= 0) WV_HIP(hipEventRecord(c->ev_stored[e], s2));
 }
 
 // make the main stream wait for everything queued on the side streams
@@ -1291,7 +1301,7 @@ float* forward_sweep(wv_ctx* c, float* traces, const std::vector<int>* snap, flo
     float* cur = c->work[0];
     float* prev = cur;
     const int ncap = (capture && every > 0) ? (c->T - 1) / every : 0;
-    const long long mm_stride = (long long)c->S * c->P * std::max(c->H, 8) * 8;
+    const long long mm_stride = (long long)c->S * c->P * std::max(c->H, 8) * 8, mm_pair = (long long)c->S * c->P * 64;
     // two steps per launch where x_{n+1} is not needed whole: no snapshot (x_{T-1} among them) or
     // capture of it, no encode
     auto needed = [&](int j) {
@@ -1311,13 +1321,15 @@ float* forward_sweep(wv_ctx* c, float* traces, const std::vector<int>* snap, flo
             reuse(n + 1);
             reuse(n + 2);
             float *const mid = c->work[(n + 1) % 4], *const out = c->work[(n + 2) % 4];
-            pair_fwd_mid(c, cur, mid, out, n, traces, c->mmpart + (n + 1) % 4 * mm_stride,
-                         c->mmpart + (n + 2) % 4 * mm_stride);
+            // the pair's min/max slots are neighbours: (0, 1) or (2, 3)
+            float* const mm = c->mmpart + n % 4 * mm_stride;
+            pair_fwd_mid(c, cur, mid, out, n, traces, mm, mm + mm_pair);
+            const bool two = fused_encode_two(c->P * c->S);
+            store_state_async(c, n + 1, mid, mm, (n + 1) % 4, 8, two ? out : nullptr, two ? (n + 2) % 4 : -1);
+            if (!two) store_state_async(c, n + 2, out, mm + mm_pair, (n + 2) % 4, 8);
             for (int j = n + 1; j <= n + 2; ++j) {
-                float* const x = c->work[j % 4];
-                store_state_async(c, j, x, c->mmpart + j % 4 * mm_stride, j % 4, 8);
-                guard_check(c, j, x, j % 4);
-                captured(j, x);
+                guard_check(c, j, c->work[j % 4], j % 4);
+                captured(j, c->work[j % 4]);
             }
             prev = mid;
             cur = out;
@@ -1348,7 +1360,7 @@ float* forward_sweep(wv_ctx* c, float* traces, const std::vector<int>* snap, flo
         } else {
             out = (snap && (*snap)[j] > 0) ? c->slot_ptr((*snap)[j]) : other_work(c, cur);
         }
-        float* mm = (ae && store) ? c->mmpart + (j % nbuf) * mm_stride : nullptr;
+        float* mm = (ae && store) ? c->mmpart + ((j - 1) % nbuf) * mm_stride : nullptr;
         // time compression: the step writes e^j straight into its window slot; the
         // buffer held window w - 2, whose compression must have read it. Full storage: into
         // the history (a copy after each step cost the 128 x 128 solve 1.6 us of its 5)

@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("shape,nsrc,nt", [((96, 100, 90), 1, 9), ((96, 96, 96), 1, 8), ((37, 150, 145), 1, 10),
-                                           ((62, 50, 260), 1, 9), ((40, 104, 96), 2, 7), ((2, 1000, 500), 1, 6)])
+                                           ((62, 50, 260), 1, 9), ((40, 104, 96), 2, 7), ((2, 1000, 500), 1, 6),
+                                           ((128, 136, 128), 1, 6)])
 def test_paired_steps(shape, nsrc, nt):
     print("case", shape, nsrc, nt, flush=True)
     nz, ny, nx = shape
@@ -64,5 +65,20 @@ def test_paired_steps(shape, nsrc, nt):
         assert J == J0 and torch.equal(g, g0)
         assert torch.equal(ae.hessvec(p.c_start, dc), H0)
         assert torch.equal(ae.hessvec(p.c_start, dc, gauss_newton=False), F0)
+        # latents only: the stored e is the codec's round trip of the state
+        L.wv_set_ae_exceptions(ae.ctx, 0)
+        net = Autoencoder(W.ae_init(2048, 512, 32, seed=4))
+        P = nz * ny * nx // 512
+        z, m = torch.empty((P, 32), dtype=torch.int16, device="cuda"), torch.empty((P, 4, 2), device="cuda")
+        q, out = torch.empty(P, device="cuda"), torch.zeros((4,) + shape, device="cuda")
+        for mode, fmt in ((L.STORE_AE_BF16, L.LATENT_BF16), (L.STORE_AE_FP8, L.LATENT_FP8)):
+            ae.set_storage(mode, ae=net)
+            ae.forward(p.c_start, p.wavelet)
+            for n in range(1, nt):
+                got = ae.load_e(n)
+                for s in range(nsrc):
+                    L.ae_encode(net.handle, ae.grid, cap[n - 1, s].contiguous(), fmt, z, m, q)
+                    L.ae_decode(net.handle, ae.grid, z, m, q, fmt, 1, out)
+                    assert torch.equal(got[s], out[0]), (mode, n, s)
         ae.close()
     full.close()
