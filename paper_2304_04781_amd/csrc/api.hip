@@ -1069,17 +1069,18 @@ float* ebuf_slot(wv_ctx* c, int b) { return c->ebuf + (long long)b * c->S * c->N
 
 // decode the fields in mask of stored state n of every source from the AE store L
 // into out (per-source stride `stride` floats; field f at + f N) on stream st, in
-// launches of at most grid work-groups (0: one launch per field)
+// launches of at most grid work-groups (0: one launch per field); nst states from n on, the
+// sources of each after those of the one before
 void decode_state(wv_ctx* c, const LatStore& L, int n, uint32_t mask, float* out, long long stride,
-                  hipStream_t st, long long grid = 0)
+                  hipStream_t st, long long grid = 0, int nst = 1)
 {
-    WV_REQUIRE(n >= 1 && n <= c->T - 1, WV_ESTATE, "stored state index out of range");
+    WV_REQUIRE(n >= 1 && n + nst - 1 <= c->T - 1, WV_ESTATE, "stored state index out of range");
     const PatchGrid pg = patch_grid(c->g.nz, c->g.ny, c->g.nx);
     // the exception patches of e are written with their exact values by the decode
     const long long q = (long long)(n - 1) * c->S;
     const ExcPatches ex{L.exc_idx + q * c->K, c->K, L.exc + q * c->K * 512, c->K > 0 ? rng_slot(c, L, q) : nullptr};
-    const int td = c->tm.begin(TM_DECODE, st);
-    ae_decode_states(c->ae, pg, c->S, lat_slot(c, L, n - 1, 0), meta_slot(c, L, n - 1, 0), qs_slot(c, L, n - 1, 0),
+    const int td = c->tm.begin(TM_DECODE, st, nst);
+    ae_decode_states(c->ae, pg, nst * c->S, lat_slot(c, L, n - 1, 0), meta_slot(c, L, n - 1, 0), qs_slot(c, L, n - 1, 0),
                      ae_fmt(c->mode), mask, out, stride, st, c->K > 0 ? &ex : nullptr, meta16_slot(c, L, n - 1, 0),
                      grid);
     c->tm.end(td, st);
@@ -1162,6 +1163,16 @@ void pipe_issue(wv_ctx* c, int n, int b)
     if (s1 != c->st) wait_event(s1, c->ev_free[b]);
     decode_e(c, n, b, s1, c->pipe_grid);
     if (s1 != c->st) WV_HIP(hipEventRecord(c->ev_ready[b], s1));
+}
+// the decodes of e^n and e^{n+1} into the slots b and b + 1, in one launch
+void pipe_issue_two(wv_ctx* c, int n, int b)
+{
+    hipStream_t s1 = side_stream(c, 0);
+    for (int q = b; q < b + 2; ++q)
+        if (s1 != c->st) wait_event(s1, c->ev_free[q]);
+    decode_state(c, c->fs, n, 1u, ebuf_slot(c, b), c->N, s1, c->pipe_grid, 2);
+    for (int q = b; q < b + 2; ++q)
+        if (s1 != c->st) WV_HIP(hipEventRecord(c->ev_ready[q], s1));
 }
 const float* pipe_take(wv_ctx* c, int b)
 {
@@ -1401,22 +1412,33 @@ void reverse_sweep(wv_ctx* c, const float* resid, const std::vector<RevAction>* 
         std::swap(ain, aout);
     };
     if (!acts && is_ae(c->mode) && c->pair.use) {
-        // two steps per launch; e^{k-2} and e^{k-3} are decoded beside the steps k and k - 1
-        static_assert(NEB >= 4, "two pairs of decoded states");
+        // two steps per launch; e^{k-2} and e^{k-3} are decoded beside the steps k and k - 1. A pair's slots are neighbours: (0, 1) or (2, 3)
+        static_assert(NEB >= 4 && NEB % 2 == 0, "two pairs of decoded states");
         pipe_start(c, PAIR_DEC_GRID);
-        for (int n = c->T - 1; n >= std::max(1, c->T - 2); --n) pipe_issue(c, n, n % NEB);
+        auto slot = [&](int n) { return (n + c->T % 2) % NEB; };
+        // In order, one launch has fewer rounds of work-groups than two; beside the steps of large grids
+        // it costs fewer events, beside those of small ones the first step waits for both decodes.
+        // Two launches / one, ms: 4 sources of 128 x 192 x 256 45.4 / 44.8, 2 x 96^3 7.2 / 6.9, 256^3
+        // 52.8 / 51.8; 160^3 (8000 patches) 11.9 / 12.4, 128^3 7.7 / 8.0
+        const bool two = side_stream(c, 0) == c->st || c->P * c->S >= 16384;
+        auto issue = [&](int k) {
+            if (k >= 2 && two) pipe_issue_two(c, k - 1, slot(k - 1));
+            else
+                for (int n = k; n >= std::max(1, k - 1); --n) pipe_issue(c, n, slot(n));
+        };
+        issue(c->T - 1);
         for (int k = c->T - 1; k >= 1; k -= 2) {
-            for (int n = k - 2; n >= std::max(1, k - 3); --n) pipe_issue(c, n, n % NEB);
+            issue(k - 2);
             if (k >= 2) {
-                const float* e1 = pipe_take(c, k % NEB);
-                pair_adj(c, ain, aout, k, resid, e1, pipe_take(c, (k - 1) % NEB), c->N, done);
+                const float* e1 = pipe_take(c, slot(k));
+                pair_adj(c, ain, aout, k, resid, e1, pipe_take(c, slot(k - 1)), c->N, done);
                 std::swap(ain, aout);
                 done += 2;
-                pipe_release(c, (k - 1) % NEB);
+                pipe_release(c, slot(k - 1));
             } else {
-                adjoint_k(k, pipe_take(c, k % NEB), c->N);
+                adjoint_k(k, pipe_take(c, slot(k)), c->N);
             }
-            pipe_release(c, k % NEB);
+            pipe_release(c, slot(k));
         }
         return;
     }
