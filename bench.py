@@ -343,9 +343,10 @@ def multisource_rates(args, p, net, c0, wav):
     kt = timed_kernels(ae, c0, w, d, 1.0, every=2)
     ae.close()
     blk = L.wv_accumulation_block()
-    work = {  # per timed launch (every class launches all sources at once)
-        "forward_stencil": ("hbm", (32.0 * S + 4.0) * N),
-        "adjoint_stencil": ("hbm", ((adjoint_bytes_per_cell(T, blk) - 4.0) * S + 4.0) * N),
+    fwd_b, adj_b = paired_bytes_per_cell(T, blk, S)
+    work = {  # per step (every class launches all sources at once, the stencils two steps)
+        "forward_stencil": ("hbm", fwd_b * N),
+        "adjoint_stencil": ("hbm", adj_b * N),
         "encode": ("mfma", S * 2.0 * P * (2048 * 512 + 512 * 32)),
         "decode_e": ("mfma", S * 2.0 * P * (32 * 512 + 512 * 512)),
     }
@@ -947,9 +948,11 @@ def main():
     log(f"device copy {copy_gbs:.0f} GB/s; streaming probe {probe}")
 
     # ---- rooflines: algorithmic bytes (flops) per launch over the measured mean launch duration
+    # (the stencils take two steps per launch here: their bytes and times are per step)
+    fwd_b, adj_b = paired_bytes_per_cell(T, L.wv_accumulation_block())
     per_launch = {
-        "forward_stencil": ("hbm", 36.0 * N),                          # read 4 fields + m, write 4 fields
-        "adjoint_stencil": ("hbm", adjoint_bytes_per_cell(T, L.wv_accumulation_block()) * N),
+        "forward_stencil": ("hbm", fwd_b * N),
+        "adjoint_stencil": ("hbm", adj_b * N),
         "encode": ("mfma", 2.0 * P * (2048 * 512 + 512 * 32)),         # two encoder layers
         "decode_e": ("mfma", 2.0 * P * (32 * 512 + 512 * 512)),        # decoder layer 3 + e rows of layer 4
     }
@@ -1047,14 +1050,14 @@ def main():
         "kernels": {k: {kk: round(vv, 4) for kk, vv in v.items()} for k, v in kernels.items()},
         "measured_peaks": {"device_copy_GBps": round(copy_gbs, 1), "library_bf16_gemm_TFLOPs": round(gemm_tf, 1),
                            "streaming_probe_GBps": probe},
-        # the same stencil kernels with the GPU to themselves (no encode or decode beside them)
+        # the stencil kernels with the GPU to themselves (no encode or decode beside them); the recomputed
+        # forward steps come in pairs only where the state between is not a checkpoint
         "checkpoint_kernels": {k: dict({"us": round(us, 2), "timed_launches": n},
                                        **({"GB/s": round(per_launch[k][1] / (us * 1e-6) / 1e9, 1),
                                            "frac_hbm": round(per_launch[k][1] / (us * 1e-6) / 1e9 / HBM_PEAK_GBS, 4),
                                            "frac_of_streaming_mix": round(per_launch[k][1] / (us * 1e-6) / 1e9 / probe[
-                                               "adjoint_mix_7in_5out" if k == "adjoint_stencil"
-                                               else "forward_mix_5in_4out"], 4)}
-                                          if k in per_launch and per_launch[k][0] == "hbm" else {}))
+                                               "adjoint_mix_7in_5out"], 4)}
+                                          if k == "adjoint_stencil" else {}))
                                for k, (us, n) in kt_ck.items() if n},
         "first_gradient_s": round(t_train_total + t_ae, 3),
         "amortized_over_10_gradients_s": round((t_train_total + 10 * t_ae) / 10, 4),
@@ -1170,6 +1173,24 @@ def adjoint_bytes_per_cell(T, block):
         first, last = j % block == 0, j % block == block - 1 or j == steps - 1
         total += 40.0 + (16.0 if first and last else 4.0 if first else 20.0 if last else 8.0)
     return total / max(steps, 1)
+
+
+def paired_bytes_per_cell(T, block, nsrc=1):
+    """(forward, adjoint): mean algorithmic bytes per cell and step of the T forward and T-1
+    adjoint steps of nsrc sources, two steps per launch with both forward states written (c^2 read once
+    per launch). Forward: 4 fields read, 2 x 4 written. Adjoint: 4 fields read and written, e of two
+    levels, the partial of the pair's place in its accumulation block (written, read and written, or read
+    with the compensated pair read and written). An odd step is taken alone."""
+    pairs = (T - 1) // 2
+    fwd = pairs * (48.0 * nsrc + 4.0) + (T - 2 * pairs) * (32.0 * nsrc + 4.0)
+    adj, j = 0.0, 0
+    while j < T - 1:
+        two = j + 2 <= T - 1
+        end = j + (2 if two else 1)
+        first, last = j % block == 0, end % block == 0 or end == T - 1
+        adj += 4.0 + nsrc * ((40.0 if two else 36.0) + (0.0 if first else 4.0) + (16.0 if last else 4.0))
+        j = end
+    return fwd / T, adj / max(T - 1, 1)
 
 
 def cpu_baseline(p, T, nsteps=20):

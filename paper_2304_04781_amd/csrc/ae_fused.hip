@@ -400,7 +400,7 @@ __global__ void __launch_bounds__(NT) encode_kernel(const EncArgs a)
 
 // Encode of few patches. The tiled kernel above needs a work-group per 128 patches to amortise
 // its reads of W1 (2 MiB per work-group), so a state of a few thousand patches leaves most CUs
-// idle and takes one work-group's whole march (57 us for 420 patches). Here a work-group takes
+// idle and takes one work-group's whole march (57 us for 210 patches). Here a work-group takes
 // 16 TI patches and 128 JW hidden units: the raw rows of its patches are all loaded at once
 // (64 TI registers), normalised and kept in LDS as the whole bfloat16 A operand in fragment
 // order, so the k loop has no barrier and waits only for its W1 fragments, RD k-steps ahead.

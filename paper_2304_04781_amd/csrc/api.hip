@@ -184,16 +184,14 @@ constexpr int NEB = WV_NEB;
 // decode there runs two steps ahead of the adjoint step that reads it, so it may take
 // longer than a step; queued as two launches (384 work-groups, then the rest at 256^3) it
 // holds fewer CUs at a time, and the adjoint step beside it ran 184 us instead of 197.
+// Beside steps in pairs a decode is one launch (a gradient of 256^3 x 160: 50.6 ms; 51.7 in launches of
+// 512 work-groups, 52.6 of 384).
 // The incremental forward sweep of a Hessian action keeps one launch (its decodes run
 // beside the encodes of the incremental states, and sliced they ran slower).
 #ifndef WV_REV_DEC_GRID
 #define WV_REV_DEC_GRID 384
 #endif
 constexpr long long REV_DEC_GRID = WV_REV_DEC_GRID;
-#ifndef WV_PAIR_DEC_GRID
-#define WV_PAIR_DEC_GRID 0
-#endif
-constexpr long long PAIR_DEC_GRID = WV_PAIR_DEC_GRID;  // the same beside steps in pairs
 
 // Latent store of the states x_1 .. x_{T-1} of every source (AE modes): latents,
 // per-patch metadata, FP8 scales and the exact e values of the exception patches
@@ -1414,7 +1412,7 @@ void reverse_sweep(wv_ctx* c, const float* resid, const std::vector<RevAction>* 
     if (!acts && is_ae(c->mode) && c->pair.use) {
         // two steps per launch; e^{k-2} and e^{k-3} are decoded beside the steps k and k - 1. A pair's slots are neighbours: (0, 1) or (2, 3)
         static_assert(NEB >= 4 && NEB % 2 == 0, "two pairs of decoded states");
-        pipe_start(c, PAIR_DEC_GRID);
+        pipe_start(c);
         auto slot = [&](int n) { return (n + c->T % 2) % NEB; };
         // In order, one launch has fewer rounds of work-groups than two; beside the steps of large grids
         // it costs fewer events, beside those of small ones the first step waits for both decodes.
